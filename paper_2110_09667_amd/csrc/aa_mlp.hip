@@ -1,13 +1,13 @@
 // aa_mlp.hip -- the mixing-weight network of the learned-guarded AA step.
 //
 // 230 -> 256 -> 256 -> 256 -> 21 (padded to 256 in / 64 out), GELU (erf form),
-// BF16 operands on the matrix cores with FP32 accumulation, FP32 master
-// weights, Adam.  Everything is a dense contraction here, so every product is
-// one LDS-tiled GEMM on gfx950's v_mfma_f32_16x16x32_bf16 (64 x 64 tile per
-// workgroup, one 16-row strip per wave, K in steps of 32: half the MFMA
-// issues and LDS passes of the 16-deep form); operand strides let the same kernel compute
-// the forward products, the input gradients (times W^T) and the weight
-// gradients (H^T times dZ).  The network is small and latency-bound.
+// BF16 operands on the matrix cores (gfx950's v_mfma_f32_16x16x32_bf16) with
+// FP32 accumulation, FP32 master weights, Adam.  The network is small and its
+// layers depend on each other, so what bounds it is launches and the latency
+// of each, not the matrix cores: a forward pass is one launch (k_mlp_forward,
+// 16 rows per workgroup, activations in LDS, weights straight from the L2 in
+// operand order), a backward pass two (k_mlp_backward: the chain of dZ;
+// k_mlp_grads: every weight and bias gradient).
 #include <math.h>
 #include <stdint.h>
 #include <string.h>
@@ -36,73 +36,15 @@ __device__ __forceinline__ float bf2f(uint16_t b) { return __uint_as_float((uint
 // register r of its result holds D[mfma_row(l, r)][l % 16].
 __device__ __forceinline__ int mfma_row(int lane, int r) { return 4 * (lane >> 4) + r; }
 
-struct GemmArgs {
-  const uint16_t* a; int64_t sa0, sa1;  // A(m, k) = a[m sa0 + k sa1]
-  const uint16_t* b; int64_t sb0, sb1;  // B(k, n) = b[k sb0 + n sb1]
-  float* c; int64_t ldc;                // C(m, n) = c[m ldc + n]
-  const float* bias;                    // added per column (may be null)
-  int M, N, K;
-  int accumulate;                       // C += A B instead of C = A B (+ bias)
-};
+constexpr int kIn = 256, kH = 256, kOutP = 64;
+constexpr int kNF = AA_MLP_FEATURES, kNO = AA_MLP_OUTPUTS;
+constexpr int kLayers = 4;
 
-constexpr int GT = 64;   // tile edge
-constexpr int GK = 32;   // K step of one MFMA
-constexpr int GKP = 40;  // LDS row stride (bf16 elements) of the K-major tiles: 80 bytes,
-                         // 16-byte aligned rows for the 8-element operand reads
-
-__global__ __launch_bounds__(256) void k_gemm_bf16(GemmArgs g) {
-  __shared__ __align__(16) uint16_t As[GT * GKP];  // [m][k]
-  __shared__ __align__(16) uint16_t Bs[GT * GKP];  // [n][k]
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  const int m0 = blockIdx.y * GT, n0 = blockIdx.x * GT;
-  v4f acc[4];
-#pragma unroll
-  for (int nb = 0; nb < 4; ++nb) acc[nb] = v4f{0.f, 0.f, 0.f, 0.f};
-  for (int k0 = 0; k0 < g.K; k0 += GK) {
-#pragma unroll
-    for (int e = tid; e < GT * GK; e += 256) {
-      const int r = e / GK, kk = e % GK;
-      const int m = m0 + r, n = n0 + r, k = k0 + kk;
-      As[r * GKP + kk] = (m < g.M && k < g.K) ? g.a[m * g.sa0 + k * g.sa1] : (uint16_t)0;
-      Bs[r * GKP + kk] = (n < g.N && k < g.K) ? g.b[k * g.sb0 + n * g.sb1] : (uint16_t)0;
-    }
-    __syncthreads();
-    const int ar = 16 * w + (lane & 15), ak = 8 * (lane >> 4);
-    const v8bf af = *reinterpret_cast<const v8bf*>(&As[ar * GKP + ak]);
-#pragma unroll
-    for (int nb = 0; nb < 4; ++nb) {
-      const int bn = 16 * nb + (lane & 15);
-      const v8bf bfr = *reinterpret_cast<const v8bf*>(&Bs[bn * GKP + ak]);
-      acc[nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af, bfr, acc[nb], 0, 0, 0);
-    }
-    __syncthreads();
-  }
-#pragma unroll
-  for (int nb = 0; nb < 4; ++nb)
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int m = m0 + 16 * w + mfma_row(lane, r), n = n0 + 16 * nb + (lane & 15);
-      if (m < g.M && n < g.N) {
-        float v = acc[nb][r];
-        float* p = g.c + m * g.ldc + n;
-        if (g.accumulate)
-          *p += v;
-        else
-          *p = v + (g.bias ? g.bias[n] : 0.f);
-      }
-    }
-}
-
-// out[r][j] = bf16(in[r][j]) for j < ncols_in, 0 for ncols_in <= j < ncols_out.
-__global__ void k_cast_pad(const float* in, int ld_in, int ncols_in, uint16_t* out, int ncols_out,
-                           int rows) {
-  const int64_t tot = (int64_t)rows * ncols_out;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < tot;
-       i += (int64_t)gridDim.x * blockDim.x) {
-    const int r = (int)(i / ncols_out), j = (int)(i % ncols_out);
-    out[i] = j < ncols_in ? f2bf(in[(int64_t)r * ld_in + j]) : (uint16_t)0;
-  }
-}
+// Packed parameters: layer l is W_l (din 256 x dout, row-major) then b_l.
+__host__ __device__ constexpr int layer_out(int l) { return l == kLayers - 1 ? kOutP : kH; }
+__host__ __device__ constexpr int layer_w(int l) { return l * (kH * kH + kH); }
+__host__ __device__ constexpr int layer_b(int l) { return layer_w(l) + kH * layer_out(l); }
+constexpr int kParams = layer_b(kLayers - 1) + kOutP;
 
 __device__ __forceinline__ float gelu_f(float z) { return 0.5f * z * (1.f + erff(z * 0.70710678118654752f)); }
 __device__ __forceinline__ float gelu_grad_f(float z) {
@@ -110,84 +52,307 @@ __device__ __forceinline__ float gelu_grad_f(float z) {
          z * expf(-0.5f * z * z) * 0.39894228040143268f;
 }
 
-// h = bf16(gelu(z))
-__global__ void k_gelu_bf16(const float* z, uint16_t* h, int64_t n) {
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
-       i += (int64_t)gridDim.x * blockDim.x)
-    h[i] = f2bf(gelu_f(z[i]));
+// Rows per workgroup (one MFMA row block), threads (eight waves; wave w owns
+// output columns 32 w .. 32 w + 31 of a hidden layer) and LDS row stride of an
+// activation tile (528 bytes: 16-byte aligned, rows four banks apart).
+constexpr int kRows = 16, kChainWG = 512, kActS = kH + 8;
+
+// Eight consecutive reduction indices of one output column, from a matrix
+// stored with the reduction index fastest (ld elements a column).
+__device__ __forceinline__ v8bf ld_op(const uint16_t* w, int ld, int n, int k) {
+  return *reinterpret_cast<const v8bf*>(w + (size_t)n * ld + k);
 }
 
-// dz = dh * gelu'(z); dzb = bf16(dz)
-__global__ void k_gelu_back(const float* dh, const float* z, float* dz, uint16_t* dzb, int64_t n) {
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
-       i += (int64_t)gridDim.x * blockDim.x) {
-    const float v = dh[i] * gelu_grad_f(z[i]);
-    dz[i] = v;
-    dzb[i] = f2bf(v);
+// acc[nb] = tile (16 x 32 STEPS, LDS) times this wave's operands
+template <int STEPS, int NB>
+__device__ __forceinline__ void mma_tile(const uint16_t (*act)[kActS], const v8bf (&b)[NB][8],
+                                         v4f (&acc)[NB]) {
+  const int lane = threadIdx.x & 63;
+#pragma unroll
+  for (int nb = 0; nb < NB; ++nb) acc[nb] = v4f{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int s = 0; s < STEPS; ++s) {
+    const v8bf af = *reinterpret_cast<const v8bf*>(&act[lane & 15][32 * s + 8 * (lane >> 4)]);
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb)
+      acc[nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af, b[nb][s], acc[nb], 0, 0, 0);
   }
 }
 
-// db[j] += sum_r dz[r][j] (fixed order over r; one thread per column)
-// Bias gradient db[j] += sum_r dz[r][j] in two fixed-order stages: block
-// (x, y) sums columns 64x..64x+63 over the y-th of kColSplit row slices (four
-// row phases per thread, combined in LDS) into part[y][j]; k_colsum_fin adds
-// the kColSplit partial sums in order.
-constexpr int kColSplit = 32;
+struct FwdArgs {
+  const float* x;        // [batch x 230]
+  float* out;            // [batch x 21] or null
+  const uint16_t* wt;    // transposed BF16 weights: W_l^T at layer_w(l)
+  const float* p;        // packed FP32 parameters (biases)
+  uint16_t* h[kLayers];  // layer inputs, kept for the backward pass
+  float* z[kLayers - 1]; // hidden pre-activations, kept
+  int batch;
+};
 
-__global__ __launch_bounds__(256) void k_colsum_part(const float* dz, int rows, int cols,
-                                                     float* part) {
-  __shared__ float red[4][64];
-  const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
-  const int j = blockIdx.x * 64 + tx;
-  const int per = (rows + kColSplit - 1) / kColSplit;
-  const int r0 = blockIdx.y * per, r1 = r0 + per < rows ? r0 + per : rows;
-  float s = 0.f;
-  if (j < cols)
-    for (int r = r0 + ty; r < r1; r += 4) s += dz[(int64_t)r * cols + j];
-  red[ty][tx] = s;
+// The whole forward pass of 16 rows.  Latency bound (16 workgroups at 256
+// rows): a layer is 16 operand loads per lane in flight from the L2, the next
+// layer's issued before this one's activation function, so a layer costs about
+// one L2 round trip plus the GELU.  At 256 rows: 23 us, where the 64 x 64 GEMM
+// tiles and elementwise kernels before it took nine launches and 120 us.
+// (Rolling the layer loop, a third of the code, changed nothing: the weights
+// Adam has just rewritten come from beyond the L2.)
+__global__ __launch_bounds__(kChainWG) void k_mlp_forward(FwdArgs a) {
+  __shared__ __align__(16) uint16_t act[2][kRows][kActS];
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const int r0 = blockIdx.x * kRows, li = lane & 15, lk = 8 * (lane >> 4);
+  v8bf b[2][8];
+  auto load = [&](int l) {
+    if (l == kLayers - 1 && w >= 4) return;
+    const int n0 = l == kLayers - 1 ? 16 * w : 32 * w;
+#pragma unroll
+    for (int nb = 0; nb < 2; ++nb)
+      if (nb == 0 || l < kLayers - 1)
+#pragma unroll
+        for (int s = 0; s < 8; ++s)
+          b[nb][s] = ld_op(a.wt + layer_w(l), kH, n0 + 16 * nb + li, 32 * s + lk);
+  };
+  load(0);
+  for (int e = tid; e < kRows * kIn; e += kChainWG) {
+    const int r = e / kIn, c = e % kIn, row = r0 + r;
+    const uint16_t v = row < a.batch && c < kNF ? f2bf(a.x[(size_t)row * kNF + c]) : (uint16_t)0;
+    act[0][r][c] = v;
+    if (row < a.batch) a.h[0][(size_t)row * kIn + c] = v;
+  }
   __syncthreads();
-  if (ty == 0 && j < cols)
-    part[(size_t)blockIdx.y * cols + j] = (red[0][tx] + red[1][tx]) + (red[2][tx] + red[3][tx]);
-}
-
-__global__ void k_colsum_fin(const float* part, int cols, float* db) {
-  const int j = blockIdx.x * blockDim.x + threadIdx.x;
-  if (j >= cols) return;
-  float s = 0.f;
-  for (int y = 0; y < kColSplit; ++y) s += part[(size_t)y * cols + j];
-  db[j] += s;
-}
-
-// out[r][j] = z[r][j] for j < 21 (network output)
-__global__ void k_take_out(const float* z, int ldz, float* out, int rows, int ncols) {
-  const int64_t tot = (int64_t)rows * ncols;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < tot;
-       i += (int64_t)gridDim.x * blockDim.x)
-    out[i] = z[(i / ncols) * ldz + (i % ncols)];
-}
-
-// Adam on FP32 master weights; clears the gradient; refreshes the BF16 copy.
-__global__ void k_adam(float* p, float* g, float* m, float* v, uint16_t* pb, int64_t n, float lr,
-                       float b1, float b2, float eps, float c1, float c2) {
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
-       i += (int64_t)gridDim.x * blockDim.x) {
-    const float gi = g[i];
-    const float mi = b1 * m[i] + (1.f - b1) * gi;
-    const float vi = b2 * v[i] + (1.f - b2) * gi * gi;
-    m[i] = mi;
-    v[i] = vi;
-    const float upd = lr * (mi / c1) / (sqrtf(vi / c2) + eps);
-    const float pi = p[i] - upd;
-    p[i] = pi;
-    pb[i] = f2bf(pi);
-    g[i] = 0.f;
+#pragma unroll
+  for (int l = 0; l < kLayers - 1; ++l) {
+    v4f acc[2];
+    mma_tile<8, 2>(act[l & 1], b, acc);
+    load(l + 1);
+#pragma unroll
+    for (int nb = 0; nb < 2; ++nb) {
+      const int n = 32 * w + 16 * nb + li;
+      const float bias = a.p[layer_b(l) + n];
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int rr = mfma_row(lane, r), row = r0 + rr;
+        const float z = acc[nb][r] + bias;
+        const uint16_t hv = f2bf(gelu_f(z));
+        act[(l + 1) & 1][rr][n] = hv;
+        if (row < a.batch) {
+          a.z[l][(size_t)row * kH + n] = z;
+          a.h[l + 1][(size_t)row * kH + n] = hv;
+        }
+      }
+    }
+    __syncthreads();
+  }
+  if (w >= 4 || !a.out) return;
+  v4f acc[1];
+  v8bf bl[1][8];
+#pragma unroll
+  for (int s = 0; s < 8; ++s) bl[0][s] = b[0][s];
+  mma_tile<8, 1>(act[(kLayers - 1) & 1], bl, acc);
+  const int n = 16 * w + li;
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    const int row = r0 + mfma_row(lane, r);
+    if (row < a.batch && n < kNO)
+      a.out[(size_t)row * kNO + n] = acc[0][r] + a.p[layer_b(kLayers - 1) + n];
   }
 }
 
-__global__ void k_to_bf16(const float* p, uint16_t* pb, int64_t n) {
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
-       i += (int64_t)gridDim.x * blockDim.x)
-    pb[i] = f2bf(p[i]);
+struct BwdArgs {
+  const float* dout;           // [batch x 21]
+  const uint16_t* wb;          // BF16 weights, packed as the parameters
+  const float* z[kLayers - 1]; // hidden pre-activations
+  float* dz[kLayers];          // FP32 gradients of the pre-activations (bias sums)
+  uint16_t* dzb[kLayers];      // their BF16 copies (weight gradients)
+  int batch;
+};
+
+// The chain dZ_3 -> dZ_0 of 16 rows: dH = dZ_l W_l^T (W_l's rows have the
+// reduction index fastest), dZ_{l-1} = dH gelu'(z_{l-1}).  As the forward pass;
+// 16 us at 256 rows, 86 us as seven launches.
+__global__ __launch_bounds__(kChainWG) void k_mlp_backward(BwdArgs a) {
+  __shared__ __align__(16) uint16_t act[2][kRows][kActS];
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const int r0 = blockIdx.x * kRows, li = lane & 15, lk = 8 * (lane >> 4);
+  v8bf b[2][8];
+  auto load = [&](int l) {
+#pragma unroll
+    for (int nb = 0; nb < 2; ++nb)
+#pragma unroll
+      for (int s = 0; s < 8; ++s)
+        if (s < layer_out(l) / 32)
+          b[nb][s] = ld_op(a.wb + layer_w(l), layer_out(l), 32 * w + 16 * nb + li, 32 * s + lk);
+  };
+  load(kLayers - 1);
+  for (int e = tid; e < kRows * kOutP; e += kChainWG) {
+    const int r = e / kOutP, c = e % kOutP, row = r0 + r;
+    const float v = row < a.batch && c < kNO ? a.dout[(size_t)row * kNO + c] : 0.f;
+    act[1][r][c] = f2bf(v);
+    if (row < a.batch) {
+      a.dz[kLayers - 1][(size_t)row * kOutP + c] = v;
+      a.dzb[kLayers - 1][(size_t)row * kOutP + c] = f2bf(v);
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int l = kLayers - 1; l >= 1; --l) {
+    float zv[2][4];
+#pragma unroll
+    for (int nb = 0; nb < 2; ++nb)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int row = r0 + mfma_row(lane, r), n = 32 * w + 16 * nb + li;
+        zv[nb][r] = row < a.batch ? a.z[l - 1][(size_t)row * kH + n] : 0.f;
+      }
+    v4f acc[2];
+    if (l == kLayers - 1)
+      mma_tile<kOutP / 32, 2>(act[l & 1], b, acc);
+    else
+      mma_tile<kH / 32, 2>(act[l & 1], b, acc);
+    if (l > 1) load(l - 1);
+#pragma unroll
+    for (int nb = 0; nb < 2; ++nb)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int rr = mfma_row(lane, r), row = r0 + rr, n = 32 * w + 16 * nb + li;
+        const float v = acc[nb][r] * gelu_grad_f(zv[nb][r]);
+        const uint16_t vb = f2bf(v);
+        act[(l - 1) & 1][rr][n] = vb;
+        if (row < a.batch) {
+          a.dz[l - 1][(size_t)row * kH + n] = v;
+          a.dzb[l - 1][(size_t)row * kH + n] = vb;
+        }
+      }
+    __syncthreads();
+  }
+}
+
+// Every gradient in one launch: dW_l += H_l^T dZ_l as 32 x 32 tiles (64 per
+// hidden layer: 208 workgroups, where 64 x 64 tiles gave 16 a layer), one
+// 16 x 16 block per wave, the batch in steps of 64 rows staged transposed in
+// LDS with the next step's 16-byte loads in flight; then the bias gradients,
+// 16 columns a workgroup.  The batch index runs in order in every sum.  At 256
+// rows 8.3 us; twelve launches took 130 us.
+constexpr int kGT = 32, kGK = 64, kGS = kGK + 8;
+constexpr int kHidTiles = (kH / kGT) * (kH / kGT);
+constexpr int kOutTiles = (kH / kGT) * (kOutP / kGT);
+constexpr int kWTiles = (kLayers - 1) * kHidTiles + kOutTiles;
+constexpr int kBiasCols = 16;
+constexpr int kBTiles = ((kLayers - 1) * kH + kOutP) / kBiasCols;
+constexpr int kColSplit = 32;  // row slices of a bias sum, four row phases each
+
+struct GradArgs {
+  const uint16_t* h[kLayers];
+  const uint16_t* dzb[kLayers];
+  const float* dz[kLayers];
+  float* g;
+  int batch;
+};
+
+// db[j] += sum_r dz[r][j]: slice sums (four phases combined as a tree), then
+// the slices in order.
+__device__ void bias_tile(const GradArgs& a, int t) {
+  __shared__ float part[kColSplit][4][kBiasCols];
+  const int per_l = kH / kBiasCols;
+  const int l = t / per_l < kLayers - 1 ? t / per_l : kLayers - 1;
+  const int j0 = (t - l * per_l) * kBiasCols, cols = layer_out(l);
+  const int per = (a.batch + kColSplit - 1) / kColSplit;
+  const int c = threadIdx.x % kBiasCols;
+  for (int i = threadIdx.x / kBiasCols; i < 4 * kColSplit; i += 256 / kBiasCols) {
+    const int y = i >> 2, ph = i & 3;
+    const int b0 = y * per, b1 = b0 + per < a.batch ? b0 + per : a.batch;
+    float s = 0.f;
+    for (int r = b0 + ph; r < b1; r += 4) s += a.dz[l][(size_t)r * cols + j0 + c];
+    part[y][ph][c] = s;
+  }
+  __syncthreads();
+  if (threadIdx.x < kBiasCols) {
+    float s = 0.f;
+    for (int y = 0; y < kColSplit; ++y)
+      s += (part[y][0][c] + part[y][1][c]) + (part[y][2][c] + part[y][3][c]);
+    a.g[layer_b(l) + j0 + c] += s;
+  }
+}
+
+__global__ __launch_bounds__(256) void k_mlp_grads(GradArgs a) {
+  if (blockIdx.x >= kWTiles) {
+    bias_tile(a, blockIdx.x - kWTiles);
+    return;
+  }
+  __shared__ __align__(16) uint16_t As[kGT][kGS], Bs[kGT][kGS];  // [column][batch row]
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const int l = blockIdx.x / kHidTiles, t = blockIdx.x % kHidTiles;
+  const int N = layer_out(l), nt = N / kGT;
+  const int m0 = t / nt * kGT, n0 = t % nt * kGT;
+  // this thread's 16 bytes of a step: row tid / 4, columns 8 (tid % 4) ...
+  const int sr = tid >> 2, sc = 8 * (tid & 3);
+  uint4 va, vb;
+  auto fetch = [&](int k0) {
+    const int r = k0 + sr;
+    va = vb = uint4{0u, 0u, 0u, 0u};
+    if (r < a.batch) {
+      va = *reinterpret_cast<const uint4*>(a.h[l] + (size_t)r * kH + m0 + sc);
+      vb = *reinterpret_cast<const uint4*>(a.dzb[l] + (size_t)r * N + n0 + sc);
+    }
+  };
+  v4f acc = v4f{0.f, 0.f, 0.f, 0.f};
+  const int mb = 16 * (w >> 1), nb = 16 * (w & 1), li = lane & 15, lk = 8 * (lane >> 4);
+  fetch(0);
+  for (int k0 = 0; k0 < a.batch; k0 += kGK) {
+    const uint32_t pa[4] = {va.x, va.y, va.z, va.w}, pv[4] = {vb.x, vb.y, vb.z, vb.w};
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      As[sc + e][sr] = (uint16_t)(pa[e >> 1] >> (16 * (e & 1)));
+      Bs[sc + e][sr] = (uint16_t)(pv[e >> 1] >> (16 * (e & 1)));
+    }
+    __syncthreads();
+    if (k0 + kGK < a.batch) fetch(k0 + kGK);
+#pragma unroll
+    for (int s = 0; s < kGK; s += 32) {
+      const v8bf af = *reinterpret_cast<const v8bf*>(&As[mb + li][s + lk]);
+      const v8bf bf = *reinterpret_cast<const v8bf*>(&Bs[nb + li][s + lk]);
+      acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af, bf, acc, 0, 0, 0);
+    }
+    __syncthreads();
+  }
+#pragma unroll
+  for (int r = 0; r < 4; ++r)
+    a.g[layer_w(l) + (size_t)(m0 + mb + mfma_row(lane, r)) * N + n0 + nb + li] += acc[r];
+}
+
+// BF16 copies of parameter i: packed, and (weights) transposed for the
+// forward operands.
+__device__ __forceinline__ void put_bf16(uint16_t* pb, uint16_t* wt, int i, float v) {
+  const uint16_t q = f2bf(v);
+  pb[i] = q;
+  const int l = i / layer_w(1) < kLayers - 1 ? i / layer_w(1) : kLayers - 1;
+  const int e = i - layer_w(l), N = layer_out(l);
+  if (e < kH * N) wt[layer_w(l) + (e % N) * kH + e / N] = q;
+}
+
+// Adam on FP32 master weights; clears the gradient; refreshes the BF16 copies.
+__global__ void k_adam(float* p, float* g, float* m, float* v, uint16_t* pb, uint16_t* wt,
+                       float lr, float b1, float b2, float eps, float c1, float c2) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= kParams) return;
+  const float gi = g[i];
+  const float mi = b1 * m[i] + (1.f - b1) * gi;
+  const float vi = b2 * v[i] + (1.f - b2) * gi * gi;
+  m[i] = mi;
+  v[i] = vi;
+  const float upd = lr * (mi / c1) / (sqrtf(vi / c2) + eps);
+  const float pi = p[i] - upd;
+  p[i] = pi;
+  put_bf16(pb, wt, i, pi);
+  g[i] = 0.f;
+}
+
+// Gradients and moments cleared, BF16 copies refreshed.
+__global__ void k_reset(const float* p, float* g, float* m, float* v, uint16_t* pb,
+                        uint16_t* wt) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= kParams) return;
+  g[i] = m[i] = v[i] = 0.f;
+  put_bf16(pb, wt, i, p[i]);
 }
 
 __global__ void k_fillf(float* p, int64_t n, float v) {
@@ -208,28 +373,9 @@ __global__ void k_init_layer(float* W, int din, int dout, int fin, int fout, uin
   }
 }
 
-// dz = [dout | 0] padded to ncols_out columns; dzb = bf16(dz)
-__global__ void k_pad_out(const float* dout, int ncols_in, float* dz, uint16_t* dzb, int ncols_out,
-                          int rows) {
-  const int64_t tot = (int64_t)rows * ncols_out;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < tot;
-       i += (int64_t)gridDim.x * blockDim.x) {
-    const int r = (int)(i / ncols_out), j = (int)(i % ncols_out);
-    const float v = j < ncols_in ? dout[(int64_t)r * ncols_in + j] : 0.f;
-    dz[i] = v;
-    dzb[i] = f2bf(v);
-  }
-}
-
 static int eltgrid(int64_t n) {
   int64_t g = (n + 255) / 256;
   return (int)(g < 1 ? 1 : g > 8192 ? 8192 : g);
-}
-
-static hipError_t gemm(const GemmArgs& g, hipStream_t st) {
-  dim3 grid((g.N + GT - 1) / GT, (g.M + GT - 1) / GT);
-  hipLaunchKernelGGL(k_gemm_bf16, grid, dim3(256), 0, st, g);
-  return hipGetLastError();
 }
 
 }  // namespace aa
@@ -241,17 +387,6 @@ using namespace aa;
 // ---------------------------------------------------------------------------
 
 namespace {
-constexpr int kIn = 256, kH = 256, kOutP = 64;
-constexpr int kNF = AA_MLP_FEATURES, kNO = AA_MLP_OUTPUTS;
-constexpr int kLayers = 4;
-const int kDin[kLayers] = {kIn, kH, kH, kH};
-const int kDout[kLayers] = {kH, kH, kH, kOutP};
-
-int64_t param_count() {
-  int64_t s = 0;
-  for (int l = 0; l < kLayers; ++l) s += (int64_t)kDin[l] * kDout[l] + kDout[l];
-  return s;
-}
 size_t al(size_t x) { return (x + 255) / 256 * 256; }
 }  // namespace
 
@@ -261,29 +396,22 @@ static aa_status mlp_reset_state(aa_mlp* n);
 struct aa_mlp {
   int max_batch = 0;
   hipStream_t stream = nullptr;
-  int64_t P = 0;
   float *p = nullptr, *g = nullptr, *m = nullptr, *v = nullptr;  // packed W0 b0 W1 b1 ...
-  uint16_t* pb = nullptr;                                          // BF16 copy of p
-  uint16_t* xb = nullptr;                                          // [B x 256]
-  float* z[kLayers] = {};                                          // pre-activations
-  uint16_t* h[kLayers] = {};                                       // h[l] = input of layer l (l >= 1)
-  float *dz = nullptr, *dh = nullptr;
-  uint16_t* dzb = nullptr;
-  float* colpart = nullptr;  // kColSplit x 256 bias-gradient partial sums
+  uint16_t *pb = nullptr, *wt = nullptr;  // BF16 copies: as packed, weights transposed
+  uint16_t* h[kLayers] = {};      // h[l] = BF16 input of layer l [B x 256]
+  float* z[kLayers - 1] = {};     // hidden pre-activations
+  float* dz[kLayers] = {};        // their gradients, and the outputs'
+  uint16_t* dzb[kLayers] = {};
   int last_batch = 0;
   int64_t t = 0;  // Adam steps taken
-  int64_t off_w[kLayers], off_b[kLayers];
 };
 
 // Zero gradients and Adam moments, refresh the BF16 weights (after an
 // initialization or a load of the master weights).
 static aa_status mlp_reset_state(aa_mlp* n) {
-  const hipStream_t st = n->stream;
   (void)hipGetLastError();  // drop a stale error left by an earlier call
-  hipLaunchKernelGGL(k_fillf, dim3(eltgrid(n->P)), dim3(256), 0, st, n->g, n->P, 0.f);
-  hipLaunchKernelGGL(k_fillf, dim3(eltgrid(n->P)), dim3(256), 0, st, n->m, n->P, 0.f);
-  hipLaunchKernelGGL(k_fillf, dim3(eltgrid(n->P)), dim3(256), 0, st, n->v, n->P, 0.f);
-  hipLaunchKernelGGL(k_to_bf16, dim3(eltgrid(n->P)), dim3(256), 0, st, n->p, n->pb, n->P);
+  hipLaunchKernelGGL(k_reset, dim3((kParams + 255) / 256), dim3(256), 0, n->stream, n->p, n->g,
+                     n->m, n->v, n->pb, n->wt);
   n->t = 0;
   return hipGetLastError() == hipSuccess ? AA_OK : AA_EHIP;
 }
@@ -297,14 +425,12 @@ extern "C" {
 
 aa_status aa_mlp_workspace_size(int max_batch, size_t* bytes) {
   if (max_batch < 1 || max_batch > (1 << 20) || !bytes) return AA_EINVAL;
-  const int64_t P = param_count();
   const size_t B = (size_t)max_batch;
-  size_t s = 4 * al(sizeof(float) * P) + al(sizeof(uint16_t) * P);
-  s += al(sizeof(uint16_t) * B * kIn);
-  s += 3 * al(sizeof(float) * B * kH) + al(sizeof(float) * B * kOutP);
-  s += 3 * al(sizeof(uint16_t) * B * kH);
-  s += 2 * al(sizeof(float) * B * kH) + al(sizeof(uint16_t) * B * kH);
-  s += al(sizeof(float) * kColSplit * kH);
+  size_t s = 4 * al(sizeof(float) * kParams) + 2 * al(sizeof(uint16_t) * kParams);
+  s += kLayers * al(sizeof(uint16_t) * B * kH);            // h
+  s += (kLayers - 1) * al(sizeof(float) * B * kH);         // z
+  for (int l = 0; l < kLayers; ++l)                        // dz, dzb
+    s += al(sizeof(float) * B * layer_out(l)) + al(sizeof(uint16_t) * B * layer_out(l));
   *bytes = s;
   return AA_OK;
 }
@@ -321,7 +447,6 @@ aa_status aa_mlp_init(aa_mlp** out, int max_batch, uint64_t seed, void* d_ws, si
   if (!n) return AA_EINVAL;
   n->max_batch = max_batch;
   n->stream = (hipStream_t)stream;
-  n->P = param_count();
   char* base = (char*)d_ws;
   size_t o = 0;
   const size_t B = (size_t)max_batch;
@@ -330,24 +455,17 @@ aa_status aa_mlp_init(aa_mlp** out, int max_batch, uint64_t seed, void* d_ws, si
     o += al(sz);
     return r;
   };
-  n->p = (float*)take(sizeof(float) * n->P);
-  n->g = (float*)take(sizeof(float) * n->P);
-  n->m = (float*)take(sizeof(float) * n->P);
-  n->v = (float*)take(sizeof(float) * n->P);
-  n->pb = (uint16_t*)take(sizeof(uint16_t) * n->P);
-  n->xb = (uint16_t*)take(sizeof(uint16_t) * B * kIn);
-  for (int l = 0; l < kLayers; ++l) n->z[l] = (float*)take(sizeof(float) * B * kDout[l]);
-  for (int l = 1; l < kLayers; ++l) n->h[l] = (uint16_t*)take(sizeof(uint16_t) * B * kH);
-  n->dz = (float*)take(sizeof(float) * B * kH);
-  n->dh = (float*)take(sizeof(float) * B * kH);
-  n->dzb = (uint16_t*)take(sizeof(uint16_t) * B * kH);
-  n->colpart = (float*)take(sizeof(float) * kColSplit * kH);
-  int64_t off = 0;
+  n->p = (float*)take(sizeof(float) * kParams);
+  n->g = (float*)take(sizeof(float) * kParams);
+  n->m = (float*)take(sizeof(float) * kParams);
+  n->v = (float*)take(sizeof(float) * kParams);
+  n->pb = (uint16_t*)take(sizeof(uint16_t) * kParams);
+  n->wt = (uint16_t*)take(sizeof(uint16_t) * kParams);
+  for (int l = 0; l < kLayers; ++l) n->h[l] = (uint16_t*)take(sizeof(uint16_t) * B * kH);
+  for (int l = 0; l < kLayers - 1; ++l) n->z[l] = (float*)take(sizeof(float) * B * kH);
   for (int l = 0; l < kLayers; ++l) {
-    n->off_w[l] = off;
-    off += (int64_t)kDin[l] * kDout[l];
-    n->off_b[l] = off;
-    off += kDout[l];
+    n->dz[l] = (float*)take(sizeof(float) * B * layer_out(l));
+    n->dzb[l] = (uint16_t*)take(sizeof(uint16_t) * B * layer_out(l));
   }
   aa_status s = aa_mlp_reseed(n, seed);
   if (s != AA_OK) {
@@ -361,23 +479,24 @@ aa_status aa_mlp_init(aa_mlp** out, int max_batch, uint64_t seed, void* d_ws, si
 aa_status aa_mlp_reseed(aa_mlp* n, uint64_t seed) {
   if (!n) return AA_EINVAL;
   const hipStream_t st = n->stream;
-  hipLaunchKernelGGL(k_fillf, dim3(eltgrid(n->P)), dim3(256), 0, st, n->p, n->P, 0.f);
+  hipLaunchKernelGGL(k_fillf, dim3(eltgrid(kParams)), dim3(256), 0, st, n->p,
+                     (int64_t)kParams, 0.f);
   for (int l = 0; l < kLayers - 1; ++l) {
     const int fin = l == 0 ? kNF : kH;
     const uint64_t sb = sm64_mix_host(sm64_mix_host(seed) + (uint64_t)l);
-    hipLaunchKernelGGL(k_init_layer, dim3(eltgrid((int64_t)kDin[l] * kDout[l])), dim3(256), 0,
-                       st, n->p + n->off_w[l], kDin[l], kDout[l], fin, kDout[l], sb,
+    hipLaunchKernelGGL(k_init_layer, dim3(eltgrid((int64_t)kH * kH)), dim3(256), 0,
+                       st, n->p + layer_w(l), kH, kH, fin, kH, sb,
                        sqrtf(2.0f / (float)fin));
   }
   // last layer: zero weights, beta-logit bias +4
-  hipLaunchKernelGGL(k_fillf, dim3(1), dim3(64), 0, st, n->p + n->off_b[kLayers - 1] + (kNO - 1),
+  hipLaunchKernelGGL(k_fillf, dim3(1), dim3(64), 0, st, n->p + layer_b(kLayers - 1) + (kNO - 1),
                      (int64_t)1, 4.0f);
   return mlp_reset_state(n);
 }
 
 aa_status aa_mlp_set_params(aa_mlp* n, const float* h) {
   if (!n || !h) return AA_EINVAL;
-  if (hipMemcpyAsync(n->p, h, sizeof(float) * n->P, hipMemcpyHostToDevice, n->stream) !=
+  if (hipMemcpyAsync(n->p, h, sizeof(float) * kParams, hipMemcpyHostToDevice, n->stream) !=
           hipSuccess ||
       hipStreamSynchronize(n->stream) != hipSuccess)
     return AA_EHIP;
@@ -386,7 +505,7 @@ aa_status aa_mlp_set_params(aa_mlp* n, const float* h) {
 
 aa_status aa_mlp_get_params(aa_mlp* n, float* h) {
   if (!n || !h) return AA_EINVAL;
-  if (hipMemcpyAsync(h, n->p, sizeof(float) * n->P, hipMemcpyDeviceToHost, n->stream) !=
+  if (hipMemcpyAsync(h, n->p, sizeof(float) * kParams, hipMemcpyDeviceToHost, n->stream) !=
           hipSuccess ||
       hipStreamSynchronize(n->stream) != hipSuccess)
     return AA_EHIP;
@@ -395,43 +514,28 @@ aa_status aa_mlp_get_params(aa_mlp* n, float* h) {
 
 aa_status aa_mlp_get_grads(aa_mlp* n, float* h) {
   if (!n || !h) return AA_EINVAL;
-  if (hipMemcpyAsync(h, n->g, sizeof(float) * n->P, hipMemcpyDeviceToHost, n->stream) !=
+  if (hipMemcpyAsync(h, n->g, sizeof(float) * kParams, hipMemcpyDeviceToHost, n->stream) !=
           hipSuccess ||
       hipStreamSynchronize(n->stream) != hipSuccess)
     return AA_EHIP;
   return AA_OK;
 }
 
-int64_t aa_mlp_param_count(void) { return param_count(); }
+int64_t aa_mlp_param_count(void) { return kParams; }
 
 aa_status aa_mlp_forward(aa_mlp* n, int batch, const float* x, float* out) {
   if (!n || !x || batch < 1 || batch > n->max_batch) return AA_EINVAL;
   const hipStream_t st = n->stream;
   (void)hipGetLastError();  // drop a stale error left by an earlier call
-  hipLaunchKernelGGL(k_cast_pad, dim3(eltgrid((int64_t)batch * kIn)), dim3(256), 0, st, x, kNF,
-                     kNF, n->xb, kIn, batch);
-  for (int l = 0; l < kLayers; ++l) {
-    GemmArgs g{};
-    g.a = l == 0 ? n->xb : n->h[l];
-    g.sa0 = kDin[l];
-    g.sa1 = 1;
-    g.b = n->pb + n->off_w[l];
-    g.sb0 = kDout[l];
-    g.sb1 = 1;
-    g.c = n->z[l];
-    g.ldc = kDout[l];
-    g.bias = n->p + n->off_b[l];
-    g.M = batch;
-    g.N = kDout[l];
-    g.K = kDin[l];
-    if (gemm(g, st) != hipSuccess) return AA_EHIP;
-    if (l < kLayers - 1)
-      hipLaunchKernelGGL(k_gelu_bf16, dim3(eltgrid((int64_t)batch * kH)), dim3(256), 0, st,
-                         n->z[l], n->h[l + 1], (int64_t)batch * kH);
-  }
-  if (out)
-    hipLaunchKernelGGL(k_take_out, dim3(eltgrid((int64_t)batch * kNO)), dim3(256), 0, st,
-                       n->z[kLayers - 1], kOutP, out, batch, kNO);
+  FwdArgs a{};
+  a.x = x;
+  a.out = out;
+  a.wt = n->wt;
+  a.p = n->p;
+  for (int l = 0; l < kLayers; ++l) a.h[l] = n->h[l];
+  for (int l = 0; l < kLayers - 1; ++l) a.z[l] = n->z[l];
+  a.batch = batch;
+  hipLaunchKernelGGL(k_mlp_forward, dim3((batch + kRows - 1) / kRows), dim3(kChainWG), 0, st, a);
   n->last_batch = batch;
   return hipGetLastError() == hipSuccess ? AA_OK : AA_EHIP;
 }
@@ -440,48 +544,22 @@ aa_status aa_mlp_backward(aa_mlp* n, int batch, const float* dout) {
   if (!n || !dout || batch < 1 || batch != n->last_batch) return AA_EINVAL;
   const hipStream_t st = n->stream;
   (void)hipGetLastError();  // drop a stale error left by an earlier call
-  // dz of the output layer: [B x 64], live columns 0..20
-  hipLaunchKernelGGL(k_pad_out, dim3(eltgrid((int64_t)batch * kOutP)), dim3(256), 0, st, dout,
-                     kNO, n->dz, n->dzb, kOutP, batch);
-  for (int l = kLayers - 1; l >= 0; --l) {
-    const int din = kDin[l], dout_l = kDout[l];
-    // dW_l += H_l^T dZ_l   (M = din, N = dout, K = batch)
-    GemmArgs gw{};
-    gw.a = l == 0 ? n->xb : n->h[l];
-    gw.sa0 = 1;
-    gw.sa1 = din;
-    gw.b = n->dzb;
-    gw.sb0 = dout_l;
-    gw.sb1 = 1;
-    gw.c = n->g + n->off_w[l];
-    gw.ldc = dout_l;
-    gw.M = din;
-    gw.N = dout_l;
-    gw.K = batch;
-    gw.accumulate = 1;
-    if (gemm(gw, st) != hipSuccess) return AA_EHIP;
-    hipLaunchKernelGGL(k_colsum_part, dim3((dout_l + 63) / 64, kColSplit), dim3(256), 0, st,
-                       n->dz, batch, dout_l, n->colpart);
-    hipLaunchKernelGGL(k_colsum_fin, dim3((dout_l + 255) / 256), dim3(256), 0, st, n->colpart,
-                       dout_l, n->g + n->off_b[l]);
-    if (l == 0) break;
-    // dH = dZ_l W_l^T   (M = batch, N = din, K = dout)
-    GemmArgs gh{};
-    gh.a = n->dzb;
-    gh.sa0 = dout_l;
-    gh.sa1 = 1;
-    gh.b = n->pb + n->off_w[l];
-    gh.sb0 = 1;
-    gh.sb1 = dout_l;
-    gh.c = n->dh;
-    gh.ldc = din;
-    gh.M = batch;
-    gh.N = din;
-    gh.K = dout_l;
-    if (gemm(gh, st) != hipSuccess) return AA_EHIP;
-    hipLaunchKernelGGL(k_gelu_back, dim3(eltgrid((int64_t)batch * kH)), dim3(256), 0, st, n->dh,
-                       n->z[l - 1], n->dz, n->dzb, (int64_t)batch * kH);
+  BwdArgs a{};
+  GradArgs ga{};
+  a.dout = dout;
+  a.wb = n->pb;
+  for (int l = 0; l < kLayers - 1; ++l) a.z[l] = n->z[l];
+  for (int l = 0; l < kLayers; ++l) {
+    a.dz[l] = n->dz[l];
+    a.dzb[l] = n->dzb[l];
+    ga.h[l] = n->h[l];
+    ga.dz[l] = n->dz[l];
+    ga.dzb[l] = n->dzb[l];
   }
+  a.batch = ga.batch = batch;
+  ga.g = n->g;
+  hipLaunchKernelGGL(k_mlp_backward, dim3((batch + kRows - 1) / kRows), dim3(kChainWG), 0, st, a);
+  hipLaunchKernelGGL(k_mlp_grads, dim3(kWTiles + kBTiles), dim3(256), 0, st, ga);
   return hipGetLastError() == hipSuccess ? AA_OK : AA_EHIP;
 }
 
@@ -491,8 +569,8 @@ aa_status aa_mlp_adam(aa_mlp* n, float lr, float b1, float b2, float eps) {
   n->t += 1;
   const float c1 = 1.f - powf(b1, (float)n->t), c2 = 1.f - powf(b2, (float)n->t);
   (void)hipGetLastError();  // drop a stale error left by an earlier call
-  hipLaunchKernelGGL(k_adam, dim3(eltgrid(n->P)), dim3(256), 0, n->stream, n->p, n->g, n->m, n->v,
-                     n->pb, n->P, lr, b1, b2, eps, c1, c2);
+  hipLaunchKernelGGL(k_adam, dim3((kParams + 255) / 256), dim3(256), 0, n->stream, n->p, n->g,
+                     n->m, n->v, n->pb, n->wt, lr, b1, b2, eps, c1, c2);
   return hipGetLastError() == hipSuccess ? AA_OK : AA_EHIP;
 }
 
