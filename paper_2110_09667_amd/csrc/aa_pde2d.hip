@@ -10,14 +10,25 @@
 // whose last row and column keep the boundary at its true distance h (the
 // 1D Galerkin products; diagonal 1 + 2^level in units of 1/H^2).
 //
-// Layout and launches.  Every level's vectors are N_l x N_l row-major
-// arrays in the workspace.  Levels of more than 32 points per side run as
-// grid-wide kernels with one thread per point (rows across blockIdx.y, x
-// across threads: neighbour loads are coalesced, no divisions); the levels
-// from 32 points down run in one kernel of one workgroup with every array in
-// LDS.  A PCG iteration is 4 launches per grid-wide level, the coarse
-// kernel and 2 vector kernels; the whole working set at N = 1024 (~60 MB)
-// stays in the Infinity Cache, so the launches are latency bound.
+// Scaled right-hand sides.  Every level works on b = H^2 r, which makes each
+// step free of the spacing: red e = b / d, black e = (b + sum of red e) / d
+// (d the diagonal in units of 1 / H^2), and after those two half-sweeps the
+// residual is zero at the black points and (sum of black e) / H^2 at the red
+// ones, so full weighting gives the next level's b as a weighted sum of black
+// values alone.  Nothing but b needs keeping for the way up: the corrected red
+// value is b / d + P e_c again.
+//
+// Layout and launches.  Every level's vectors are N_l x N_l row-major arrays
+// in the workspace.  Levels of more than 64 points per side take one launch
+// down (k_down: pre-smoothing and restriction) and one up (k_up: correction
+// and post-smoothing), each a tile per workgroup with its halo recomputed in
+// LDS; the levels from 64 points down run in one kernel of one workgroup with
+// every array in LDS, the last ones (at most 8 points per side) as one
+// precomputed matrix.  On the fine grid k_down also takes the conjugate
+// gradient's update of x and r, and k_up gives r.z.  A PCG iteration at N =
+// 1024 is 10 launches (23 when each half-sweep, each restriction and each
+// vector update was one); the whole working set (~60 MB) stays in the Infinity
+// Cache, so the launches are latency bound.
 //
 // Reductions (r.z, p.q, r.r): each workgroup stores its partial sum, and
 // every workgroup of the kernel that needs the value sums all partials itself
@@ -38,9 +49,12 @@ namespace pde {
 
 constexpr int kBX = 256;           // threads per workgroup of the grid-wide kernels
 constexpr int kMaxWG = 1024;       // workgroups of a grid-wide kernel (partials)
-constexpr int kCoarseN = 32;       // levels of at most this many points per side in LDS
+constexpr int kCoarseN = 32;       // the hierarchy must reach this many points per side
+constexpr int kLdsN = 64;          // levels of at most this many points per side in LDS
+constexpr int kMatN = 8;           // levels of at most this many as one matrix
 constexpr int kCoarseWG = 1024;    // threads of the coarse kernel
-constexpr int kCoarseLds = 3 * (1024 + 256 + 64 + 16 + 4 + 1);
+// b and z of the LDS levels with a border of zeros (66, 34, 18, 10, ... per side)
+constexpr int kCoarseLds = 2 * (66 * 66 + 34 * 34 + 18 * 18 + 10 * 10 + 6 * 6 + 4 * 4 + 3 * 3);
 constexpr int kMaxLevels = 32;
 
 // integer state words
@@ -48,13 +62,14 @@ enum : int { I_DONE = 0, I_ITERS = 1, I_CONV = 2, I_COUNT = 64 };
 // scalar slots: r.r of the right-hand side, rho of the previous iteration
 enum : int { S_RR0 = 0, S_RHO_PREV = 1, S_COUNT = 8 };
 
+// Level operator, diagonal in units of 1 / H^2: 4 inside, 2 + dl on the last
+// row or column, 2 dl in the last corner (dl = 1 + 2^level).
 struct Lev {
   int N;
-  double H2;     // spacing squared
-  double dlast;  // last diagonal entry of the level's 1D operator, times H^2
-  double* r;     // right-hand side (level 0: the PCG residual)
-  double* e;     // pre-smoothed correction
-  double* z;     // post-smoothed correction (the cycle's output on the level)
+  double H2;      // spacing squared
+  double i1, i2;  // 1 / (2 + dl), 1 / (2 dl)
+  double* b;      // scaled right-hand side H^2 r (level 0: none, r is unscaled)
+  double* z;      // post-smoothed correction (the cycle's output on the level)
 };
 
 struct Pcg {
@@ -70,102 +85,36 @@ struct Pcg {
   int fixed;         // >= 0: exactly this many iterations
 };
 
-// --------------------------------------------------------------------------
-// point operations (shared by the grid-wide kernels and the LDS kernel)
-// --------------------------------------------------------------------------
-
-__device__ __forceinline__ double diag_at(int i, int j, int N, double dl) {
-  return ((i == N - 1) ? dl : 2.0) + ((j == N - 1) ? dl : 2.0);
+// reciprocal of the diagonal at (i, j)
+__device__ __forceinline__ double inv_diag(int i, int j, int N, double i1, double i2) {
+  const bool x = i == N - 1, y = j == N - 1;
+  return x ? (y ? i2 : i1) : (y ? i1 : 0.25);
 }
 
-// sum of the four neighbours (zero outside), left, right, below, above
-__device__ __forceinline__ double nb_sum(const double* u, int i, int j, int N) {
-  const int64_t p = (int64_t)j * N + i;
-  const double l = i > 0 ? u[p - 1] : 0.0;
-  const double r = i < N - 1 ? u[p + 1] : 0.0;
-  const double d = j > 0 ? u[p - N] : 0.0;
-  const double a = j < N - 1 ? u[p + N] : 0.0;
-  return ((l + r) + d) + a;
+// bilinear interpolation at a red point (i + j even): a coarse point itself
+// (both odd), or the mean of four (both even; index -1 is the boundary).
+// at(I, J) returns the coarse value.
+template <class At>
+__device__ __forceinline__ double interp_red(int i, int j, At&& at) {
+  const int I = i >> 1, J = j >> 1;
+  if (i & 1) return at(I, J);
+  return 0.25 * ((at(I - 1, J - 1) + at(I, J - 1)) + (at(I - 1, J) + at(I, J)));
 }
 
-// red pre-smoothing from a zero start at red point (i, j)
-__device__ __forceinline__ double red0(const double* r, int i, int j, int N, double H2,
-                                       double dl) {
-  return H2 * r[(int64_t)j * N + i] / diag_at(i, j, N, dl);
-}
-
-// pre-smoothing (red then black Gauss-Seidel from E = 0) at (i, j)
-__device__ __forceinline__ double pre_point(const double* r, int i, int j, int N, double H2,
-                                            double dl) {
-  if (((i + j) & 1) == 0) return red0(r, i, j, N, H2, dl);
-  const double l = i > 0 ? red0(r, i - 1, j, N, H2, dl) : 0.0;
-  const double rt = i < N - 1 ? red0(r, i + 1, j, N, H2, dl) : 0.0;
-  const double d = j > 0 ? red0(r, i, j - 1, N, H2, dl) : 0.0;
-  const double a = j < N - 1 ? red0(r, i, j + 1, N, H2, dl) : 0.0;
-  return (H2 * r[(int64_t)j * N + i] + (((l + rt) + d) + a)) / diag_at(i, j, N, dl);
-}
-
-// residual r - A e at (i, j); zero outside the grid
-__device__ __forceinline__ double res_point(const double* r, const double* e, int i, int j,
-                                            int N, double H2, double dl) {
-  if (i < 0 || j < 0 || i >= N || j >= N) return 0.0;
-  const int64_t p = (int64_t)j * N + i;
-  return r[p] - (diag_at(i, j, N, dl) * e[p] - nb_sum(e, i, j, N)) / H2;
-}
-
-// full weighting of the residual at coarse point (I, J): along x, then y
-__device__ __forceinline__ double restrict_point(const double* r, const double* e, int I, int J,
-                                                 int N, double H2, double dl) {
-  const int ic = 2 * I + 1, jc = 2 * J + 1;
-  double row[3];
-#pragma unroll
-  for (int t = 0; t < 3; ++t) {
-    const int j = jc - 1 + t;
-    row[t] = 0.5 * res_point(r, e, ic - 1, j, N, H2, dl) + res_point(r, e, ic, j, N, H2, dl) +
-             0.5 * res_point(r, e, ic + 1, j, N, H2, dl);
-  }
-  return (0.5 * row[0] + row[1] + 0.5 * row[2]) / 4.0;
-}
-
-// bilinear interpolation of the coarse correction (Nc per side) at fine (i, j):
-// along x, then y; coarse index -1 is the boundary
-__device__ __forceinline__ double interp_x(const double* ec, int i, int J, int Nc) {
-  const double* row = ec + (int64_t)J * Nc;
-  if (i & 1) return row[(i - 1) >> 1];
-  const int I = i >> 1;
-  return (I > 0 ? 0.5 * row[I - 1] : 0.0) + 0.5 * row[I];
-}
-
-__device__ __forceinline__ double interp_point(const double* ec, int i, int j, int Nc) {
-  if (j & 1) return interp_x(ec, i, (j - 1) >> 1, Nc);
-  const int J = j >> 1;
-  return (J > 0 ? 0.5 * interp_x(ec, i, J - 1, Nc) : 0.0) + 0.5 * interp_x(ec, i, J, Nc);
-}
-
-// corrected pre-smoothed value e + P e_c at (i, j) (ec null: no correction)
-__device__ __forceinline__ double corr_at(const double* e, const double* ec, int i, int j, int N,
-                                          int Nc) {
-  const double v = e[(int64_t)j * N + i];
-  return ec ? v + interp_point(ec, i, j, Nc) : v;
-}
-
-// after the coarse correction: red points e + P e_c; black points their
-// Gauss-Seidel value from the corrected red neighbours
-__device__ __forceinline__ double post_black_point(const double* r, const double* e,
-                                                   const double* ec, int i, int j, int N, int Nc,
-                                                   double H2, double dl) {
-  if (((i + j) & 1) == 0) return corr_at(e, ec, i, j, N, Nc);
-  const double l = i > 0 ? corr_at(e, ec, i - 1, j, N, Nc) : 0.0;
-  const double rt = i < N - 1 ? corr_at(e, ec, i + 1, j, N, Nc) : 0.0;
-  const double d = j > 0 ? corr_at(e, ec, i, j - 1, N, Nc) : 0.0;
-  const double a = j < N - 1 ? corr_at(e, ec, i, j + 1, N, Nc) : 0.0;
-  return (H2 * r[(int64_t)j * N + i] + (((l + rt) + d) + a)) / diag_at(i, j, N, dl);
-}
-
-// the final red half-sweep at red point (i, j) from the black values in z
-__device__ __forceinline__ double post_red_point(const double* r, const double* z, int i, int j,
-                                                 int N, double H2, double dl) {
-  return (H2 * r[(int64_t)j * N + i] + nb_sum(z, i, j, N)) / diag_at(i, j, N, dl);
+// scaled right-hand side of coarse point (I, J) from the pre-smoothed black
+// values e around fine point (2 I + 1, 2 J + 1) of an N x N grid: its own
+// residual plus a quarter of its four corners' (a corner outside the grid has
+// none), each the sum of four black values.  e points at that fine point, with
+// row stride S; values one point outside the grid are zero, further out none
+// is read.
+__device__ __forceinline__ double restrict_red(const double* e, int S, int ic, int jc, int N) {
+  const double wx = ic + 1 < N ? 1.5 : 1.25;  // of (ic, jc +- 1)
+  const double wy = jc + 1 < N ? 1.5 : 1.25;  // of (ic +- 1, jc)
+  const double in = wx * (e[-S] + e[S]) + wy * (e[-1] + e[1]);
+  double out = (e[-S - 2] + e[S - 2]) + (e[-2 * S - 1] + e[-2 * S + 1]);
+  if (ic + 1 < N) out += e[-S + 2] + e[S + 2];
+  if (jc + 1 < N) out += e[2 * S - 1] + e[2 * S + 1];
+  return in + 0.25 * out;
 }
 
 // --------------------------------------------------------------------------
@@ -189,7 +138,7 @@ __device__ double block_sum(double v, double* lds4) {
 __device__ void partial_store(double v, double* parts) {
   __shared__ double lds[16];
   const double s = block_sum(v, lds);
-  if (threadIdx.x == 0) parts[blockIdx.y * gridDim.x + blockIdx.x] = s;
+  if (threadIdx.x == 0) parts[blockIdx.x] = s;
 }
 
 // the sum of np partials, in one fixed order (every workgroup gets the same)
@@ -207,7 +156,7 @@ __device__ __forceinline__ bool pcg_check(const Pcg& a, int k) {
   if (a.ist[I_DONE]) return true;
   const double rr = sum_parts(a.p_rr, a.np_fine);
   const double rr0 = k == 0 ? rr : a.sc[S_RR0];
-  if (k == 0 && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) a.sc[S_RR0] = rr;
+  if (k == 0 && blockIdx.x == 0 && threadIdx.x == 0) a.sc[S_RR0] = rr;
   bool stop;
   int conv;
   if (a.fixed >= 0) {
@@ -217,7 +166,7 @@ __device__ __forceinline__ bool pcg_check(const Pcg& a, int k) {
     conv = rr <= a.tol2 * rr0;
     stop = conv || k >= a.max_iter;
   }
-  if (stop && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) {
+  if (stop && blockIdx.x == 0 && threadIdx.x == 0) {
     a.ist[I_DONE] = 1;
     a.ist[I_ITERS] = k;
     a.ist[I_CONV] = conv;
@@ -226,117 +175,321 @@ __device__ __forceinline__ bool pcg_check(const Pcg& a, int k) {
 }
 
 // --------------------------------------------------------------------------
-// grid-wide level kernels: thread (x, row) over points (i, j), rows strided
+// grid-wide level kernels: one tile per workgroup and turn
 // --------------------------------------------------------------------------
 
-#define PDE_ROWS(N) for (int j = blockIdx.y; j < (N); j += gridDim.y)
-#define PDE_COLS(N) for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < (N); i += gridDim.x * blockDim.x)
+// Tiles of TX x TY fine points (64 x 16 from 512 points per side; 32 x 8
+// below, where 64 x 16 would leave fewer than 64 workgroups).
+constexpr int kTileBig = 512;
+__host__ __device__ constexpr int tiles_of(int N, int T) { return (N + T - 1) / T; }
 
-__global__ __launch_bounds__(kBX) void k_pre(Lev L, Pcg a, int k, int check) {
-  if (check ? pcg_check(a, k) : a.ist[I_DONE] != 0) return;
-  PDE_ROWS(L.N) PDE_COLS(L.N) L.e[(int64_t)j * L.N + i] = pre_point(L.r, i, j, L.N, L.H2, L.dlast);
-}
-
-__global__ __launch_bounds__(kBX) void k_restrict(Lev L, Lev C, Pcg a) {
-  if (a.ist[I_DONE]) return;
-  PDE_ROWS(C.N) PDE_COLS(C.N)
-    C.r[(int64_t)j * C.N + i] = restrict_point(L.r, L.e, i, j, L.N, L.H2, L.dlast);
-}
-
-__global__ __launch_bounds__(kBX) void k_post_black(Lev L, const double* ec, int Nc, Pcg a) {
-  if (a.ist[I_DONE]) return;
-  PDE_ROWS(L.N) PDE_COLS(L.N)
-    L.z[(int64_t)j * L.N + i] = post_black_point(L.r, L.e, ec, i, j, L.N, Nc, L.H2, L.dlast);
-}
-
-// final red half-sweep; on level 0 also rho_k = r . z
-__global__ __launch_bounds__(kBX) void k_post_red(Lev L, Pcg a, int k, int dot) {
-  if (a.ist[I_DONE]) return;
-  double acc = 0.0;
-  PDE_ROWS(L.N) PDE_COLS(L.N) {
-    const int64_t p = (int64_t)j * L.N + i;
-    double zv;
-    if (((i + j) & 1) == 0) {
-      zv = post_red_point(L.r, L.z, i, j, L.N, L.H2, L.dlast);
-      L.z[p] = zv;
-    } else {
-      zv = L.z[p];
-    }
-    if (dot) acc = fma(L.r[p], zv, acc);
-  }
-  if (dot) partial_store(acc, a.p_rho);
-}
-
-// --------------------------------------------------------------------------
-// the levels from 32 points per side down: one workgroup, arrays in LDS
-// --------------------------------------------------------------------------
-
-struct CoarseArgs {
-  const double* r_in;  // right-hand side of the first coarse level (global)
-  double* z_out;       // its post-smoothed correction (global)
-  int N[kMaxLevels];   // sizes of the coarse levels
-  double H2[kMaxLevels];
-  double dl[kMaxLevels];
-  int nlev;
+// The PCG update that precedes a cycle on the fine grid: alpha = rho / p.q,
+// x += alpha p, r_out = r_in - alpha q (r_out is another buffer: neighbouring
+// tiles recompute r in their halos), r.r.
+struct DownFine {
+  const double* r_in;
+  double* r_out;
+  const double* p;
+  const double* q;
+  double* x;
 };
 
-__global__ __launch_bounds__(kCoarseWG) void k_coarse(CoarseArgs c, Pcg a, int k, int check,
-                                                      int dot) {
+enum : int { DOWN_LEVEL = 0, DOWN_FIRST = 1, DOWN_UPDATE = 2 };
+
+// Pre-smoothing from zero (red, black) and restriction of one level: reads b
+// (level 0: r), writes the next level's b.  Bound by latency: one read of a
+// tile with a halo of two points, two LDS phases.  At N = 1024 the fine level
+// with the update 14 us (k_update + k_pre + k_restrict: 13 + 8 + 9 us).
+template <int TX, int TY, int MODE>
+__global__ __launch_bounds__(kBX) void k_down(Lev L, Lev C, DownFine f, Pcg a, int k, int check) {
+  constexpr int W = TX + 5, H = TY + 5;  // points 2 I0 - 2 .. 2 I0 + TX + 2
+  __shared__ double sb[H * W], se[H * W];
   if (check ? pcg_check(a, k) : a.ist[I_DONE] != 0) return;
-  __shared__ double buf[kCoarseLds];
-  __shared__ int sN[kMaxLevels], soff[kMaxLevels];
-  __shared__ double sH2[kMaxLevels], sdl[kMaxLevels];
-  const int t = threadIdx.x, nt = blockDim.x;
-  if (t == 0) {
-    int off = 0;
-    for (int l = 0; l < c.nlev; ++l) {
-      sN[l] = c.N[l];
-      sH2[l] = c.H2[l];
-      sdl[l] = c.dl[l];
-      soff[l] = off;
-      off += 3 * c.N[l] * c.N[l];
-    }
+  double alpha = 0.0;
+  if (MODE == DOWN_UPDATE) {
+    const double rho = sum_parts(a.p_rho, a.np_rho);
+    alpha = rho / sum_parts(a.p_pq, a.np_fine);
+    // rho for the next iteration's beta (k_dir read the previous one already)
+    if (blockIdx.x == 0 && threadIdx.x == 0) a.sc[S_RHO_PREV] = rho;
   }
-  __syncthreads();
-  // level l: right-hand side R(l), pre-smoothed E(l), post-smoothed Z(l)
-#define R_(l) (buf + soff[l])
-#define E_(l) (buf + soff[l] + sN[l] * sN[l])
-#define Z_(l) (buf + soff[l] + 2 * sN[l] * sN[l])
-  for (int p = t; p < sN[0] * sN[0]; p += nt) R_(0)[p] = c.r_in[p];
-  __syncthreads();
-  for (int l = 0; l < c.nlev; ++l) {
-    const int N = sN[l];
-    for (int p = t; p < N * N; p += nt) E_(l)[p] = pre_point(R_(l), p % N, p / N, N, sH2[l], sdl[l]);
-    __syncthreads();
-    if (l + 1 < c.nlev) {
-      const int Nc = sN[l + 1];
-      for (int p = t; p < Nc * Nc; p += nt)
-        R_(l + 1)[p] = restrict_point(R_(l), E_(l), p % Nc, p / Nc, N, sH2[l], sdl[l]);
-      __syncthreads();
+  const int N = L.N, tx = tiles_of(N, TX), nt = tx * tiles_of(N, TY);
+  double acc = 0.0;
+  for (int t = blockIdx.x; t < nt; t += gridDim.x) {
+    const int i0 = t % tx * TX, j0 = t / tx * TY;
+    for (int e = threadIdx.x; e < H * W; e += kBX) {
+      const int y = e / W, x = e % W, i = i0 + x - 2, j = j0 + y - 2;
+      double b = 0.0, red = 0.0;
+      if (i >= 0 && j >= 0 && i < N && j < N) {
+        const int64_t p = (int64_t)j * N + i;
+        if (MODE == DOWN_LEVEL) {
+          b = L.b[p];
+        } else if (MODE == DOWN_FIRST) {
+          b = L.H2 * f.r_in[p];
+        } else {
+          const double rv = fma(-alpha, f.q[p], f.r_in[p]);
+          if (x >= 2 && y >= 2 && x < TX + 2 && y < TY + 2) {
+            f.r_out[p] = rv;
+            f.x[p] = fma(alpha, f.p[p], f.x[p]);
+            acc = fma(rv, rv, acc);
+          }
+          b = L.H2 * rv;
+        }
+        if (((i + j) & 1) == 0) red = b * inv_diag(i, j, N, L.i1, L.i2);
+      }
+      sb[e] = b;
+      se[e] = red;
     }
+    __syncthreads();
+    for (int e = threadIdx.x; e < (H - 2) * (W / 2); e += kBX) {
+      const int y = 1 + e / (W / 2), s = e % (W / 2);
+      const int x = 1 + 2 * s + (y & 1);  // i + j odd (i0, j0 even)
+      const int i = i0 + x - 2, j = j0 + y - 2, c = y * W + x;
+      if (x < W - 1 && i >= 0 && j >= 0 && i < N && j < N)
+        se[c] = (sb[c] + (((se[c - 1] + se[c + 1]) + se[c - W]) + se[c + W])) *
+                inv_diag(i, j, N, L.i1, L.i2);
+    }
+    __syncthreads();
+    for (int e = threadIdx.x; e < TX / 2 * (TY / 2); e += kBX) {
+      const int Y = e / (TX / 2), X = e % (TX / 2), I = (i0 >> 1) + X, J = (j0 >> 1) + Y;
+      if (I < C.N && J < C.N)
+        C.b[(int64_t)J * C.N + I] =
+            restrict_red(se + (2 * Y + 3) * W + 2 * X + 3, W, 2 * I + 1, 2 * J + 1, N);
+    }
+    __syncthreads();
+  }
+  if (MODE == DOWN_UPDATE) partial_store(acc, a.p_rr);
+}
+
+// Correction from the coarse level (ec, Nc per side) and post-smoothing (black,
+// red) of one level; on the fine grid b = H^2 r and rho = r.z is formed.
+// Three LDS phases on a tile with a halo of two points.
+template <int TX, int TY, bool FINE>
+__global__ __launch_bounds__(kBX) void k_up(Lev L, const double* r, const double* ec, int Nc,
+                                            Pcg a, int dot) {
+  constexpr int W = TX + 4, H = TY + 4;
+  __shared__ double sb[H * W], sz[H * W];
+  if (a.ist[I_DONE]) return;
+  const int N = L.N, tx = tiles_of(N, TX), nt = tx * tiles_of(N, TY);
+  const double* src = FINE ? r : L.b;
+  const double scale = FINE ? L.H2 : 1.0;
+  double acc = 0.0;
+  for (int t = blockIdx.x; t < nt; t += gridDim.x) {
+    const int i0 = t % tx * TX, j0 = t / tx * TY;
+    for (int e = threadIdx.x; e < H * W; e += kBX) {
+      const int y = e / W, x = e % W, i = i0 + x - 2, j = j0 + y - 2;
+      double b = 0.0, z = 0.0;
+      if (i >= 0 && j >= 0 && i < N && j < N) {
+        b = src[(int64_t)j * N + i];
+        if (FINE) b *= scale;
+        if (((i + j) & 1) == 0)
+          z = b * inv_diag(i, j, N, L.i1, L.i2) + interp_red(i, j, [&](int I, int J) {
+                return I >= 0 && J >= 0 ? ec[(int64_t)J * Nc + I] : 0.0;
+              });
+      }
+      sb[e] = b;
+      sz[e] = z;
+    }
+    __syncthreads();
+    for (int e = threadIdx.x; e < (H - 2) * (W / 2 - 1); e += kBX) {
+      const int y = 1 + e / (W / 2 - 1), s = e % (W / 2 - 1);
+      const int x = 1 + 2 * s + (y & 1);
+      const int i = i0 + x - 2, j = j0 + y - 2, c = y * W + x;
+      if (i >= 0 && j >= 0 && i < N && j < N)
+        sz[c] = (sb[c] + (((sz[c - 1] + sz[c + 1]) + sz[c - W]) + sz[c + W])) *
+                inv_diag(i, j, N, L.i1, L.i2);
+    }
+    __syncthreads();
+    for (int e = threadIdx.x; e < TX * TY; e += kBX) {
+      const int y = e / TX, x = e % TX, i = i0 + x, j = j0 + y, c = (y + 2) * W + x + 2;
+      if (i < N && j < N) {
+        double z = sz[c];
+        if (((i + j) & 1) == 0)
+          z = (sb[c] + (((sz[c - 1] + sz[c + 1]) + sz[c - W]) + sz[c + W])) *
+              inv_diag(i, j, N, L.i1, L.i2);
+        L.z[(int64_t)j * N + i] = z;
+        if (FINE) acc = fma(sb[c], z, acc);
+      }
+    }
+    __syncthreads();
+  }
+  if (FINE && dot) partial_store(acc / L.H2, a.p_rho);
+}
+
+// --------------------------------------------------------------------------
+// the levels from 64 points per side down: one workgroup, arrays in LDS
+// --------------------------------------------------------------------------
+
+// LDS levels 0 .. nlev-1 (each half the one before it); with nmat > 0 the
+// level after them (nmat points per side, at most 8) and everything below it
+// is the matrix `mat` (nmat^2 square, symmetric up to rounding) applied to its
+// scaled right-hand side.
+struct CoarseArgs {
+  const double* in;    // right-hand side of the first LDS level (global)
+  double scale;        // b = scale * in
+  double* z_out;       // its post-smoothed correction (global)
+  int N[kMaxLevels];   // sizes of the LDS levels
+  double i1[kMaxLevels];
+  double i2[kMaxLevels];
+  int off[kMaxLevels + 1];  // where a level's b and z start in LDS
+  int nlev;
+  int nmat;
+  const double* mat;   // [out][in]
+};
+
+// The cycle on the LDS levels, right-hand side b and red e = b / d of level 0
+// in place.  Arrays have a border of zeros (row stride N + 2).  A thread takes
+// the colour's point `slot` of rows t / 32, t / 32 + 32, ...: no divisions.
+struct CoarseLds {
+  double* buf;
+  const CoarseArgs& c;
+  __device__ double* b(int l) const { return buf + c.off[l]; }
+  __device__ double* z(int l) const { return buf + (c.off[l] + c.off[l + 1]) / 2; }
+};
+
+// body(i, j, offset) over the points of one colour (0: i + j even)
+template <class Body>
+__device__ __forceinline__ void colour_points(int N, int colour, Body&& body) {
+  const int s = threadIdx.x & 31, S = N + 2;
+  for (int j = threadIdx.x >> 5; j < N; j += (int)(blockDim.x >> 5)) {
+    const int i = 2 * s + ((j + colour) & 1);
+    if (i < N) body(i, j, (j + 1) * S + i + 1);
+  }
+}
+
+// Gauss-Seidel on one colour of a bordered level
+__device__ __forceinline__ void gs_colour(const double* b, double* z, int N, int colour, double i1,
+                                          double i2) {
+  const int S = N + 2;
+  colour_points(N, colour, [&](int i, int j, int c) {
+    z[c] = (b[c] + (((z[c - 1] + z[c + 1]) + z[c - S]) + z[c + S])) * inv_diag(i, j, N, i1, i2);
+  });
+}
+
+// matv: this thread's share of the matrix (row t / 16, columns t % 16, + 16, ...)
+__device__ __forceinline__ void coarse_cycle(const CoarseLds& A, const double (&matv)[4]) {
+  const CoarseArgs& c = A.c;
+  __shared__ double mb[kMatN * kMatN], mz[kMatN * kMatN];
+  for (int l = 0; l < c.nlev; ++l) {
+    const int N = c.N[l], S = N + 2;
+    double *b = A.b(l), *z = A.z(l);
+    gs_colour(b, z, N, 1, c.i1[l], c.i2[l]);  // black, after red = b / d
+    __syncthreads();
+    const bool last = l + 1 == c.nlev;
+    if (last && c.nmat == 0) break;
+    const int Nc = N / 2;
+    for (int J = threadIdx.x >> 5; J < Nc; J += (int)(blockDim.x >> 5)) {
+      const int I = threadIdx.x & 31;
+      if (I < Nc) {
+        const double v = restrict_red(z + (2 * J + 2) * S + 2 * I + 2, S, 2 * I + 1, 2 * J + 1, N);
+        if (last) {
+          mb[J * Nc + I] = v;
+        } else {
+          const int cc = (J + 1) * (Nc + 2) + I + 1;
+          A.b(l + 1)[cc] = v;
+          if (((I + J) & 1) == 0)
+            A.z(l + 1)[cc] = v * inv_diag(I, J, Nc, c.i1[l + 1], c.i2[l + 1]);
+        }
+      }
+    }
+    __syncthreads();
+  }
+  if (c.nmat) {
+    const int n2 = c.nmat * c.nmat, row = threadIdx.x >> 4;
+    double v = 0.0;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int col = (threadIdx.x & 15) + 16 * q;
+      if (col < n2) v = fma(matv[q], mb[col], v);
+    }
+#pragma unroll
+    for (int o = 8; o >= 1; o >>= 1) v += __shfl_xor(v, o, 64);
+    if (row < n2 && (threadIdx.x & 15) == 0) mz[row] = v;
+    __syncthreads();
   }
   for (int l = c.nlev - 1; l >= 0; --l) {
-    const int N = sN[l];
-    const double* ec = l + 1 < c.nlev ? Z_(l + 1) : nullptr;
-    const int Nc = l + 1 < c.nlev ? sN[l + 1] : 0;
-    for (int p = t; p < N * N; p += nt)
-      Z_(l)[p] = post_black_point(R_(l), E_(l), ec, p % N, p / N, N, Nc, sH2[l], sdl[l]);
-    __syncthreads();
-    for (int p = t; p < N * N; p += nt) {
-      const int i = p % N, j = p / N;
-      if (((i + j) & 1) == 0) Z_(l)[p] = post_red_point(R_(l), Z_(l), i, j, N, sH2[l], sdl[l]);
+    const int N = c.N[l];
+    double *b = A.b(l), *z = A.z(l);
+    const bool last = l + 1 == c.nlev;
+    if (!last || c.nmat) {
+      const int Nc = N / 2;
+      const double* zc = last ? nullptr : A.z(l + 1);
+      colour_points(N, 0, [&](int i, int j, int p) {
+        z[p] += interp_red(i, j, [&](int I, int J) {
+          return last ? (I >= 0 && J >= 0 ? mz[J * Nc + I] : 0.0) : zc[(J + 1) * (Nc + 2) + I + 1];
+        });
+      });
+      __syncthreads();
+      gs_colour(b, z, N, 1, c.i1[l], c.i2[l]);
+      __syncthreads();
     }
+    gs_colour(b, z, N, 0, c.i1[l], c.i2[l]);
     __syncthreads();
   }
-  double acc = 0.0;
-  for (int p = t; p < sN[0] * sN[0]; p += nt) {
-    c.z_out[p] = Z_(0)[p];
-    if (dot) acc = fma(R_(0)[p], Z_(0)[p], acc);
+}
+
+__device__ __forceinline__ void load_mat(const CoarseArgs& c, double (&matv)[4]) {
+  const int n2 = c.nmat * c.nmat, row = threadIdx.x >> 4;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const int col = (threadIdx.x & 15) + 16 * q;
+    matv[q] = row < n2 && col < n2 ? c.mat[row * n2 + col] : 0.0;
   }
-#undef R_
-#undef E_
-#undef Z_
-  if (dot) partial_store(acc, a.p_rho);
+}
+
+// One workgroup: bound by its barrier phases (5 a level, 64 and 32 and 16
+// points per side at N = 1024, then the matrix in 2 instead of another 16).
+__global__ __launch_bounds__(kCoarseWG) void k_coarse(CoarseArgs c, Pcg a, int k, int check,
+                                                      int dot) {
+  __shared__ double buf[kCoarseLds];
+  double matv[4];
+  load_mat(c, matv);
+  if (check ? pcg_check(a, k) : a.ist[I_DONE] != 0) return;
+  const CoarseLds A{buf, c};
+  const int t = threadIdx.x, N = c.N[0], S = N + 2;
+  for (int e = t; e < c.off[c.nlev]; e += kCoarseWG) buf[e] = 0.0;
+  __syncthreads();
+  for (int j = t >> 6; j < N; j += kCoarseWG / 64) {
+    const int i = t & 63;
+    if (i < N) {
+      const int p = (j + 1) * S + i + 1;
+      const double v = c.scale * c.in[j * N + i];
+      A.b(0)[p] = v;
+      if (((i + j) & 1) == 0) A.z(0)[p] = v * inv_diag(i, j, N, c.i1[0], c.i2[0]);
+    }
+  }
+  __syncthreads();
+  coarse_cycle(A, matv);
+  double acc = 0.0;
+  for (int j = t >> 6; j < N; j += kCoarseWG / 64) {
+    const int i = t & 63;
+    if (i < N) {
+      const int p = (j + 1) * S + i + 1;
+      const double z = A.z(0)[p];
+      c.z_out[j * N + i] = z;
+      if (dot) acc = fma(A.b(0)[p], z, acc);
+    }
+  }
+  if (dot) partial_store(acc / c.scale, a.p_rho);
+}
+
+// The matrix of the last levels: workgroup e runs their cycle (c.nmat = 0) on
+// the e-th unit vector and stores column e.
+__global__ __launch_bounds__(kCoarseWG) void k_matrix(CoarseArgs c, double* mat) {
+  __shared__ double buf[kCoarseLds];
+  const CoarseLds A{buf, c};
+  const int N = c.N[0], S = N + 2, n2 = N * N;
+  for (int e = threadIdx.x; e < kCoarseLds; e += kCoarseWG) buf[e] = 0.0;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    const int i = blockIdx.x % N, j = blockIdx.x / N, p = (j + 1) * S + i + 1;
+    A.b(0)[p] = 1.0;
+    if (((i + j) & 1) == 0) A.z(0)[p] = inv_diag(i, j, N, c.i1[0], c.i2[0]);
+  }
+  __syncthreads();
+  const double none[4] = {0.0, 0.0, 0.0, 0.0};
+  coarse_cycle(A, none);
+  for (int r = threadIdx.x; r < n2; r += kCoarseWG)
+    mat[(size_t)r * n2 + blockIdx.x] = A.z(0)[(r / N + 1) * S + r % N + 1];
 }
 
 // --------------------------------------------------------------------------
@@ -358,8 +511,8 @@ __global__ __launch_bounds__(kBX) void k_init(int problem, double lambda, const 
                                               const double* u, double* x, double* r, int N,
                                               Pcg a) {
   double acc = 0.0;
-  PDE_ROWS(N) PDE_COLS(N) {
-    const int64_t p = (int64_t)j * N + i;
+  const int64_t n = (int64_t)N * N;
+  for (int64_t p = (int64_t)blockIdx.x * kBX + threadIdx.x; p < n; p += (int64_t)gridDim.x * kBX) {
     double v;
     if (problem == AA_PDE_BRATU) v = lambda * exp(u[p]);
     else if (problem == 0) v = u[p];
@@ -368,7 +521,7 @@ __global__ __launch_bounds__(kBX) void k_init(int problem, double lambda, const 
     x[p] = 0.0;
     acc = fma(v, v, acc);
   }
-  if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) {
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
     a.ist[I_DONE] = 0;
     a.ist[I_ITERS] = 0;
     a.ist[I_CONV] = 0;
@@ -377,42 +530,56 @@ __global__ __launch_bounds__(kBX) void k_init(int problem, double lambda, const 
 }
 
 // p = z + beta p_prev (beta = rho_k / rho_{k-1}; p = z at k = 0), q = A p, p.q
+template <int TX, int TY>
 __global__ __launch_bounds__(kBX) void k_dir(const double* z, const double* p_prev,
                                              double* p_cur, double* q, int N, double ih2, Pcg a,
                                              int k) {
+  constexpr int W = TX + 2, H = TY + 2;
+  __shared__ double sp[H * W];
   if (a.ist[I_DONE]) return;
   const bool first = k == 0;
   const double rho = sum_parts(a.p_rho, a.np_rho);
   const double beta = first ? 0.0 : rho / a.sc[S_RHO_PREV];
+  const int tx = tiles_of(N, TX), nt = tx * tiles_of(N, TY);
   double acc = 0.0;
-  PDE_ROWS(N) PDE_COLS(N) {
-    const int64_t p = (int64_t)j * N + i;
-#define PN(o) (first ? z[o] : z[o] + beta * p_prev[o])
-    const double pc = PN(p);
-    const double l = i > 0 ? PN(p - 1) : 0.0;
-    const double rt = i < N - 1 ? PN(p + 1) : 0.0;
-    const double d = j > 0 ? PN(p - N) : 0.0;
-    const double up = j < N - 1 ? PN(p + N) : 0.0;
-#undef PN
-    const double qv = (4.0 * pc - (((l + rt) + d) + up)) * ih2;
-    p_cur[p] = pc;
-    q[p] = qv;
-    acc = fma(pc, qv, acc);
+  for (int t = blockIdx.x; t < nt; t += gridDim.x) {
+    const int i0 = t % tx * TX, j0 = t / tx * TY;
+    for (int e = threadIdx.x; e < H * W; e += kBX) {
+      const int i = i0 + e % W - 1, j = j0 + e / W - 1;
+      double v = 0.0;
+      if (i >= 0 && j >= 0 && i < N && j < N) {
+        const int64_t p = (int64_t)j * N + i;
+        v = first ? z[p] : fma(beta, p_prev[p], z[p]);
+      }
+      sp[e] = v;
+    }
+    __syncthreads();
+    for (int e = threadIdx.x; e < TX * TY; e += kBX) {
+      const int y = e / TX, x = e % TX, i = i0 + x, j = j0 + y, c = (y + 1) * W + x + 1;
+      if (i < N && j < N) {
+        const double pc = sp[c];
+        const double qv = (4.0 * pc - (((sp[c - 1] + sp[c + 1]) + sp[c - W]) + sp[c + W])) * ih2;
+        p_cur[(int64_t)j * N + i] = pc;
+        q[(int64_t)j * N + i] = qv;
+        acc = fma(pc, qv, acc);
+      }
+    }
+    __syncthreads();
   }
   partial_store(acc, a.p_pq);
 }
 
-// alpha = rho_k / (p.q); x += alpha p; r -= alpha q; r.r -> rr[k + 1]
+// alpha = rho_k / (p.q); x += alpha p; r -= alpha q; r.r (grids whose whole
+// cycle runs in k_coarse: there is no k_down to take this)
 __global__ __launch_bounds__(kBX) void k_update(const double* p_cur, const double* q, double* x,
-                                                double* r, int N, Pcg a, int k) {
+                                                double* r, int N, Pcg a) {
   if (a.ist[I_DONE]) return;
   const double rho = sum_parts(a.p_rho, a.np_rho);
   const double alpha = rho / sum_parts(a.p_pq, a.np_fine);
   // rho_k for the next iteration's beta (k_dir read the previous one already)
-  if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) a.sc[S_RHO_PREV] = rho;
+  if (blockIdx.x == 0 && threadIdx.x == 0) a.sc[S_RHO_PREV] = rho;
   double acc = 0.0;
-  PDE_ROWS(N) PDE_COLS(N) {
-    const int64_t p = (int64_t)j * N + i;
+  for (int p = blockIdx.x * kBX + threadIdx.x; p < N * N; p += gridDim.x * kBX) {
     x[p] = fma(alpha, p_cur[p], x[p]);
     const double rv = fma(-alpha, q[p], r[p]);
     r[p] = rv;
@@ -424,9 +591,6 @@ __global__ __launch_bounds__(kBX) void k_update(const double* p_cur, const doubl
 __global__ void k_reset(int* ist) {
   if (threadIdx.x < I_COUNT) ist[threadIdx.x] = 0;
 }
-
-#undef PDE_ROWS
-#undef PDE_COLS
 
 }  // namespace pde
 }  // namespace aa
@@ -443,9 +607,10 @@ struct aa_pde2d {
   double lambda, tol;
   int max_iter, fixed;
   hipStream_t st;
-  int nlev, first_coarse;  // levels >= first_coarse run in k_coarse
+  int nlev, first_lds;     // levels >= first_lds run in k_coarse
+  int first_mat;           // levels >= first_mat are its matrix (nlev: none)
   Lev lev[kMaxLevels];
-  double *r, *z, *e0, *p[2], *q, *sc, *p_rr, *p_rho, *p_pq;
+  double *r[2], *z, *p[2], *q, *sc, *p_rr, *p_rho, *p_pq, *mat;
   int* ist;
   int last_iters, last_conv, predicted;
 };
@@ -468,9 +633,9 @@ int hierarchy(int64_t N, int* sizes) {
   return L;
 }
 
-int first_coarse_level(const int* sizes, int L) {
+int first_level(const int* sizes, int L, int most) {
   for (int l = 0; l < L; ++l)
-    if (sizes[l] <= kCoarseN) return l;
+    if (sizes[l] <= most) return l;
   return -1;
 }
 
@@ -488,9 +653,10 @@ size_t layout(int64_t N, int max_iter, const int* sizes, int L, aa_pde2d* c, cha
   double* p_rr = (double*)take(kMaxWG * sizeof(double));
   double* p_rho = (double*)take(kMaxWG * sizeof(double));
   double* p_pq = (double*)take(kMaxWG * sizeof(double));
-  double* r = (double*)take(n * 8);
+  double* mat = (double*)take(kMatN * kMatN * kMatN * kMatN * sizeof(double));
+  double* r0 = (double*)take(n * 8);
+  double* r1 = (double*)take(n * 8);
   double* z = (double*)take(n * 8);
-  double* e0 = (double*)take(n * 8);
   double* p0 = (double*)take(n * 8);
   double* p1 = (double*)take(n * 8);
   double* q = (double*)take(n * 8);
@@ -500,9 +666,10 @@ size_t layout(int64_t N, int max_iter, const int* sizes, int L, aa_pde2d* c, cha
     c->p_rr = p_rr;
     c->p_rho = p_rho;
     c->p_pq = p_pq;
-    c->r = r;
+    c->mat = mat;
+    c->r[0] = r0;
+    c->r[1] = r1;
     c->z = z;
-    c->e0 = e0;
     c->p[0] = p0;
     c->p[1] = p1;
     c->q = q;
@@ -510,31 +677,24 @@ size_t layout(int64_t N, int max_iter, const int* sizes, int L, aa_pde2d* c, cha
   const double h = 1.0 / (double)(N + 1);
   for (int l = 0; l < L; ++l) {
     const size_t nl = (size_t)sizes[l] * (size_t)sizes[l];
-    double *lr = r, *le = e0, *lz = z;
+    double *lb = nullptr, *lz = z;
     if (l > 0) {
-      lr = (double*)take(nl * 8);
-      le = (double*)take(nl * 8);
+      lb = (double*)take(nl * 8);
       lz = (double*)take(nl * 8);
     }
     if (c) {
-      const double H = h * (double)(1ll << l);
-      c->lev[l] = Lev{sizes[l], H * H, 1.0 + (double)(1ll << l), lr, le, lz};
+      const double H = h * (double)(1ll << l), dl = 1.0 + (double)(1ll << l);
+      c->lev[l] = Lev{sizes[l], H * H, 1.0 / (2.0 + dl), 1.0 / (2.0 * dl), lb, lz};
     }
   }
   return off;
 }
 
-dim3 grid_for(int N) {
-  const int gx = (N + kBX - 1) / kBX;
-  int gy = kMaxWG / gx;
-  if (gy < 1) gy = 1;
-  if (gy > N) gy = N;
-  return dim3((unsigned)gx, (unsigned)gy);
-}
-
-dim3 block_for(int N) {
-  const int bx = N >= kBX ? kBX : ((N + 63) / 64) * 64;
-  return dim3((unsigned)bx);
+// workgroups of a tiled kernel on an N x N level
+int tile_grid(int N) {
+  const int64_t nt = N >= kTileBig ? (int64_t)tiles_of(N, 64) * tiles_of(N, 16)
+                                   : (int64_t)tiles_of(N, 32) * tiles_of(N, 8);
+  return (int)(nt < kMaxWG ? nt : kMaxWG);
 }
 
 Pcg pcg_args(const aa_pde2d* c) {
@@ -544,59 +704,102 @@ Pcg pcg_args(const aa_pde2d* c) {
   a.p_rr = c->p_rr;
   a.p_rho = c->p_rho;
   a.p_pq = c->p_pq;
-  const dim3 g = grid_for(c->N);
-  a.np_fine = (int)(g.x * g.y);
-  a.np_rho = c->first_coarse == 0 ? 1 : a.np_fine;  // r.z from the coarse kernel
+  a.np_fine = tile_grid(c->N);
+  a.np_rho = c->first_lds == 0 ? 1 : a.np_fine;  // r.z from the coarse kernel
   a.tol2 = c->tol * c->tol;
   a.max_iter = c->max_iter;
   a.fixed = c->fixed;
   return a;
 }
 
-// one V-cycle on r (level 0) into z; `check` runs the stopping test before
-// iteration k in the first kernel, `dot` stores rho_k = r . z
-hipError_t launch_vcycle(const aa_pde2d* c, const Pcg& a, int k, int check, int dot) {
-  const int fc = c->first_coarse;
-  for (int l = 0; l < fc; ++l) {
-    const Lev& L = c->lev[l];
-    hipLaunchKernelGGL(k_pre, grid_for(L.N), block_for(L.N), 0, c->st, L, a, k, check && l == 0);
-    const Lev& Cl = c->lev[l + 1];
-    hipLaunchKernelGGL(k_restrict, grid_for(Cl.N), block_for(Cl.N), 0, c->st, L, Cl, a);
-  }
+CoarseArgs coarse_args(const aa_pde2d* c, int from, int to, int nmat) {
   CoarseArgs ca;
   memset(&ca, 0, sizeof(ca));
-  ca.r_in = c->lev[fc].r;
-  ca.z_out = c->lev[fc].z;
-  ca.nlev = c->nlev - fc;
-  for (int l = fc; l < c->nlev; ++l) {
-    ca.N[l - fc] = c->lev[l].N;
-    ca.H2[l - fc] = c->lev[l].H2;
-    ca.dl[l - fc] = c->lev[l].dlast;
+  ca.scale = 1.0;
+  ca.nlev = to - from;
+  for (int l = from; l < to; ++l) {
+    ca.N[l - from] = c->lev[l].N;
+    ca.i1[l - from] = c->lev[l].i1;
+    ca.i2[l - from] = c->lev[l].i2;
+    ca.off[l - from + 1] = ca.off[l - from] + 2 * (c->lev[l].N + 2) * (c->lev[l].N + 2);
   }
-  hipLaunchKernelGGL(k_coarse, dim3(1), dim3(kCoarseWG), 0, c->st, ca, a, k, check && fc == 0,
-                     dot && fc == 0);
-  for (int l = fc - 1; l >= 0; --l) {
-    const Lev& L = c->lev[l];
-    const Lev& Cl = c->lev[l + 1];
-    hipLaunchKernelGGL(k_post_black, grid_for(L.N), block_for(L.N), 0, c->st, L,
-                       (const double*)Cl.z, Cl.N, a);
-    hipLaunchKernelGGL(k_post_red, grid_for(L.N), block_for(L.N), 0, c->st, L, a, k,
-                       dot && l == 0);
+  ca.nmat = nmat;
+  ca.mat = c->mat;
+  return ca;
+}
+
+template <int MODE>
+void launch_down(const aa_pde2d* c, int l, const DownFine& f, const Pcg& a, int k, int check) {
+  const Lev &L = c->lev[l], &C = c->lev[l + 1];
+  if (L.N >= kTileBig)
+    hipLaunchKernelGGL((k_down<64, 16, MODE>), dim3(tile_grid(L.N)), dim3(kBX), 0, c->st, L, C, f,
+                       a, k, check);
+  else
+    hipLaunchKernelGGL((k_down<32, 8, MODE>), dim3(tile_grid(L.N)), dim3(kBX), 0, c->st, L, C, f,
+                       a, k, check);
+}
+
+template <bool FINE>
+void launch_up(const aa_pde2d* c, int l, const double* r, const Pcg& a, int dot) {
+  const Lev &L = c->lev[l], &C = c->lev[l + 1];
+  if (L.N >= kTileBig)
+    hipLaunchKernelGGL((k_up<64, 16, FINE>), dim3(tile_grid(L.N)), dim3(kBX), 0, c->st, L, r,
+                       (const double*)C.z, C.N, a, dot);
+  else
+    hipLaunchKernelGGL((k_up<32, 8, FINE>), dim3(tile_grid(L.N)), dim3(kBX), 0, c->st, L, r,
+                       (const double*)C.z, C.N, a, dot);
+}
+
+// One V-cycle into z: on r[0] (k = 0), or on r[k & 1] after the PCG update
+// that forms it from the previous iteration's p, q and r (k > 0).  `pcg`: the
+// stopping test before iteration k runs in the first kernel that follows the
+// residual's norm, and rho_k = r . z is stored.
+hipError_t launch_vcycle(const aa_pde2d* c, const Pcg& a, int k, int pcg, double* x) {
+  const int fl = c->first_lds;
+  const double* r = c->r[k & 1];
+  if (fl == 0) {
+    r = c->r[0];  // updated in place
+    if (k > 0)
+      hipLaunchKernelGGL(k_update, dim3(a.np_fine), dim3(kBX), 0, c->st,
+                         (const double*)c->p[(k + 1) & 1], (const double*)c->q, x, c->r[0], c->N,
+                         a);
   }
+  for (int l = 0; l < fl; ++l) {
+    const DownFine f{c->r[l == 0 && k > 0 ? (k + 1) & 1 : 0], c->r[k & 1], c->p[(k + 1) & 1], c->q,
+                     x};
+    if (l > 0)
+      launch_down<DOWN_LEVEL>(c, l, f, a, k, pcg && l == 1);
+    else if (k > 0)
+      launch_down<DOWN_UPDATE>(c, l, f, a, k, 0);
+    else
+      launch_down<DOWN_FIRST>(c, l, f, a, k, 0);
+  }
+  const int to = c->first_mat;
+  CoarseArgs ca = coarse_args(c, fl, to, to < c->nlev ? c->lev[to].N : 0);
+  ca.in = fl == 0 ? r : c->lev[fl].b;
+  if (fl == 0) ca.scale = c->lev[0].H2;
+  ca.z_out = c->lev[fl].z;
+  hipLaunchKernelGGL(k_coarse, dim3(1), dim3(kCoarseWG), 0, c->st, ca, a, k, pcg && fl <= 1,
+                     pcg && fl == 0);
+  for (int l = fl - 1; l > 0; --l) launch_up<false>(c, l, nullptr, a, 0);
+  if (fl > 0) launch_up<true>(c, 0, r, a, pcg);
   return hipGetLastError();
 }
 
+// PCG iteration k: the update of iteration k - 1 and the cycle, then p, q
 hipError_t launch_iteration(const aa_pde2d* c, const Pcg& a, int k, double* x) {
-  hipError_t e = launch_vcycle(c, a, k, 1, 1);
+  hipError_t e = launch_vcycle(c, a, k, 1, x);
   if (e != hipSuccess) return e;
   const int N = c->N;
-  const double h = 1.0 / (double)(N + 1);
+  const double h = 1.0 / (double)(N + 1), ih2 = 1.0 / (h * h);
   double* pc = c->p[k & 1];
   const double* pp = c->p[(k + 1) & 1];
-  hipLaunchKernelGGL(k_dir, grid_for(N), block_for(N), 0, c->st, (const double*)c->z, pp, pc,
-                     c->q, N, 1.0 / (h * h), a, k);
-  hipLaunchKernelGGL(k_update, grid_for(N), block_for(N), 0, c->st, (const double*)pc,
-                     (const double*)c->q, x, c->r, N, a, k);
+  if (N >= kTileBig)
+    hipLaunchKernelGGL((k_dir<64, 16>), dim3(a.np_fine), dim3(kBX), 0, c->st,
+                       (const double*)c->z, pp, pc, c->q, N, ih2, a, k);
+  else
+    hipLaunchKernelGGL((k_dir<32, 8>), dim3(a.np_fine), dim3(kBX), 0, c->st, (const double*)c->z,
+                       pp, pc, c->q, N, ih2, a, k);
   return hipGetLastError();
 }
 
@@ -608,8 +811,8 @@ aa_status solve(aa_pde2d* c, int problem, const double* b, const double* u, doub
   (void)hipGetLastError();
   const Pcg a = pcg_args(c);
   const int N = c->N;
-  hipLaunchKernelGGL(k_init, grid_for(N), block_for(N), 0, c->st, problem, c->lambda, b, u, x,
-                     c->r, N, a);
+  hipLaunchKernelGGL(k_init, dim3(a.np_fine), dim3(kBX), 0, c->st, problem, c->lambda, b, u, x,
+                     c->r[0], N, a);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return AA_EHIP;
   const int last = c->fixed >= 0 ? c->fixed : c->max_iter;
@@ -642,7 +845,7 @@ aa_status aa_pde2d_workspace_size(int64_t N, int max_iter, size_t* bytes) {
   if (!bytes || N < 1 || N > 65536 || max_iter < 1 || max_iter > 100000) return AA_EINVAL;
   int sizes[kMaxLevels];
   const int L = hierarchy(N, sizes);
-  if (L < 1 || first_coarse_level(sizes, L) < 0) return AA_EINVAL;
+  if (L < 1 || first_level(sizes, L, kCoarseN) < 0) return AA_EINVAL;
   *bytes = layout(N, max_iter, sizes, L, nullptr, nullptr);
   return AA_OK;
 }
@@ -670,11 +873,19 @@ aa_status aa_pde2d_init(aa_pde2d** ctx, int64_t N, int problem, double lambda, d
   c->st = (hipStream_t)stream;
   int sizes[kMaxLevels];
   c->nlev = hierarchy(N, sizes);
-  c->first_coarse = first_coarse_level(sizes, c->nlev);
+  c->first_lds = first_level(sizes, c->nlev, kLdsN);
+  c->first_mat = c->nlev;
+  for (int l = c->first_lds + 1; l < c->nlev && c->first_mat == c->nlev; ++l)
+    if (sizes[l] <= kMatN) c->first_mat = l;
   layout(N, max_iter, sizes, c->nlev, c, (char*)d_workspace);
   c->predicted = 8;
   (void)hipGetLastError();
   hipLaunchKernelGGL(k_reset, dim3(1), dim3(64), 0, c->st, c->ist);
+  if (c->first_mat < c->nlev) {
+    const int n = c->lev[c->first_mat].N;
+    hipLaunchKernelGGL(k_matrix, dim3(n * n), dim3(kCoarseWG), 0, c->st,
+                       coarse_args(c, c->first_mat, c->nlev, 0), c->mat);
+  }
   if (hipGetLastError() != hipSuccess) {
     free(c);
     return AA_EHIP;
@@ -706,8 +917,8 @@ aa_status aa_pde2d_vcycle(aa_pde2d* c, const double* d_r, double* d_z) {
   const size_t n = (size_t)c->N * (size_t)c->N;
   hipLaunchKernelGGL(k_reset, dim3(1), dim3(64), 0, c->st, c->ist);
   hipError_t e = hipGetLastError();
-  if (e == hipSuccess) e = hipMemcpyAsync(c->r, d_r, n * 8, hipMemcpyDeviceToDevice, c->st);
-  if (e == hipSuccess) e = launch_vcycle(c, pcg_args(c), 0, 0, 0);
+  if (e == hipSuccess) e = hipMemcpyAsync(c->r[0], d_r, n * 8, hipMemcpyDeviceToDevice, c->st);
+  if (e == hipSuccess) e = launch_vcycle(c, pcg_args(c), 0, 0, nullptr);
   if (e == hipSuccess) e = hipMemcpyAsync(d_z, c->z, n * 8, hipMemcpyDeviceToDevice, c->st);
   return hipst(e);
 }

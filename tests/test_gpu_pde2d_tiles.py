@@ -1,0 +1,42 @@
+"""One multigrid cycle and the solve at sizes where the tiled level kernels and
+the LDS levels have edges: one to eight points (the matrix of the last levels,
+even and odd), odd last levels, the largest LDS level, tiles cut by the grid
+(both tile shapes), against the CPU oracle.  Tolerances as for the other
+sizes: the cycle is a few hundred roundings deep (1e-13 of the largest value),
+the solve's error is set by its own tolerance."""
+import numpy as np
+import pytest
+
+import aa_workloads as W
+from gpu_util import device, rel_inf, to_dev
+from oracle import pde2d as P
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("N", [3, 4, 6, 10, 12, 14, 31, 56, 62, 72, 100, 124, 144, 248, 496, 544, 992])
+def test_cycle_at_tile_edges(N):
+    import torch
+    device()
+    from paper_2110_09667_amd import aa
+    r = W.normal(N, 3, N * N)
+    ctx = aa.PDE2D(N, aa.PDE_BRATU)
+    z = torch.full((N * N,), np.nan, dtype=torch.float64, device="cuda")
+    ctx.vcycle(to_dev(r), z)
+    ref = P.vcycle(r.reshape(N, N), 1.0 / (N + 1)).reshape(-1)
+    assert rel_inf(z.cpu().numpy(), ref) <= 1e-13
+
+
+@pytest.mark.parametrize("N", [6, 62, 72, 124, 544])
+def test_solve_at_tile_edges(N):
+    import torch
+    device()
+    from paper_2110_09667_amd import aa
+    rhs = W.normal(N, 4, N * N)
+    ctx = aa.PDE2D(N, aa.PDE_BRATU)
+    x = torch.full((N * N,), np.nan, dtype=torch.float64, device="cuda")
+    ref, iters, conv = P.pcg(rhs.reshape(N, N), 1.0 / (N + 1), 1e-10, 200)[:3]
+    for _ in range(2):  # the second solve starts from a predicted batch
+        ctx.solve(to_dev(rhs), x)
+        assert ctx.last() == (iters, True) and conv
+        assert rel_inf(x.cpu().numpy(), ref.reshape(-1)) <= 1e-11
