@@ -178,9 +178,10 @@ __device__ __forceinline__ bool pcg_check(const Pcg& a, int k) {
 // grid-wide level kernels: one tile per workgroup and turn
 // --------------------------------------------------------------------------
 
-// Tiles of TX x TY fine points (64 x 16 from 512 points per side; 32 x 8
-// below, where 64 x 16 would leave fewer than 64 workgroups).
-constexpr int kTileBig = 512;
+// Tiles of TX x TY fine points: 64 x 16 from 1024 points per side, where that
+// fills the chip's 1024 resident workgroups in one turn; 32 x 8 below (at 512
+// points 64 x 16 took 6.3 us down and 5.4 us up, 32 x 8 5.7 and 4.2 us).
+constexpr int kTileBig = 1024;
 __host__ __device__ constexpr int tiles_of(int N, int T) { return (N + T - 1) / T; }
 
 // The PCG update that precedes a cycle on the fine grid: alpha = rho / p.q,
@@ -194,50 +195,79 @@ struct DownFine {
   double* x;
 };
 
+// Grid index of this thread's u-th point of a W x H tile whose first point is
+// (i, j), or -1 past the tile or outside the N x N grid.
+template <int W, int H>
+__device__ __forceinline__ int64_t tile_at(int u, int i, int j, int N) {
+  const int e = threadIdx.x + u * kBX;
+  i += e % W;
+  j += e / W;
+  return e < W * H && i >= 0 && j >= 0 && i < N && j < N ? (int64_t)j * N + i : -1;
+}
+
 enum : int { DOWN_LEVEL = 0, DOWN_FIRST = 1, DOWN_UPDATE = 2 };
 
 // Pre-smoothing from zero (red, black) and restriction of one level: reads b
 // (level 0: r), writes the next level's b.  Bound by latency: one read of a
-// tile with a halo of two points, two LDS phases.  At N = 1024 the fine level
-// with the update 14 us (k_update + k_pre + k_restrict: 13 + 8 + 9 us).
+// tile with a halo of two points, every load issued before the first use, two
+// LDS phases.  At N = 1024 the fine level with the update takes 17 us, the
+// levels of 512 to 128 points 3.6 to 5.7 us each; with separate kernels for the
+// update, the smoothing and the restriction they took 13 + 8 + 9 and 9 to 14.
 template <int TX, int TY, int MODE>
 __global__ __launch_bounds__(kBX) void k_down(Lev L, Lev C, DownFine f, Pcg a, int k, int check) {
   constexpr int W = TX + 5, H = TY + 5;  // points 2 I0 - 2 .. 2 I0 + TX + 2
+  constexpr int U = (H * W + kBX - 1) / kBX, V = TX * TY / kBX;
   __shared__ double sb[H * W], se[H * W];
   if (check ? pcg_check(a, k) : a.ist[I_DONE] != 0) return;
-  double alpha = 0.0;
-  if (MODE == DOWN_UPDATE) {
-    const double rho = sum_parts(a.p_rho, a.np_rho);
-    alpha = rho / sum_parts(a.p_pq, a.np_fine);
-    // rho for the next iteration's beta (k_dir read the previous one already)
-    if (blockIdx.x == 0 && threadIdx.x == 0) a.sc[S_RHO_PREV] = rho;
-  }
   const int N = L.N, tx = tiles_of(N, TX), nt = tx * tiles_of(N, TY);
-  double acc = 0.0;
+  const double* src = MODE == DOWN_LEVEL ? L.b : f.r_in;
+  double acc = 0.0, alpha = 0.0;
   for (int t = blockIdx.x; t < nt; t += gridDim.x) {
     const int i0 = t % tx * TX, j0 = t / tx * TY;
-    for (int e = threadIdx.x; e < H * W; e += kBX) {
-      const int y = e / W, x = e % W, i = i0 + x - 2, j = j0 + y - 2;
-      double b = 0.0, red = 0.0;
-      if (i >= 0 && j >= 0 && i < N && j < N) {
-        const int64_t p = (int64_t)j * N + i;
-        if (MODE == DOWN_LEVEL) {
-          b = L.b[p];
-        } else if (MODE == DOWN_FIRST) {
-          b = L.H2 * f.r_in[p];
-        } else {
-          const double rv = fma(-alpha, f.q[p], f.r_in[p]);
-          if (x >= 2 && y >= 2 && x < TX + 2 && y < TY + 2) {
-            f.r_out[p] = rv;
-            f.x[p] = fma(alpha, f.p[p], f.x[p]);
-            acc = fma(rv, rv, acc);
-          }
-          b = L.H2 * rv;
-        }
-        if (((i + j) & 1) == 0) red = b * inv_diag(i, j, N, L.i1, L.i2);
+    // every load of the tile in flight at once, before the scalars they meet
+    double b[U], qv[U], xv[V], pv[V];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int64_t p = tile_at<W, H>(u, i0 - 2, j0 - 2, N);
+      b[u] = src[p < 0 ? 0 : p];
+      if (MODE == DOWN_UPDATE) qv[u] = f.q[p < 0 ? 0 : p];
+    }
+    if (MODE == DOWN_UPDATE) {
+#pragma unroll
+      for (int v = 0; v < V; ++v) {
+        const int64_t p = tile_at<TX, TY>(v, i0, j0, N);
+        xv[v] = f.x[p < 0 ? 0 : p];
+        pv[v] = f.p[p < 0 ? 0 : p];
       }
-      sb[e] = b;
-      se[e] = red;
+      if (t == (int)blockIdx.x) {
+        const double rho = sum_parts(a.p_rho, a.np_rho);
+        alpha = rho / sum_parts(a.p_pq, a.np_fine);
+        // rho for the next iteration's beta (k_dir read the previous one already)
+        if (blockIdx.x == 0 && threadIdx.x == 0) a.sc[S_RHO_PREV] = rho;
+      }
+#pragma unroll
+      for (int v = 0; v < V; ++v) {
+        const int64_t p = tile_at<TX, TY>(v, i0, j0, N);
+        if (p >= 0) f.x[p] = fma(alpha, pv[v], xv[v]);
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int e = threadIdx.x + u * kBX, y = e / W, x = e % W, i = i0 + x - 2, j = j0 + y - 2;
+      const int64_t p = tile_at<W, H>(u, i0 - 2, j0 - 2, N);
+      double v = p >= 0 ? b[u] : 0.0;
+      if (MODE == DOWN_UPDATE && p >= 0) {
+        v = fma(-alpha, qv[u], v);
+        if (x >= 2 && y >= 2 && x < TX + 2 && y < TY + 2) {
+          f.r_out[p] = v;
+          acc = fma(v, v, acc);
+        }
+      }
+      if (MODE != DOWN_LEVEL) v *= L.H2;
+      if (e < H * W) {
+        sb[e] = v;
+        se[e] = ((i + j) & 1) == 0 ? v * inv_diag(i, j, N, L.i1, L.i2) : 0.0;
+      }
     }
     __syncthreads();
     for (int e = threadIdx.x; e < (H - 2) * (W / 2); e += kBX) {
@@ -262,32 +292,52 @@ __global__ __launch_bounds__(kBX) void k_down(Lev L, Lev C, DownFine f, Pcg a, i
 
 // Correction from the coarse level (ec, Nc per side) and post-smoothing (black,
 // red) of one level; on the fine grid b = H^2 r and rho = r.z is formed.
-// Three LDS phases on a tile with a halo of two points.
+// Four LDS phases on a tile with a halo of two points: 10 us on the fine grid at
+// N = 1024, 3.6 to 4.2 us on the levels of 512 to 128 points (two half-sweep
+// kernels: 8 + 12 and 9 to 13).
 template <int TX, int TY, bool FINE>
 __global__ __launch_bounds__(kBX) void k_up(Lev L, const double* r, const double* ec, int Nc,
                                             Pcg a, int dot) {
   constexpr int W = TX + 4, H = TY + 4;
-  __shared__ double sb[H * W], sz[H * W];
+  constexpr int WC = TX / 2 + 3, HC = TY / 2 + 3;  // coarse points i0 / 2 - 2 ..
+  constexpr int U = (H * W + kBX - 1) / kBX, UC = (HC * WC + kBX - 1) / kBX;
+  __shared__ double sb[H * W], sz[H * W], sc[HC * WC];
   if (a.ist[I_DONE]) return;
   const int N = L.N, tx = tiles_of(N, TX), nt = tx * tiles_of(N, TY);
   const double* src = FINE ? r : L.b;
-  const double scale = FINE ? L.H2 : 1.0;
   double acc = 0.0;
   for (int t = blockIdx.x; t < nt; t += gridDim.x) {
     const int i0 = t % tx * TX, j0 = t / tx * TY;
-    for (int e = threadIdx.x; e < H * W; e += kBX) {
-      const int y = e / W, x = e % W, i = i0 + x - 2, j = j0 + y - 2;
-      double b = 0.0, z = 0.0;
-      if (i >= 0 && j >= 0 && i < N && j < N) {
-        b = src[(int64_t)j * N + i];
-        if (FINE) b *= scale;
-        if (((i + j) & 1) == 0)
-          z = b * inv_diag(i, j, N, L.i1, L.i2) + interp_red(i, j, [&](int I, int J) {
-                return I >= 0 && J >= 0 ? ec[(int64_t)J * Nc + I] : 0.0;
-              });
+    double b[U], cv[UC];
+#pragma unroll
+    for (int u = 0; u < UC; ++u) {
+      const int64_t p = tile_at<WC, HC>(u, i0 / 2 - 2, j0 / 2 - 2, Nc);
+      cv[u] = ec[p < 0 ? 0 : p];
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int64_t p = tile_at<W, H>(u, i0 - 2, j0 - 2, N);
+      b[u] = src[p < 0 ? 0 : p];
+    }
+#pragma unroll
+    for (int u = 0; u < UC; ++u) {
+      const int e = threadIdx.x + u * kBX;
+      if (e < HC * WC) sc[e] = tile_at<WC, HC>(u, i0 / 2 - 2, j0 / 2 - 2, Nc) >= 0 ? cv[u] : 0.0;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int e = threadIdx.x + u * kBX, y = e / W, x = e % W, i = i0 + x - 2, j = j0 + y - 2;
+      if (e < H * W) {
+        const bool in = tile_at<W, H>(u, i0 - 2, j0 - 2, N) >= 0;
+        const double v = in ? (FINE ? L.H2 * b[u] : b[u]) : 0.0;
+        sb[e] = v;
+        // coarse point (I, J) is at sc[(J - j0 / 2 + 2) WC + I - i0 / 2 + 2]
+        sz[e] = in && ((i + j) & 1) == 0
+                    ? v * inv_diag(i, j, N, L.i1, L.i2) +
+                          interp_red(x, y, [&](int I, int J) { return sc[(J + 1) * WC + I + 1]; })
+                    : 0.0;
       }
-      sb[e] = b;
-      sz[e] = z;
     }
     __syncthreads();
     for (int e = threadIdx.x; e < (H - 2) * (W / 2 - 1); e += kBX) {
@@ -299,7 +349,9 @@ __global__ __launch_bounds__(kBX) void k_up(Lev L, const double* r, const double
                 inv_diag(i, j, N, L.i1, L.i2);
     }
     __syncthreads();
-    for (int e = threadIdx.x; e < TX * TY; e += kBX) {
+#pragma unroll
+    for (int u = 0; u < TX * TY / kBX; ++u) {
+      const int e = threadIdx.x + u * kBX;
       const int y = e / TX, x = e % TX, i = i0 + x, j = j0 + y, c = (y + 2) * W + x + 2;
       if (i < N && j < N) {
         double z = sz[c];
@@ -537,24 +589,30 @@ __global__ __launch_bounds__(kBX) void k_dir(const double* z, const double* p_pr
   constexpr int W = TX + 2, H = TY + 2;
   __shared__ double sp[H * W];
   if (a.ist[I_DONE]) return;
+  constexpr int U = (H * W + kBX - 1) / kBX;
   const bool first = k == 0;
-  const double rho = sum_parts(a.p_rho, a.np_rho);
-  const double beta = first ? 0.0 : rho / a.sc[S_RHO_PREV];
   const int tx = tiles_of(N, TX), nt = tx * tiles_of(N, TY);
-  double acc = 0.0;
+  double acc = 0.0, beta = 0.0;
   for (int t = blockIdx.x; t < nt; t += gridDim.x) {
     const int i0 = t % tx * TX, j0 = t / tx * TY;
-    for (int e = threadIdx.x; e < H * W; e += kBX) {
-      const int i = i0 + e % W - 1, j = j0 + e / W - 1;
-      double v = 0.0;
-      if (i >= 0 && j >= 0 && i < N && j < N) {
-        const int64_t p = (int64_t)j * N + i;
-        v = first ? z[p] : fma(beta, p_prev[p], z[p]);
-      }
-      sp[e] = v;
+    double zv[U], pv[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int64_t p = tile_at<W, H>(u, i0 - 1, j0 - 1, N);
+      zv[u] = z[p < 0 ? 0 : p];
+      pv[u] = first ? 0.0 : p_prev[p < 0 ? 0 : p];
+    }
+    if (t == (int)blockIdx.x && !first) beta = sum_parts(a.p_rho, a.np_rho) / a.sc[S_RHO_PREV];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int e = threadIdx.x + u * kBX;
+      if (e < H * W)
+        sp[e] = tile_at<W, H>(u, i0 - 1, j0 - 1, N) >= 0 ? fma(beta, pv[u], zv[u]) : 0.0;
     }
     __syncthreads();
-    for (int e = threadIdx.x; e < TX * TY; e += kBX) {
+#pragma unroll
+    for (int u = 0; u < TX * TY / kBX; ++u) {
+      const int e = threadIdx.x + u * kBX;
       const int y = e / TX, x = e % TX, i = i0 + x, j = j0 + y, c = (y + 1) * W + x + 1;
       if (i < N && j < N) {
         const double pc = sp[c];
