@@ -11,10 +11,76 @@ namespace aa {
 // wavefront reductions
 // ---------------------------------------------------------------------------
 
+// Lane exchanges on the vector units (a ds_bpermute shuffle is a trip through
+// LDS, two for a double): lanes 32 and 16 apart swap halves with gfx950's
+// v_permlane*_swap, nearer ones move by DPP.
+typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+
+// One register pair of two lanes classes swapped: x = (a of the lower lanes,
+// b of the lower lanes), y = (a of the upper, b of the upper), lower / upper by
+// lane bit M (32 or 16); x + y is the halving butterfly's step.
+template <int M>
+__device__ __forceinline__ double swap_add(double a, double b) {
+  static_assert(M == 32 || M == 16, "lane bit");
+  const u32x2 ua = __builtin_bit_cast(u32x2, a), ub = __builtin_bit_cast(u32x2, b);
+  u32x2 x, y;
+  if constexpr (M == 32) {
+    const auto lo = __builtin_amdgcn_permlane32_swap(ua.x, ub.x, false, false);
+    const auto hi = __builtin_amdgcn_permlane32_swap(ua.y, ub.y, false, false);
+    x = u32x2{lo[0], hi[0]};
+    y = u32x2{lo[1], hi[1]};
+  } else {
+    const auto lo = __builtin_amdgcn_permlane16_swap(ua.x, ub.x, false, false);
+    const auto hi = __builtin_amdgcn_permlane16_swap(ua.y, ub.y, false, false);
+    x = u32x2{lo[0], hi[0]};
+    y = u32x2{lo[1], hi[1]};
+  }
+  return __builtin_bit_cast(double, x) + __builtin_bit_cast(double, y);
+}
+
+template <int CTRL>
+__device__ __forceinline__ double dpp(double v) {
+  const u32x2 u = __builtin_bit_cast(u32x2, v);
+  u32x2 r;
+  r.x = (unsigned)__builtin_amdgcn_update_dpp(0, (int)u.x, CTRL, 0xf, 0xf, false);
+  r.y = (unsigned)__builtin_amdgcn_update_dpp(0, (int)u.y, CTRL, 0xf, 0xf, false);
+  return __builtin_bit_cast(double, r);
+}
+
+// v of lane ^ M, M in {1, 2, 4, 8}: quad permutations; a reversal of eight
+// (xor 7) and of four (xor 3); a rotation of sixteen by eight.
+template <int M>
+__device__ __forceinline__ double lane_xor(double v) {
+  static_assert(M == 1 || M == 2 || M == 4 || M == 8, "lane bit");
+  if constexpr (M == 1) return dpp<0xB1>(v);
+  else if constexpr (M == 2) return dpp<0x4E>(v);
+  else if constexpr (M == 4) return dpp<0x1B>(dpp<0x141>(v));
+  else return dpp<0x128>(v);
+}
+
+// v + (v of lane ^ M)
+template <int M>
+__device__ __forceinline__ double add_xor(double v) {
+  if constexpr (M >= 16) return swap_add<M>(v, v);
+  else return v + lane_xor<M>(v);
+}
+
 __device__ __forceinline__ double wave_sum(double v) {
-#pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o, 64);
-  return v;
+  v = add_xor<32>(v);
+  v = add_xor<16>(v);
+  v = add_xor<8>(v);
+  v = add_xor<4>(v);
+  v = add_xor<2>(v);
+  return add_xor<1>(v);
+}
+
+// v of lane `lane` (the same in every lane)
+__device__ __forceinline__ double lane_value(double v, int lane) {
+  const u32x2 u = __builtin_bit_cast(u32x2, v);
+  u32x2 r;
+  r.x = (unsigned)__builtin_amdgcn_readlane((int)u.x, lane);
+  r.y = (unsigned)__builtin_amdgcn_readlane((int)u.y, lane);
+  return __builtin_bit_cast(double, r);
 }
 
 // Sum N per-lane values across the 64 lanes at once (N a power of two, <= 64).
@@ -22,29 +88,36 @@ __device__ __forceinline__ double wave_sum(double v) {
 // its values selected by lane bit h and adds its partner's copy of that half.
 // After log2(N) steps lane l holds column (l mod N) summed over the lanes that
 // share its low bits; the remaining xor steps finish the sum.  N - 1 +
-// 6 - log2(N) shuffles instead of 6 N.
+// 6 - log2(N) exchanges instead of 6 N.
 template <int H, int N>
 __device__ __forceinline__ void halve_step(double (&v)[N], int lane) {
-  if constexpr (H >= 1) {
+  if constexpr (H >= 16) {
+#pragma unroll
+    for (int i = 0; i < H; ++i) v[i] = swap_add<H>(v[i], v[i + H]);
+    halve_step<H / 2, N>(v, lane);
+  } else if constexpr (H >= 1) {
     const bool upper = (lane & H) != 0;
 #pragma unroll
     for (int i = 0; i < H; ++i) {
       const double keep = upper ? v[i + H] : v[i];
       const double send = upper ? v[i] : v[i + H];
-      v[i] = keep + __shfl_xor(send, H, 64);
+      v[i] = keep + lane_xor<H>(send);
     }
     halve_step<H / 2, N>(v, lane);
   }
+}
+
+template <int O>
+__device__ __forceinline__ double finish_xor(double r) {
+  if constexpr (O < 64) return finish_xor<2 * O>(add_xor<O>(r));
+  else return r;
 }
 
 template <int N>
 __device__ __forceinline__ double multi_reduce(double (&v)[N]) {
   const int lane = threadIdx.x & 63;
   halve_step<N / 2, N>(v, lane);
-  double r = v[0];
-#pragma unroll
-  for (int o = N; o < 64; o <<= 1) r += __shfl_xor(r, o, 64);
-  return r;
+  return finish_xor<N>(v[0]);
 }
 
 // ---------------------------------------------------------------------------

@@ -17,6 +17,19 @@ namespace aa {
 // dense tails, run by one workgroup once the reduced values are in red[]
 // ---------------------------------------------------------------------------
 
+// Row `row` of columns c0, c0 + step, ... of a column-major matrix (kTailCols
+// of them, those before column 0 or past c0 + step (kTailCols - 1) clamped).
+constexpr int kTailCols = 8;
+__device__ __forceinline__ void tail_cols(const double* M, int cap, int c0, int step, int row,
+                                          double (&v)[kTailCols]) {
+#pragma unroll
+  for (int u = 0; u < kTailCols; ++u) {
+    int c = c0 + u * step;
+    c = c < 0 ? 0 : (c < cap ? c : cap - 1);
+    v[u] = M[row + (size_t)c * cap];
+  }
+}
+
 // Back substitution R gamma = c (Alg. 2, last line) by one wave: lane l < k1
 // holds c_l in x on entry.  c is also kept in coef1 (free after QRAdd; the
 // learned step reads it as a feature) unless keep_c is false (the lagged
@@ -29,10 +42,26 @@ __device__ __forceinline__ void rhs_backsolve(const Small& sm, int k1, double x,
   const int cap = sm.cap;
   if (keep_c && lane < k1) sm.coef1[lane] = x;
   double gam = 0.0;
-  for (int a = k1 - 1; a >= 0; --a) {
-    const double ga = __shfl(x, a, 64) / sm.R[a + (size_t)a * cap];
-    if (lane < a) x -= sm.R[lane + (size_t)a * cap] * ga;
-    if (lane == a) gam = ga;
+  // lane l reads row l of R; kTailCols columns in flight, the diagonal from
+  // the lane that holds it (one dependent load per column took half of the
+  // finalize: 20 columns 7 us)
+  double r[kTailCols];
+  tail_cols(sm.R, cap, k1 - 1, -1, lane < k1 ? lane : 0, r);
+  for (int a0 = k1 - 1; a0 >= 0; a0 -= kTailCols) {
+    double cur[kTailCols];
+#pragma unroll
+    for (int u = 0; u < kTailCols; ++u) cur[u] = r[u];
+    if (a0 - kTailCols >= 0)
+      tail_cols(sm.R, cap, a0 - kTailCols, -1, lane < k1 ? lane : 0, r);
+#pragma unroll
+    for (int u = 0; u < kTailCols; ++u) {
+      const int a = a0 - u;
+      if (a >= 0) {
+        const double ga = lane_value(x, a) / lane_value(cur[u], a);
+        if (lane < a) x -= cur[u] * ga;
+        if (lane == a) gam = ga;
+      }
+    }
   }
   if (lane < k1) sm.gamma[lane] = gam;
 }
@@ -53,13 +82,15 @@ __device__ inline void run_tail(const Small& sm, const Tail& t, const double* re
       break;
     case TAIL_NORM: {
       const double nv = sqrt(red[t.idx]);
-      if (tid == 0) {
-        R[k + (size_t)k * cap] = nv;
+      if (tid < 64) {
         // breakdown: R_kk not above 64 eps times the column's norm (the
         // column numerically in the span of the window), or non-finite
-        double col = nv * nv;
-        for (int j = 0; j < k; ++j) col += R[j + (size_t)k * cap] * R[j + (size_t)k * cap];
-        if (!(nv > kBreakdownRel * sqrt(col)) || !isfinite(nv)) *sm.status = AA_EBREAKDOWN;
+        const double rj = lane < k ? R[lane + (size_t)k * cap] : 0.0;
+        const double col = nv * nv + wave_sum(rj * rj);
+        if (lane == 0) {
+          R[k + (size_t)k * cap] = nv;
+          if (!(nv > kBreakdownRel * sqrt(col)) || !isfinite(nv)) *sm.status = AA_EBREAKDOWN;
+        }
       }
       if (t.rhs) {
         // c_k = q_k^T f = (w^T f) / R_kk; c_0..c_{k-1} were stashed in gamma
@@ -92,11 +123,23 @@ __device__ inline void run_tail(const Small& sm, const Tail& t, const double* re
         for (int i = tid; i < k; i += nthr) sm.gamma[i] = red[t.zoff + i];
       if (tid < 64) {
         double x = (lane < k) ? red[lane] : 0.0;
-        for (int b = 0; b < k; ++b) {
-          const double rb = __shfl(x, b, 64);
-          if (lane > b && lane < k) {
-            const double tab = (lane == k - 1) ? red[k + b] : T[lane + (size_t)b * cap];
-            x -= tab * rb;
+        // rows 0..k-2 of T in memory, kTailCols columns in flight (row k-1,
+        // being written, comes from red)
+        const int row = lane < k ? lane : 0;
+        double tc[kTailCols];
+        tail_cols(T, cap, 0, 1, row, tc);
+        for (int b0 = 0; b0 < k; b0 += kTailCols) {
+          double cur[kTailCols];
+#pragma unroll
+          for (int u = 0; u < kTailCols; ++u) cur[u] = tc[u];
+          if (b0 + kTailCols < k) tail_cols(T, cap, b0 + kTailCols, 1, row, tc);
+#pragma unroll
+          for (int u = 0; u < kTailCols; ++u) {
+            const int b = b0 + u;
+            if (b < k - 1) {  // (no row below the last)
+              const double rb = lane_value(x, b);
+              if (lane > b && lane < k) x -= (lane == k - 1 ? red[k + b] : cur[u]) * rb;
+            }
           }
         }
         if (lane < k) {
@@ -751,25 +794,28 @@ __device__ inline void givens_body(const Small& sm, int k, double* H) {
     H[i + j * k] = sm.R[i + (size_t)(j + 1) * cap];
   }
   __syncthreads();
-  for (int j = 0; j < nc; ++j) {
-    const double x = H[j + j * k], y = H[(j + 1) + j * k];
-    const double rho = hypot(x, y);
-    const double c = rho > 0.0 ? x / rho : 1.0;
-    const double s = rho > 0.0 ? y / rho : 0.0;
-    __syncthreads();
-    for (int col = j + tid; col < nc; col += nthr) {
-      const double hj = H[j + col * k], hj1 = H[(j + 1) + col * k];
-      H[j + col * k] = c * hj + s * hj1;
-      H[(j + 1) + col * k] = -s * hj + c * hj1;
+  // one wave, lane = column, the current row in registers: no barriers, the
+  // next row's LDS read under the rotation's square root and divisions
+  if (tid < 64) {
+    const int lane = tid, col = lane < nc ? lane : 0;
+    double a = H[col * k], nxt = H[1 + col * k];
+    for (int j = 0; j < nc; ++j) {
+      const double b = nxt;
+      if (j + 1 < nc) nxt = H[(j + 2) + col * k];
+      const double x = lane_value(a, j), y = lane_value(b, j);
+      const double rho = hypot(x, y);
+      const double c = rho > 0.0 ? x / rho : 1.0;
+      const double s = rho > 0.0 ? y / rho : 0.0;
+      const double top = c * a + s * b;
+      a = -s * a + c * b;
+      if (lane >= j && lane < nc) H[j + lane * k] = top;
+      if (lane == 0) {
+        sm.givens[j] = c;
+        sm.givens[cap + j] = s;
+      }
     }
-    if (tid == 0) {
-      sm.givens[j] = c;
-      sm.givens[cap + j] = s;
-    }
-    __syncthreads();
-    if (tid == 0) H[(j + 1) + j * k] = 0.0;
-    __syncthreads();
   }
+  __syncthreads();
   for (int idx = tid; idx < k * k; idx += nthr) {
     const int i = idx % k, j = idx / k;
     sm.R[i + (size_t)j * cap] = (i < nc && j < nc && i <= j) ? H[i + j * k] : 0.0;
