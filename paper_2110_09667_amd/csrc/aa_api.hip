@@ -569,9 +569,32 @@ aa_status fused_step(aa_ctx* c, const double* x, const double* g, double* x_next
     }
     vecs += m_i + 3;
   }
-  hipError_t e = timed(c, AA_K_FUSED, vecs,
-                       [&] { return launch_batch(a, 1, kb, gram, batch_stage_cols(c->m, c->variant, c->flags),
-                                           c->stream); });
+  // A window in step with the iteration index takes the register-resident
+  // kernel; one changed by hand (aa_qr_add / delete / load) the general one.
+  const bool resident = resident_fits(c->n, c->m) && (i > c->m ? c->k >= 1 : c->k < c->m);
+  StepArgs s{};
+  if (resident) {
+    s.n = c->n; s.ld = c->ldq; s.m = c->m; s.k = c->k;
+    s.m_i = (int)(i < c->m ? i : c->m);
+    s.m_prev = c->m_i;
+    s.slot = i > 0 ? (int)((i - 1) % c->m) : 0;
+    s.slot0 = (int)((i - s.m_i) % c->m);
+    s.iter = i;
+    s.first = i == 0;
+    s.flags = c->flags;
+    s.x = x; s.g = g; s.xn = x_next;
+    s.f_prev = c->f_prev; s.g_prev = c->g_prev; s.Q = c->Q; s.ring = c->ring;
+    s.sm = c->sm;
+    s.sm.stop = c->stop_dev;
+    s.state = c->d_bstate;
+    s.stop_mode = c->stop_mode;
+    s.stop_tol = c->stop_tol;
+  }
+  hipError_t e = timed(c, AA_K_FUSED, vecs, [&] {
+    return resident ? launch_resident(s, c->variant, c->stream)
+                    : launch_batch(a, 1, kb, gram,
+                                   batch_stage_cols(c->m, c->variant, c->flags), c->stream);
+  });
   if (e != hipSuccess) return AA_EHIP;
   if (i == 0) {
     c->iter = 1;

@@ -258,6 +258,25 @@ struct BatchArgs {
   float dscale;           // scale of dout (1 / count)
 };
 
+// One iteration of a single instance in one workgroup with its vectors in
+// registers (aa_resident.hip), for the shapes resident_fits accepts.
+struct StepArgs {
+  int64_t n, ld;          // length, leading dimension of Q / ring
+  int m, k;               // window, columns of Q on entry
+  int m_i, m_prev;        // window of this iteration and of the one before it
+  int slot, slot0;        // ring slots of this and of the oldest Delta g
+  int64_t iter;
+  int first;              // i = 0: x_1 = G(x_0)
+  unsigned flags;
+  const double* x; const double* g; double* xn;
+  double* f_prev; double* g_prev; double* Q; double* ring;
+  Small sm;               // with its stop state
+  BState* state;          // keeps m_i for the other one-workgroup kernel
+  int stop_mode; double stop_tol;
+};
+bool resident_fits(int64_t n, int m);
+hipError_t launch_resident(const StepArgs&, int variant, hipStream_t);
+
 // stage_cols: largest number of columns the Gram staging holds (0: none);
 // dynamic LDS = max(kbucket^2, gram_lds_doubles(stage_cols)) doubles.
 // pairs: row pairs per lane per tile of the batched kernel's passes (4 or 2:
