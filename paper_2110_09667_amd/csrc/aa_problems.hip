@@ -9,6 +9,7 @@
 
 namespace aa {
 
+// Any size (more than 2^31 points, or more per side than the tiles address).
 __global__ __launch_bounds__(256) void k_stencil(int dim, int64_t s, double ih2, double omega,
                                                  double c, const double* __restrict__ f,
                                                  const double* __restrict__ u,
@@ -18,52 +19,50 @@ __global__ __launch_bounds__(256) void k_stencil(int dim, int64_t s, double ih2,
     out[p] = stencil_point(u, f, dim, s, ih2, omega, c, p);
 }
 
-// dim >= 2: one workgroup per tile of TY consecutive grid rows (y0 .. y0+TY-1
-// at one z), its threads along x: the tile's coordinates come from one scalar
-// division per workgroup instead of three 64-bit divisions per point (256^3:
-// 151 -> 142 us).  Same arithmetic, in the same order, as stencil_point.
-// Tiles of 4, 8 or 16 rows (more y neighbours found in the workgroup's own
-// reads) measured no faster in 3D and slower in 2D (fewer workgroups), so a
-// tile is one row.  f and the output are streamed non-temporally
-// (AA_STENCIL_NT, default on: 142 -> 136 us at 256^3, 112 -> 104 us in 2D).
-#ifndef AA_STENCIL_TY
-#define AA_STENCIL_TY 1
-#endif
-#ifndef AA_STENCIL_NT
-#define AA_STENCIL_NT 1
-#endif
-constexpr int kStencilTY = AA_STENCIL_TY;
+constexpr int kMarchWG = 1024, kMarchChunk = 16;
 
-__global__ __launch_bounds__(256) void k_stencil_tile(int dim, int s, double ih2, double omega,
-                                                      double c, const double* __restrict__ f,
-                                                      const double* __restrict__ u,
-                                                      double* __restrict__ out, int ntile_y) {
-  const int b = blockIdx.x;
-  const int z = b / ntile_y, y0 = (b % ntile_y) * kStencilTY;  // z = 0 in 2D
-  const int64_t s2 = (int64_t)s * s;
-  for (int ty = 0; ty < kStencilTY; ++ty) {
-    const int y = y0 + ty;
-    if (y >= s) break;
-    const int64_t base = (int64_t)z * s2 + (int64_t)y * s;
-    for (int x = threadIdx.x; x < s; x += blockDim.x) {
-      const int64_t p = base + x;
-      const double up = u[p];
-      double nb = 0.0;
-      if (x > 0) nb += u[p - 1];
-      if (x < s - 1) nb += u[p + 1];
+// One thread per point of a plane (3D), row (2D) or line segment (1D), marching
+// `chunk` planes along the slowest dimension with the three planes' values in
+// registers.  A plane's points are taken in memory order, so a workgroup's
+// 1024 are a few whole rows and most of the y neighbours are its own reads.
+// What bounds the map is the traffic beyond the eight L2s: consecutive
+// workgroups run on different ones, so with one grid row per workgroup u was
+// fetched five times (three rows, two planes); marching fetches it about 1.7
+// times at s = 256: 140 -> 94 us there (4.3 TB/s of its 3 vectors), 39.7 -> 26.2
+// at s = 160, 13.9 -> 9 at s = 101, 28.5 -> 21.5 for 2048^2 (workgroups of 512
+// or 256 points and chunks of 8 or 32: 100 to 113 us at s = 256, the rest
+// within 5 %).  Same arithmetic, in the same order, as stencil_point.  f
+// and the output are streamed non-temporally.
+template <int DIM>
+__global__ __launch_bounds__(1024) void k_stencil_march(int s, double ih2, double omega, double c,
+                                                        const double* __restrict__ f,
+                                                        const double* __restrict__ u,
+                                                        double* __restrict__ out, int plane,
+                                                        int chunk) {
+  const int q = blockIdx.x * blockDim.x + threadIdx.x;  // point of the plane
+  if (q >= plane) return;
+  const int x = DIM == 3 ? q % s : q, y = DIM == 3 ? q / s : 0;
+  const int z0 = DIM == 1 ? 0 : blockIdx.y * chunk;
+  const int z1 = DIM == 1 ? 1 : z0 + chunk < s ? z0 + chunk : s;
+  int64_t p = (int64_t)z0 * plane + q;
+  double lo = z0 > 0 ? u[p - plane] : 0.0, mid = u[p];
+  for (int z = z0; z < z1; ++z, p += plane) {
+    const bool more = DIM > 1 && z < s - 1;
+    const double hi = more ? u[p + plane] : 0.0;
+    const double fv = __builtin_nontemporal_load(f + p);
+    double nb = 0.0;
+    if (x > 0) nb += u[p - 1];
+    if (x < s - 1) nb += u[p + 1];
+    if (DIM == 3) {
       if (y > 0) nb += u[p - s];
       if (y < s - 1) nb += u[p + s];
-      if (dim >= 3) {
-        if (z > 0) nb += u[p - s2];
-        if (z < s - 1) nb += u[p + s2];
-      }
-      const double au = (2.0 * dim * up - nb) * ih2;
-#if AA_STENCIL_NT
-      __builtin_nontemporal_store(up - omega * (au + c * up * up * up - __builtin_nontemporal_load(f + p)), out + p);
-#else
-      out[p] = up - omega * (au + c * up * up * up - f[p]);
-#endif
     }
+    if (z > 0) nb += lo;
+    if (more) nb += hi;
+    const double au = (2.0 * DIM * mid - nb) * ih2;
+    __builtin_nontemporal_store(mid - omega * (au + c * mid * mid * mid - fv), out + p);
+    lo = mid;
+    mid = hi;
   }
 }
 
@@ -73,17 +72,36 @@ hipError_t launch_stencil(int dim, int64_t s, double h, double omega, double c,
   int64_t n = s;
   if (dim >= 2) n *= s;
   if (dim >= 3) n *= s;
-  if (dim >= 2 && s <= 65536) {
-    const int64_t ntile_y = (s + kStencilTY - 1) / kStencilTY;
-    const int64_t nwg = ntile_y * (dim >= 3 ? s : 1);
-    hipLaunchKernelGGL(k_stencil_tile, dim3((unsigned)nwg), dim3(s < 256 ? (s + 63) / 64 * 64 : 256),
-                       0, st, dim, (int)s, 1.0 / (h * h), omega, c, f, u, out, (int)ntile_y);
-    return hipGetLastError();
+  const double ih2 = 1.0 / (h * h);
+  const int64_t plane = dim == 3 ? s * s : s;
+  if (plane < (1 << 30)) {
+    // workgroups of 1024 points from a quarter million points (256 below: more
+    // of them on the chip), the shortest chunk that leaves one resident round,
+    // at most 16 planes
+    const int64_t wg = n >= 1024 * 256 ? kMarchWG : 256;
+    const int block = (int)(plane < wg ? (plane + 63) / 64 * 64 : wg);
+    const int64_t gx = (plane + block - 1) / block;
+    const int64_t resident = 2048 * 256 / block;  // workgroups the chip holds
+    int64_t chunk = dim == 1 ? 1 : (gx * s + resident - 1) / resident;
+    chunk = chunk > kMarchChunk ? kMarchChunk : chunk;
+    const int64_t gy = dim == 1 ? 1 : (s + chunk - 1) / chunk;
+    if (gy <= 65535) {
+      const dim3 g((unsigned)gx, (unsigned)gy), b((unsigned)block);
+      if (dim == 1)
+        hipLaunchKernelGGL(k_stencil_march<1>, g, b, 0, st, (int)s, ih2, omega, c, f, u, out,
+                           (int)plane, (int)chunk);
+      else if (dim == 2)
+        hipLaunchKernelGGL(k_stencil_march<2>, g, b, 0, st, (int)s, ih2, omega, c, f, u, out,
+                           (int)plane, (int)chunk);
+      else
+        hipLaunchKernelGGL(k_stencil_march<3>, g, b, 0, st, (int)s, ih2, omega, c, f, u, out,
+                           (int)plane, (int)chunk);
+      return hipGetLastError();
+    }
   }
   int64_t blocks = (n + 255) / 256;
   int grid = (int)(blocks < 65536 ? blocks : 65536);
-  hipLaunchKernelGGL(k_stencil, dim3(grid), dim3(256), 0, st, dim, s, 1.0 / (h * h), omega, c,
-                     f, u, out, n);
+  hipLaunchKernelGGL(k_stencil, dim3(grid), dim3(256), 0, st, dim, s, ih2, omega, c, f, u, out, n);
   return hipGetLastError();
 }
 
@@ -160,31 +178,33 @@ __global__ __launch_bounds__(kEmWG) void k_em_partials(EmArgs a) {
 }
 
 // Every workgroup sums the G partials of the six values in the same fixed
-// order (so all agree bit for bit), forms G(mu)_i = sum x w_i / sum w_i and
-// writes its share of the replicas: out[3 r + i] = G(mu)_i.
+// order (so all agree bit for bit; a wave takes the values c, c + 4), forms
+// G(mu)_i = sum x w_i / sum w_i and writes its share of the replicas: entry e
+// is G(mu)_{e mod 3}, two entries a store in memory order.  (One wave summing
+// and a thread writing each replica's three entries 24 bytes apart took 17.5
+// us for 500,000 replicas.)
 __global__ __launch_bounds__(kEmWG) void k_em_broadcast(const double* __restrict__ partials,
                                                         int G, double* __restrict__ out,
-                                                        int64_t nrep) {
-  __shared__ double s_g[3];
+                                                        int64_t n) {
+  __shared__ double s_t[6];
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  if (w == 0) {
-    double t[6];
-#pragma unroll
-    for (int c = 0; c < 6; ++c) {
-      double v = 0.0;
-      for (int g = lane; g < G; g += 64) v += partials[(size_t)c * G + g];
-      t[c] = wave_sum(v);
-    }
-    if (lane < 3) s_g[lane] = t[lane] / t[lane + 3];
+  for (int c = w; c < 6; c += kEmWG / 64) {
+    double v = 0.0;
+    for (int g = lane; g < G; g += 64) v += partials[(size_t)c * G + g];
+    v = wave_sum(v);
+    if (lane == 0) s_t[c] = v;
   }
   __syncthreads();
-  const double g0 = s_g[0], g1 = s_g[1], g2 = s_g[2];
-  for (int64_t r = (int64_t)blockIdx.x * kEmWG + threadIdx.x; r < nrep;
-       r += (int64_t)gridDim.x * kEmWG) {
-    out[3 * r] = g0;
-    out[3 * r + 1] = g1;
-    out[3 * r + 2] = g2;
-  }
+  const double g0 = s_t[0] / s_t[3], g1 = s_t[1] / s_t[4], g2 = s_t[2] / s_t[5];
+  // entries 2 r and 2 r + 1; the launch's stride (pairs) is a multiple of
+  // three, so a thread's phase never changes
+  const int64_t first = (int64_t)blockIdx.x * kEmWG + threadIdx.x;
+  const int ph = (int)((2 * first) % 3);
+  const double a = ph == 0 ? g0 : ph == 1 ? g1 : g2, b = ph == 0 ? g1 : ph == 1 ? g2 : g0;
+  const int64_t npair = n / 2, stride = (int64_t)gridDim.x * kEmWG;
+  for (int64_t r = first; r < npair; r += stride)
+    *reinterpret_cast<f64x2*>(out + 2 * r) = f64x2{a, b};
+  if ((n & 1) && first == 0) out[n - 1] = g2;  // n is a multiple of three
 }
 
 hipError_t launch_em(const double alpha[3], const double sigma[3], const double* x, int64_t N,
@@ -202,10 +222,11 @@ hipError_t launch_em(const double alpha[3], const double sigma[3], const double*
   int64_t g = (N + kEmWG - 1) / kEmWG;
   const int G = (int)(g > kEmMaxGrid ? kEmMaxGrid : g);
   hipLaunchKernelGGL(k_em_partials, dim3(G), dim3(kEmWG), 0, st, a);
-  const int64_t nrep = n / 3;
-  int64_t gb = (nrep + kEmWG - 1) / kEmWG;
-  const int GB = (int)(gb > 2048 ? 2048 : (gb < 1 ? 1 : gb));
-  hipLaunchKernelGGL(k_em_broadcast, dim3(GB), dim3(kEmWG), 0, st, work, G, out, nrep);
+  // a multiple of three workgroups (the stores' stride), at most three a
+  // compute unit
+  int64_t gb = (n / 2 + kEmWG - 1) / kEmWG;
+  const int GB = (int)((gb < 768 ? (gb < 1 ? 1 : gb) : 768) + 2) / 3 * 3;
+  hipLaunchKernelGGL(k_em_broadcast, dim3(GB), dim3(kEmWG), 0, st, work, G, out, n);
   return hipGetLastError();
 }
 
