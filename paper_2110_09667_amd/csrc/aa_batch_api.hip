@@ -44,16 +44,19 @@ struct aa_batch {
   float* d_out = nullptr;   // [count x AA_MLP_OUTPUTS]
   float* d_dout = nullptr;  // [count x AA_MLP_OUTPUTS]
   int pairs = 4;            // row pairs per lane per tile of the persistent kernel
-  // split path: once few instances are active, the large ones leave the
-  // persistent kernel and run on the grid-wide passes (many workgroups each)
+  // instances with many workgroups each (aa_batch_wide.hip): those the cost
+  // model takes out of the persistent kernel for good, and those the split
+  // policy adds once few are active
   int64_t split_min_n = 65536;  // 0: never
   int split_active_max = 0;     // split when at most this many are active (0: CUs / 4)
-  int* d_skip = nullptr;        // [count] 1: left out of the persistent kernel
-  StopState* d_stops = nullptr; // [count] stop state of a split instance
-  double* d_partials = nullptr; // shared by the split instances' passes
-  std::vector<BInst> hinst;     // host copies of the descriptors
-  std::vector<int> split;       // instances on the split path
-  std::vector<aa_ctx*> views;   // their contexts
+  std::vector<int> cost_wide, split;
+  std::vector<BInst> hinst;      // host copies of the descriptors
+  int* d_skip = nullptr;         // [count] kWideNo: in the persistent kernel
+  WideItem* d_items = nullptr;   // [items_cap]
+  WideItem* d_list = nullptr;    // [count]
+  int64_t items_cap = 0;
+  int nitems = 0, nwide = 0;     // chunks and instances of the wide passes
+  double* d_partials = nullptr;  // shared by them
 };
 
 namespace {
@@ -83,16 +86,27 @@ size_t instance_bytes(int64_t n, int m, bool learned) {
   return b;
 }
 
-// Reduction partials of one grid-wide pass (the split path's passes run one
-// after another and share them): 199 values x 8192 workgroups, as a
-// single-instance context holds.
-constexpr size_t kSplitPartials = (size_t)(3 * AA_MAX_COLS + 4) * 8192;
+// Reduction partials of the wide passes (every instance's widest reduction,
+// value by chunk): 199 values x 8192 workgroups, as a single-instance context
+// holds.
+constexpr size_t kWidePartials = (size_t)(3 * AA_MAX_COLS + 4) * 8192;
+constexpr int64_t kWideTile = 1024;     // rows of a tile of the wide passes
+constexpr int64_t kWideChunks = 512;    // most chunks of an instance
+constexpr int64_t kWideMaxN = 1 << 30;  // their row indices are 32 bits in the stencil
 
-size_t header_bytes(int count, bool learned) {
+int64_t wide_tiles(int64_t n) { return (n + kWideTile - 1) / kWideTile; }
+
+int64_t wide_items_cap(int count, const aa_batch_instance* inst) {
+  int64_t t = 0;
+  for (int j = 0; j < count; ++j) t += std::min(wide_tiles(inst[j].n), kWideChunks);
+  return t;
+}
+
+size_t header_bytes(int count, const aa_batch_instance* inst, bool learned) {
   size_t b = align_up(sizeof(BInst) * count) + align_up(sizeof(BState) * count) +
              align_up(sizeof(int) * count) + align_up(sizeof(unsigned));
-  b += align_up(sizeof(int) * count) + align_up(sizeof(StopState) * count) +
-       align_up(sizeof(double) * kSplitPartials);
+  b += align_up(sizeof(int) * count) + align_up(sizeof(WideItem) * wide_items_cap(count, inst)) +
+       align_up(sizeof(WideItem) * count) + align_up(sizeof(double) * kWidePartials);
   if (learned)
     b += align_up(sizeof(float) * count * kFeat) + 2 * align_up(sizeof(float) * count * kOuts);
   return b;
@@ -119,7 +133,7 @@ hipError_t enqueue_mode(aa_batch* b, int mode, float dscale) {
   a.max_iter = b->max_iter;
   a.ov_iter = -1;
   a.mode = mode;
-  a.skip = mode == BM_PLAIN && !b->split.empty() ? b->d_skip : nullptr;
+  a.skip = mode == BM_PLAIN && b->nwide > 0 ? b->d_skip : nullptr;
   a.feat = b->d_feat;
   a.out = b->d_out;
   a.dout = b->d_dout;
@@ -138,38 +152,141 @@ hipError_t enqueue_mode(aa_batch* b, int mode, float dscale) {
                       batch_stage_cols(b->mmax, b->variant, b->flags), b->stream, b->pairs);
 }
 
-// One iteration of every split instance on the grid-wide passes: G by the
-// stencil kernel, aa_step on the instance's view, then its batched state.
-hipError_t enqueue_split(aa_batch* b) {
-  for (size_t t = 0; t < b->split.size(); ++t) {
-    const int j = b->split[t];
-    const BInst& I = b->hinst[j];
-    hipError_t e = launch_stencil(I.dim, I.s, I.h, I.omega, I.c, I.f, I.x, I.g, b->stream);
-    if (e != hipSuccess) return e;
-    if (aa_step(b->views[t], I.x, I.g, I.x) != AA_OK) return hipErrorUnknown;
-    int64_t it = 0;
-    int k = 0, mi = 0;
-    view_counters(b->views[t], &it, &k, &mi);
-    e = launch_split_state(b->d_state + j, b->d_stops + j, I.sm, k, mi, b->stream);
-    if (e != hipSuccess) return e;
-  }
-  return hipSuccess;
+// Values of an instance's widest reduction in the wide passes.
+int64_t wide_values(const aa_batch* b, int j) {
+  const int64_t m = b->m[j];
+  return std::max(3 * m + 4, b->gram ? m * (m + 1) / 2 : (int64_t)0);
 }
 
-// Return every split instance to the persistent kernel (its memory layout is
-// the same on both paths).
-hipError_t merge_split(aa_batch* b) {
-  if (b->split.empty()) return hipSuccess;
-  for (aa_ctx* v : b->views) view_destroy(v);
-  b->views.clear();
+// Vectors of n doubles a recycled iteration moves (fused ICWY: the others
+// differ by what the threshold below does not see).
+double iter_bytes(const aa_batch* b, int j) {
+  return 8.0 * (double)b->n[j] * (4.0 * b->m[j] + 18.0);
+}
+
+// The instances that gain from many workgroups: those with more bytes than a
+// threshold, the one that makes an iteration shortest under these rates
+// (measured on the 2D tables): the persistent kernel takes as long as its
+// largest instance on one workgroup (20 GB/s) or as all of them together (4.8
+// TB/s); the wide passes stream 4.9 TB/s and cost their launches.  The
+// 4096-instance table (100 GB, largest 0.2 GB) stays persistent; of 512 such
+// instances (12.5 GB) nearly all bytes go wide.
+void choose_wide(aa_batch* b) {
+  std::vector<int> ord(b->count);
+  std::iota(ord.begin(), ord.end(), 0);
+  std::stable_sort(ord.begin(), ord.end(),
+                   [&](int x, int y) { return iter_bytes(b, x) > iter_bytes(b, y); });
+  double total = 0.0;
+  for (int j : ord) total += iter_bytes(b, j);
+  constexpr double kOne = 20e9, kAll = 4.8e12, kWide = 4.9e12, kLaunch = 4.5e-6;
+  const double passes = 12.0 + (b->variant == AA_MGS ? 2.0 * b->mmax : 0.0);
+  auto cost = [&](double wide, int next) {  // the first `next` instances are wide
+    double t = next > 0 ? passes * kLaunch + wide / kWide : 0.0;
+    if (next < b->count)
+      t += std::max(iter_bytes(b, ord[next]) / kOne, (total - wide) / kAll);
+    return t;
+  };
+  double best = 0.95 * cost(0.0, 0), wide = 0.0;  // by 5 % at least
+  int take = 0;
+  for (int i = 0; i < b->count && b->n[ord[i]] < kWideMaxN; ++i) {
+    wide += iter_bytes(b, ord[i]);
+    const double t = cost(wide, i + 1);
+    if (t < best) {
+      best = t;
+      take = i + 1;
+    }
+  }
+  b->cost_wide.assign(ord.begin(), ord.begin() + take);
+}
+
+// Chunks of every wide instance (largest first), their partials, the tables.
+// Chunks are as long as leaves about 4096 of them, at most 16 tiles, longer
+// where the tables or the partials would not hold them; instances that even
+// one chunk each does not fit stay in the persistent kernel.
+aa_status plan_wide(aa_batch* b) {
+  drop_graph(b);
+  std::vector<int> set = b->split;
+  for (int j : b->cost_wide)
+    if (std::find(b->split.begin(), b->split.end(), j) == b->split.end()) set.push_back(j);
+  std::stable_sort(set.begin(), set.end(),
+                   [&](int x, int y) { return iter_bytes(b, x) > iter_bytes(b, y); });
+  size_t room = 0, keep = 0;
+  while (keep < set.size() && room + wide_values(b, set[keep]) <= kWidePartials)
+    room += wide_values(b, set[keep++]);
+  set.resize(keep);
+  int64_t tiles = 0;
+  for (int j : set) tiles += wide_tiles(b->n[j]);
+  int64_t per = std::min<int64_t>(16, std::max<int64_t>(1, tiles / 4096));
+  auto chunks = [&](int j) {
+    const int64_t t = wide_tiles(b->n[j]);
+    const int64_t q = std::max(per, (t + kWideChunks - 1) / kWideChunks);
+    return (t + q - 1) / q;
+  };
+  for (;; per *= 2) {
+    int64_t items = 0;
+    size_t part = 0;
+    for (int j : set) {
+      items += chunks(j);
+      part += (size_t)(wide_values(b, j) * chunks(j));
+    }
+    if (items <= b->items_cap && part <= kWidePartials) break;
+  }
+  std::vector<int> skip(b->count, (int)kWideNo);
+  std::vector<WideItem> items, list;
+  size_t off = 0;
+  for (int j : set) {
+    const int c = (int)chunks(j);
+    skip[j] = std::find(b->split.begin(), b->split.end(), j) != b->split.end() ? kWideSplit
+                                                                               : kWideCost;
+    b->hinst[j].sm.partials = b->d_partials + off;
+    off += (size_t)(wide_values(b, j) * c);
+    list.push_back(WideItem{j, 0, c});
+    for (int q = 0; q < c; ++q) items.push_back(WideItem{j, q, c});
+  }
+  for (size_t t = 0; t < b->split.size();)
+    if (skip[b->split[t]] != kWideSplit) b->split.erase(b->split.begin() + t);
+    else ++t;
+  b->nitems = (int)items.size();
+  b->nwide = (int)list.size();
+  auto put = [&](void* dst, const void* src, size_t bytes) {
+    return bytes == 0 ||
+           hipMemcpyAsync(dst, src, bytes, hipMemcpyHostToDevice, b->stream) == hipSuccess;
+  };
+  const bool ok = put(b->d_skip, skip.data(), sizeof(int) * skip.size()) &&
+                  put(b->d_items, items.data(), sizeof(WideItem) * items.size()) &&
+                  put(b->d_list, list.data(), sizeof(WideItem) * list.size()) &&
+                  put(b->d_inst, b->hinst.data(), sizeof(BInst) * b->hinst.size()) &&
+                  hipStreamSynchronize(b->stream) == hipSuccess;
+  return ok ? AA_OK : AA_EHIP;
+}
+
+hipError_t enqueue_wide(aa_batch* b) {
+  WideArgs a{};
+  a.inst = b->d_inst;
+  a.state = b->d_state;
+  a.items = b->d_items;
+  a.list = b->d_list;
+  a.split = b->d_skip;
+  a.variant = b->variant;
+  a.flags = b->flags;
+  a.tol = b->tol;
+  a.max_iter = b->max_iter;
+  a.kgram = b->kbucket < 16 ? 16 : b->kbucket;
+  return launch_wide(a, b->nitems, b->nwide, b->kbucket, b->mmax, b->gram,
+                     batch_stage_cols(b->mmax, b->variant, b->flags), b->stream);
+}
+
+// End the split policy's choices (the cost model's stay).
+aa_status merge_split(aa_batch* b) {
+  if (b->split.empty()) return AA_OK;
   b->split.clear();
-  return launch_set_int(b->d_skip, b->count, 0, b->stream);
+  return plan_wide(b);
 }
 
 // Split policy, evaluated when a run starts: once at most split_active_max
 // instances are active (the persistent kernel no longer fills the chip), the
-// active instances with n >= split_min_n leave it for the grid-wide passes;
-// split instances that have stopped are dropped from the list.
+// active instances with n >= split_min_n leave it; split instances that have
+// stopped are dropped from the list.
 aa_status update_split(aa_batch* b) {
   if (b->split_min_n <= 0) return AA_OK;
   std::vector<BState> hs(b->count);
@@ -177,11 +294,11 @@ aa_status update_split(aa_batch* b) {
                      b->stream) != hipSuccess ||
       hipStreamSynchronize(b->stream) != hipSuccess)
     return AA_EHIP;
+  bool changed = false;
   for (size_t t = 0; t < b->split.size();) {
     if (!hs[b->split[t]].active) {
-      view_destroy(b->views[t]);
-      b->views.erase(b->views.begin() + t);
       b->split.erase(b->split.begin() + t);
+      changed = true;
     } else {
       ++t;
     }
@@ -190,47 +307,34 @@ aa_status update_split(aa_batch* b) {
   for (const BState& st : hs) active += st.active ? 1 : 0;
   int amax = b->split_active_max;
   if (amax <= 0) {
-    // measured crossover of the 2D table's largest instances (n ~ 1.5e5 to
-    // 2.6e5): one workgroup streams ~19 GB/s, one instance on the grid-wide
-    // passes ~1.4 TB/s (launch-bound at that n); below ~80 active instances
-    // the split path wins
+    // a workgroup an instance: with a quarter of the compute units in use an
+    // iteration takes as long as the largest instance
     int dev = 0, cus = 256;
     if (hipGetDevice(&dev) == hipSuccess)
       (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
     amax = cus / 4 > 1 ? cus / 4 : 1;
   }
-  if (active == 0 || active > amax) return AA_OK;
-  std::vector<int> add;
-  for (int j = 0; j < b->count; ++j)
-    if (hs[j].active && !hs[j].pending && hs[j].iter >= 1 && b->n[j] >= b->split_min_n &&
-        std::find(b->split.begin(), b->split.end(), j) == b->split.end())
-      add.push_back(j);
-  for (int j : add) {
-    const BState& st = hs[j];
-    StopState s0{};
-    s0.done = 0;
-    s0.cur = st.iter;
-    if (hipMemcpyAsync(b->d_stops + j, &s0, sizeof(s0), hipMemcpyHostToDevice, b->stream) !=
-        hipSuccess)
-      return AA_EHIP;
-    const int one = 1;
-    if (hipMemcpyAsync(b->d_skip + j, &one, sizeof(int), hipMemcpyHostToDevice, b->stream) !=
-        hipSuccess)
-      return AA_EHIP;
-    aa_ctx* v = view_create(b->hinst[j], b->variant, b->flags, b->d_partials, b->d_stops + j,
-                            st.iter, st.k, st.m_i, b->tol, b->max_iter, b->stream);
-    if (!v) return AA_EINVAL;
-    b->split.push_back(j);
-    b->views.push_back(v);
-  }
-  if (!add.empty()) drop_graph(b);
-  return hipStreamSynchronize(b->stream) == hipSuccess ? AA_OK : AA_EHIP;
+  if (active > 0 && active <= amax)
+    for (int j = 0; j < b->count; ++j)
+      if (hs[j].active && !hs[j].pending && hs[j].iter >= 1 && b->n[j] >= b->split_min_n &&
+          b->n[j] < kWideMaxN &&
+          std::find(b->split.begin(), b->split.end(), j) == b->split.end()) {
+        b->split.push_back(j);
+        changed = true;
+      }
+  return changed ? plan_wide(b) : AA_OK;
 }
 
 hipError_t enqueue(aa_batch* b, int iters) {
   for (int i = 0; i < iters; ++i) {
-    hipError_t e = enqueue_mode(b, BM_PLAIN, 0.f);
-    if (e != hipSuccess) return e;
+    if (b->nwide < b->count) {
+      const hipError_t e = enqueue_mode(b, BM_PLAIN, 0.f);
+      if (e != hipSuccess) return e;
+    }
+    if (b->nwide > 0) {
+      const hipError_t e = enqueue_wide(b);
+      if (e != hipSuccess) return e;
+    }
   }
   return hipSuccess;
 }
@@ -244,9 +348,10 @@ aa_status aa_batch_workspace_size(int count, const aa_batch_instance* inst, int 
   if (count < 1 || !inst || !bytes || variant < AA_MGS || variant > AA_ICWY) return AA_EINVAL;
   if (flags & AA_ICWY_T_TRANSFORM) return AA_EINVAL;  // one-workgroup step: Gram refresh only
   const bool learned = (flags & AA_BATCH_LEARNED) != 0;
-  size_t tot = header_bytes(count, learned);
-  for (int j = 0; j < count; ++j) {
+  for (int j = 0; j < count; ++j)
     if (!valid_instance(inst[j])) return AA_EINVAL;
+  size_t tot = header_bytes(count, inst, learned);
+  for (int j = 0; j < count; ++j) {
     if (learned && inst[j].m > kWin) return AA_EINVAL;  // features cover a 20-column window
     tot += instance_bytes(inst[j].n, inst[j].m, learned);
   }
@@ -280,8 +385,10 @@ aa_status aa_batch_init(aa_batch** out, int count, const aa_batch_instance* inst
   b->d_order = (int*)(base + o); o = align_up(o + sizeof(int) * count);
   b->d_counter = (unsigned*)(base + o); o = align_up(o + sizeof(unsigned));
   b->d_skip = (int*)(base + o); o = align_up(o + sizeof(int) * count);
-  b->d_stops = (StopState*)(base + o); o = align_up(o + sizeof(StopState) * count);
-  b->d_partials = (double*)(base + o); o = align_up(o + sizeof(double) * kSplitPartials);
+  b->items_cap = wide_items_cap(count, inst);
+  b->d_items = (WideItem*)(base + o); o = align_up(o + sizeof(WideItem) * b->items_cap);
+  b->d_list = (WideItem*)(base + o); o = align_up(o + sizeof(WideItem) * count);
+  b->d_partials = (double*)(base + o); o = align_up(o + sizeof(double) * kWidePartials);
   b->learned = (flags & AA_BATCH_LEARNED) != 0;
   if (b->learned) {
     b->d_feat = (float*)(base + o); o = align_up(o + sizeof(float) * count * kFeat);
@@ -336,16 +443,13 @@ aa_status aa_batch_init(aa_batch** out, int count, const aa_batch_instance* inst
   b->kbucket = bucket(mmax);
   b->mmax = mmax;
   b->gram = batch_needs_gram(variant, flags);
-  hipError_t e = hipMemcpyAsync(b->d_inst, hi.data(), sizeof(BInst) * count,
-                                hipMemcpyHostToDevice, b->stream);
-  if (e == hipSuccess)
-    e = hipMemcpyAsync(b->d_state, hs.data(), sizeof(BState) * count, hipMemcpyHostToDevice,
-                       b->stream);
-  if (e == hipSuccess) e = launch_batch_init(b->d_inst, count, b->stream);
-  if (e == hipSuccess) e = launch_set_int(b->d_skip, count, 0, b->stream);
-  if (e == hipSuccess) e = hipStreamSynchronize(b->stream);
   b->hinst = hi;
-  if (e != hipSuccess) {
+  choose_wide(b);
+  hipError_t e = hipMemcpyAsync(b->d_state, hs.data(), sizeof(BState) * count,
+                                hipMemcpyHostToDevice, b->stream);
+  // plan_wide stores the descriptors and waits
+  if (e != hipSuccess || plan_wide(b) != AA_OK ||
+      launch_batch_init(b->d_inst, count, b->stream) != hipSuccess) {
     delete b;
     return AA_EHIP;
   }
@@ -380,7 +484,7 @@ aa_status aa_batch_set_split(aa_batch* b, int64_t min_n, int active_max) {
   if (!b || min_n < 0 || active_max < 0) return AA_EINVAL;
   b->split_min_n = min_n;
   b->split_active_max = active_max;
-  if (min_n == 0 && merge_split(b) != hipSuccess) return AA_EHIP;
+  if (min_n == 0 && merge_split(b) != AA_OK) return AA_EHIP;
   return AA_OK;
 }
 
@@ -400,8 +504,9 @@ aa_status aa_batch_set_tiles(aa_batch* b, int pairs) {
 aa_status aa_batch_autotune(aa_batch* b, int iters, const char* cache_path,
                             aa_batch_schedule* best) {
   if (!b || iters < 1) return AA_EINVAL;
-  // candidates are timed on the persistent kernel alone: every instance back in it
-  if (merge_split(b) != hipSuccess) return AA_EHIP;
+  // the split policy's instances go back first: the schedule is chosen for
+  // the batch as it starts
+  if (merge_split(b) != AA_OK) return AA_EHIP;
   int dev = 0;
   hipDeviceProp_t prop;
   if (hipGetDevice(&dev) != hipSuccess || hipGetDeviceProperties(&prop, dev) != hipSuccess)
@@ -509,15 +614,6 @@ aa_status aa_batch_run(aa_batch* b, int iters) {
     const aa_status s = update_split(b);
     if (s != AA_OK) return s;
   }
-  if (!b->split.empty()) {
-    // the persistent kernel leaves the split instances out; each of them
-    // then runs its iteration on the grid-wide passes (host sequenced)
-    for (int i = 0; i < iters; ++i) {
-      if (enqueue_mode(b, BM_PLAIN, 0.f) != hipSuccess) return AA_EHIP;
-      if (enqueue_split(b) != hipSuccess) return AA_EHIP;
-    }
-    return AA_OK;
-  }
   if (!b->use_graph || b->stream == nullptr) return enqueue(b, iters) == hipSuccess ? AA_OK : AA_EHIP;
   if (b->exec_iters != iters) {
     drop_graph(b);
@@ -560,7 +656,7 @@ aa_status aa_batch_read(aa_batch* b, aa_batch_state* states, int* active) {
 aa_status aa_batch_run_learned(aa_batch* b, aa_mlp* net, int iters) {
   if (!b || !net || iters < 0 || !b->learned) return AA_EINVAL;
   if (mlp_stream(net) != b->stream || mlp_max_batch(net) < b->count) return AA_EINVAL;
-  if (merge_split(b) != hipSuccess) return AA_EHIP;  // the learned step is one-workgroup only
+  if (merge_split(b) != AA_OK) return AA_EHIP;  // the learned step is one-workgroup only
   for (int i = 0; i < iters; ++i) {
     if (enqueue_mode(b, BM_PHASE_A, 0.f) != hipSuccess) return AA_EHIP;
     aa_status s = aa_mlp_forward(net, b->count, b->d_feat, b->d_out);
@@ -573,7 +669,7 @@ aa_status aa_batch_run_learned(aa_batch* b, aa_mlp* net, int iters) {
 aa_status aa_batch_train(aa_batch* b, aa_mlp* net, int iters, float lr) {
   if (!b || !net || iters < 0 || !b->learned || !(lr >= 0.f)) return AA_EINVAL;
   if (mlp_stream(net) != b->stream || mlp_max_batch(net) < b->count) return AA_EINVAL;
-  if (merge_split(b) != hipSuccess) return AA_EHIP;
+  if (merge_split(b) != AA_OK) return AA_EHIP;
   const float dscale = 1.0f / (float)b->count;
   for (int i = 0; i < iters; ++i) {
     if (enqueue_mode(b, BM_PHASE_A, 0.f) != hipSuccess) return AA_EHIP;
@@ -605,7 +701,6 @@ aa_status aa_batch_read_learning(aa_batch* b, float* feat, float* out, float* do
 aa_status aa_batch_destroy(aa_batch* b) {
   if (!b) return AA_OK;
   drop_graph(b);
-  for (aa_ctx* v : b->views) view_destroy(v);
   delete b;
   return AA_OK;
 }

@@ -249,7 +249,7 @@ struct BatchArgs {
   int64_t ov_iter; int ov_k;
   int mode;               // BatchMode
   const int* skip;        // plain mode: instances the persistent kernel leaves out
-                          // (advanced on the grid-wide passes instead); may be null
+                          // (non-zero: advanced by launch_wide); may be null
   int stop_mode;          // fused single-instance step: the stopping test
   double stop_tol;
   float* feat;            // [count x kFeat] network inputs (phase A)
@@ -299,21 +299,26 @@ hipStream_t mlp_stream(const aa_mlp*);
 int mlp_max_batch(const aa_mlp*);
 hipError_t launch_batch_reset(unsigned* counter, hipStream_t);
 
-// A single-instance context over a batched instance's memory (Q, history,
-// small block), with a shared partials buffer and its own stop state: the
-// batch's split path runs a large instance's iterations on the grid-wide
-// passes.  Counters are the instance's (iteration, columns, window); tol and
-// max_iter the batch's (the instance stops at the start of iteration i with
-// ||f_i|| <= tol ||f_0|| or i >= max_iter).
-aa_ctx* view_create(const BInst& I, int variant, unsigned flags, double* partials,
-                    StopState* stop, int64_t iter, int k, int m_i, double tol, int64_t max_iter,
-                    hipStream_t st);
-void view_counters(const aa_ctx* c, int64_t* iter, int* k, int* m_i);
-void view_destroy(aa_ctx* c);
-hipError_t launch_set_int(int* p, int64_t n, int v, hipStream_t);
-// The batched state of a split instance from its stop state and small block.
-hipError_t launch_split_state(BState* st, const StopState* stop, const Small& sm, int k, int m_i,
-                              hipStream_t);
+// Batched iterations with many workgroups per instance (aa_batch_wide.hip).
+// An item is one chunk of an instance: tiles chunk, chunk + chunks, ...; the
+// instance's Small::partials holds (values of its widest reduction) x chunks
+// doubles.  n < 2^30.
+struct WideItem { int j, chunk, chunks; };
+struct WideArgs {
+  const BInst* inst; BState* state;
+  const WideItem* items;  // one per workgroup of a pass
+  const WideItem* list;   // one per instance
+  const int* split;       // [instance] kWideCost or kWideSplit
+  int variant; unsigned flags;
+  double tol; int64_t max_iter;
+  int kgram;              // columns the Gram instance holds
+};
+// Why an instance is left out of the persistent kernel: the cost model, or the
+// split policy of aa_batch_set_split (which also ends it in the iteration that
+// breaks down).
+enum : int { kWideNo = 0, kWideCost = 1, kWideSplit = 2 };
+hipError_t launch_wide(const WideArgs&, int nitems, int ninst, int kbucket, int mmax, bool gram,
+                       int stage_cols, hipStream_t);
 hipError_t launch_batch_init(BInst* inst, int count, hipStream_t);
 
 // launchers (aa_kernels.hip)
