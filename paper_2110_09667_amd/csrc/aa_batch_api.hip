@@ -92,6 +92,7 @@ size_t instance_bytes(int64_t n, int m, bool learned) {
 constexpr size_t kWidePartials = (size_t)(3 * AA_MAX_COLS + 4) * 8192;
 constexpr int64_t kWideTile = 1024;     // rows of a tile of the wide passes
 constexpr int64_t kWideChunks = 512;    // most chunks of an instance
+constexpr int64_t kWideMinN = 512;      // rows from which the cost model takes an instance
 constexpr int64_t kWideMaxN = 1 << 30;  // their row indices are 32 bits in the stencil
 
 int64_t wide_tiles(int64_t n) { return (n + kWideTile - 1) / kWideTile; }
@@ -165,33 +166,46 @@ double iter_bytes(const aa_batch* b, int j) {
 }
 
 // The instances that gain from many workgroups: those with more bytes than a
-// threshold, the one that makes an iteration shortest under these rates
-// (measured on the 2D tables): the persistent kernel takes as long as its
-// largest instance on one workgroup (20 GB/s) or as all of them together (4.8
-// TB/s); the wide passes stream 4.9 TB/s and cost their launches.  The
-// 4096-instance table (100 GB, largest 0.2 GB) stays persistent; of 512 such
-// instances (12.5 GB) nearly all bytes go wide.
+// threshold, the one that makes an iteration shortest in this model of both
+// kernels (fitted to 2D tables of 1 to 4096 instances of side 8 to 512).  The
+// persistent kernel takes 45 us and its bytes at 20 GB/s for an instance, the
+// batch as long as its largest (times 1.2 beside others), as its share of the
+// 512 resident workgroups (times 1.7) or as its bytes at 4.8 TB/s; the wide
+// passes take 4.5 us a launch, 0.05 us an instance and the bytes at 5.1 TB/s.
+// Measured, us an iteration, persistent / wide: 8 instances of side 64 to 256
+// 1700 / 115, 32 of 32 to 128 (DCGS-2) 372 / 104, 2000 of 16 to 48 454 / 359,
+// 4096 of 32 to 512 20757 / 20047, one of side 32 60 / 62.
 void choose_wide(aa_batch* b) {
   std::vector<int> ord(b->count);
   std::iota(ord.begin(), ord.end(), 0);
   std::stable_sort(ord.begin(), ord.end(),
                    [&](int x, int y) { return iter_bytes(b, x) > iter_bytes(b, y); });
+  constexpr double kFixed = 45e-6, kOne = 20e9, kAll = 4.8e12, kResident = 512.0;
+  constexpr double kLaunch = 4.5e-6, kInst = 0.05e-6, kWide = 5.1e12;
   double total = 0.0;
   for (int j : ord) total += iter_bytes(b, j);
-  constexpr double kOne = 20e9, kAll = 4.8e12, kWide = 4.9e12, kLaunch = 4.5e-6;
   const double passes = 12.0 + (b->variant == AA_MGS ? 2.0 * b->mmax : 0.0);
   auto cost = [&](double wide, int next) {  // the first `next` instances are wide
-    double t = next > 0 ? passes * kLaunch + wide / kWide : 0.0;
-    if (next < b->count)
-      t += std::max(iter_bytes(b, ord[next]) / kOne, (total - wide) / kAll);
+    double t = next > 0 ? passes * kLaunch + next * kInst + wide / kWide : 0.0;
+    if (next < b->count) {
+      const double rest = total - wide;
+      t += std::max({1.2 * (kFixed + iter_bytes(b, ord[next]) / kOne),
+                     1.7 * ((b->count - next) * kFixed + rest / kOne) / kResident, rest / kAll});
+    }
     return t;
   };
-  double best = 0.95 * cost(0.0, 0), wide = 0.0;  // by 5 % at least
+  // by 3 % at least; by 30 % where both kernels run one after the other (the
+  // model is no better than that: 2000 instances of side 16 to 48 took 513 us
+  // divided, 454 persistent)
+  const double all = cost(0.0, 0);
+  double best = all, wide = 0.0;
   int take = 0;
-  for (int i = 0; i < b->count && b->n[ord[i]] < kWideMaxN; ++i) {
+  for (int i = 0; i < b->count; ++i) {
+    // below 512 rows (one pair a lane) a pass's workgroup is not even filled
+    if (b->n[ord[i]] < kWideMinN || b->n[ord[i]] >= kWideMaxN) break;
     wide += iter_bytes(b, ord[i]);
     const double t = cost(wide, i + 1);
-    if (t < best) {
+    if (t < best && t < (i + 1 < b->count ? 0.7 : 0.97) * all) {
       best = t;
       take = i + 1;
     }
