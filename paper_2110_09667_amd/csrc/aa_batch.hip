@@ -743,7 +743,13 @@ __global__ __launch_bounds__(kWG, 2) void k_batch(BatchArgs b) {
     __syncthreads();
     const int idx = s_idx;
     __syncthreads();
-    if (idx >= b.count) break;
+    if (idx >= b.count) {
+      // every workgroup takes exactly one number past the end: the last of
+      // them leaves the counter at zero for the next launch (a reset kernel
+      // before each launch cost 4.5 us an iteration)
+      if (threadIdx.x == 0 && idx == b.count + (int)gridDim.x - 1) *b.counter = 0u;
+      break;
+    }
     const int j = b.order[idx];
     if (b.skip && b.skip[j]) continue;  // on the grid-wide passes this iteration
     const BState st = b.state[j];
@@ -759,15 +765,12 @@ __global__ __launch_bounds__(kWG, 2) void k_batch(BatchArgs b) {
   }
 }
 
-__global__ void k_batch_reset(unsigned* counter) {
-  if (threadIdx.x == 0) *counter = 0u;
-}
-
 // R = 0, T = I, coefficients, Givens, scalars and status cleared; one
-// workgroup per instance.
-__global__ void k_batch_init(BInst* inst, int count) {
+// workgroup per instance.  Also the work counter.
+__global__ void k_batch_init(BInst* inst, int count, unsigned* counter) {
   const int j = blockIdx.x;
   if (j >= count) return;
+  if (j == 0 && threadIdx.x == 0) *counter = 0u;
   const Small sm = inst[j].sm;
   const int cap = sm.cap;
   for (int i = threadIdx.x; i < cap * cap; i += blockDim.x) {
@@ -825,15 +828,9 @@ int batch_stage_cols(int mmax, int variant, unsigned flags) {
   return cols < kg ? cols : kg;  // wider windows fall back to the separate passes
 }
 
-hipError_t launch_batch_init(BInst* inst, int count, hipStream_t st) {
+hipError_t launch_batch_init(BInst* inst, int count, unsigned* counter, hipStream_t st) {
   (void)hipGetLastError();  // drop a stale error left by an earlier call
-  hipLaunchKernelGGL(p4::k_batch_init, dim3(count), dim3(kWG), 0, st, inst, count);
-  return hipGetLastError();
-}
-
-hipError_t launch_batch_reset(unsigned* counter, hipStream_t st) {
-  (void)hipGetLastError();  // drop a stale error left by an earlier call
-  hipLaunchKernelGGL(p4::k_batch_reset, dim3(1), dim3(64), 0, st, counter);
+  hipLaunchKernelGGL(p4::k_batch_init, dim3(count), dim3(kWG), 0, st, inst, count, counter);
   return hipGetLastError();
 }
 

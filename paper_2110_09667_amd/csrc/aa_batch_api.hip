@@ -3,9 +3,10 @@
 // The workspace holds the instance descriptors, their device-updated states,
 // the schedule (instance order and work counter) and, per instance, G(x),
 // f_{i-1}, G(x_{i-1}), Delta f, Q, the Delta g history and the small dense
-// block.  aa_batch_run enqueues one persistent launch per iteration (after a
-// one-thread reset of the work counter); with a non-NULL stream the sequence
-// for a given iteration count is captured once as a HIP graph and replayed.
+// block.  aa_batch_run enqueues, per iteration, one launch of the persistent
+// kernel (aa_batch.hip) and the passes of the wide instances
+// (aa_batch_wide.hip); with a non-NULL stream the sequence for a given
+// iteration count is captured once as a HIP graph and replayed.
 #include <stdio.h>
 #include <string.h>
 
@@ -147,8 +148,6 @@ hipError_t enqueue_mode(aa_batch* b, int mode, float dscale) {
     grid = 2 * cus;
   }
   if (grid > b->count) grid = b->count;
-  hipError_t e = launch_batch_reset(b->d_counter, b->stream);
-  if (e != hipSuccess) return e;
   return launch_batch(a, grid, b->kbucket, b->gram,
                       batch_stage_cols(b->mmax, b->variant, b->flags), b->stream, b->pairs);
 }
@@ -463,7 +462,7 @@ aa_status aa_batch_init(aa_batch** out, int count, const aa_batch_instance* inst
                                 hipMemcpyHostToDevice, b->stream);
   // plan_wide stores the descriptors and waits
   if (e != hipSuccess || plan_wide(b) != AA_OK ||
-      launch_batch_init(b->d_inst, count, b->stream) != hipSuccess) {
+      launch_batch_init(b->d_inst, count, b->d_counter, b->stream) != hipSuccess) {
     delete b;
     return AA_EHIP;
   }

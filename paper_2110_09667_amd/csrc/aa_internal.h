@@ -240,7 +240,7 @@ static_assert(sizeof(BState) == sizeof(aa_batch_state), "BState mirrors aa_batch
 
 struct BatchArgs {
   BInst* inst; BState* state; const int* order; int count;
-  unsigned* counter;      // work counter, reset before every launch
+  unsigned* counter;      // work counter, zero between launches
   int variant; unsigned flags;
   double tol; int64_t max_iter;
   // fused single-instance step (ov_iter >= 0): instance 0 only, with the
@@ -297,7 +297,6 @@ int batch_stage_cols(int mmax, int variant, unsigned flags);
 bool batch_needs_gram(int variant, unsigned flags);
 hipStream_t mlp_stream(const aa_mlp*);
 int mlp_max_batch(const aa_mlp*);
-hipError_t launch_batch_reset(unsigned* counter, hipStream_t);
 
 // Batched iterations with many workgroups per instance (aa_batch_wide.hip).
 // An item is one chunk of an instance: tiles chunk, chunk + chunks, ...; the
@@ -319,7 +318,7 @@ struct WideArgs {
 enum : int { kWideNo = 0, kWideCost = 1, kWideSplit = 2 };
 hipError_t launch_wide(const WideArgs&, int nitems, int ninst, int kbucket, int mmax, bool gram,
                        int stage_cols, hipStream_t);
-hipError_t launch_batch_init(BInst* inst, int count, hipStream_t);
+hipError_t launch_batch_init(BInst* inst, int count, unsigned* counter, hipStream_t);
 
 // launchers (aa_kernels.hip)
 // Profiling hook: while set, the next finalize launch records this event on
