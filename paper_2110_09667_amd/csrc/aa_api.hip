@@ -92,7 +92,7 @@ int64_t leading_dim(int64_t n) {
 struct Layout {
   int64_t ldq;
   size_t off_Q, off_ring, off_W, off_fp, off_gp, off_R, off_T, off_c0, off_c1, off_gam,
-      off_giv, off_scal, off_status, off_stop, off_part, off_binst, off_bstate, total;
+      off_giv, off_scal, off_status, off_stop, off_part, off_pend, off_Rg, off_binst, off_bstate, total;
 };
 
 Layout make_layout(int64_t n, int m, unsigned flags) {
@@ -119,6 +119,10 @@ Layout make_layout(int64_t n, int m, unsigned flags) {
   L.off_stop = o; o = align_up(o + sizeof(StopState));
   const size_t part = kPartials;
   L.off_part = o; o = align_up(o + sizeof(double) * part);
+  if (!(flags & AA_QR_ONLY)) {
+    L.off_pend = o; o = align_up(o + sizeof(double) * 2 * kPendMax);
+    L.off_Rg = o; o = align_up(o + sizeof(double) * cap * cap);
+  }
   L.off_binst = o; o = align_up(o + sizeof(BInst));
   L.off_bstate = o; o = align_up(o + sizeof(BState));
   L.total = o;
@@ -216,8 +220,12 @@ Tail tail(int op, int k) {
 // basis and the last pass's tail solves R gamma = c (Alg. 2, last line):
 // the first pass adds Q^T f to its block dot products, the norm pass adds
 // w^T f (c_k = w^T f / R_kk); *rhs_done reports whether that happened.
+//
+// Inside a step (pend non-null) reductions may wait for the next pass, and the
+// division of w by R_kk is left to the pass that follows (*scol: the column).
 aa_status qr_add_impl(aa_ctx* c, const double* v, const double* f = nullptr,
-                      bool* rhs_done = nullptr, bool first_done = false) {
+                      bool* rhs_done = nullptr, bool first_done = false, Pend* pend = nullptr,
+                      int* scol = nullptr) {
   const int k = c->k;
   if (k >= c->cap) return AA_ESTATE;
   if (first_done && (k == 0 || c->variant == AA_MGS)) return AA_EINVAL;
@@ -240,7 +248,7 @@ aa_status qr_add_impl(aa_ctx* c, const double* v, const double* f = nullptr,
   if (k == 0) {
     // Alg. 2 with i = 1 (and every QRAdd into an empty window): normalize.
     d.xx = 1;
-    chk(timed(c, AA_K_DOTS, 1, [&] { return launch_dots(d, c->sm, tn, G, st); }));
+    chk(timed(c, AA_K_DOTS, 1, [&] { return launch_dots(d, c->sm, tn, G, st, pend); }));
     c->syncs_add += 1;
   } else {
     switch (c->variant) {
@@ -248,7 +256,7 @@ aa_status qr_add_impl(aa_ctx* c, const double* v, const double* f = nullptr,
         Tail t0 = tail(TAIL_MGS_R, k);
         t0.row = 0;
         d.nx = 1;
-        chk(timed(c, AA_K_DOTS, 2, [&] { return launch_dots(d, c->sm, t0, G, st); }));
+        chk(timed(c, AA_K_DOTS, 2, [&] { return launch_dots(d, c->sm, t0, G, st, pend); }));
         const double* cur = v;
         for (int j = 1; j < k; ++j) {
           UpdArgs uj = u;
@@ -256,13 +264,13 @@ aa_status qr_add_impl(aa_ctx* c, const double* v, const double* f = nullptr,
           uj.rev = (j & 1);  // alternate with the previous pass (dots: forward)
           Tail tj = tail(TAIL_MGS_R, k);
           tj.row = j;
-          chk(timed(c, AA_K_UPDATE, 4, [&] { return launch_update(uj, c->sm, tj, G, st); }));
+          chk(timed(c, AA_K_UPDATE, 4, [&] { return launch_update(uj, c->sm, tj, G, st, pend); }));
           cur = c->W;
         }
         UpdArgs uk = u;
         uk.v = cur; uk.out = slotk; uk.j0 = k - 1; uk.nc = 1; uk.c1 = Rcol; uk.nrm = 1;
         uk.rev = (k & 1);
-        chk(timed(c, AA_K_UPDATE, 3, [&] { return launch_update(uk, c->sm, tn, G, st); }));
+        chk(timed(c, AA_K_UPDATE, 3, [&] { return launch_update(uk, c->sm, tn, G, st, pend); }));
         c->syncs_add += k + 1;
         break;
       }
@@ -275,13 +283,13 @@ aa_status qr_add_impl(aa_ctx* c, const double* v, const double* f = nullptr,
         }
         if (!first_done)
           chk(timed(c, AA_K_DOTS, k + 1 + zf,
-                    [&] { return launch_dots(d, c->sm, ts, G, st); }));
+                    [&] { return launch_dots(d, c->sm, ts, G, st, pend); }));
         // the three passes alternate direction: dots forward, this pass
         // backward, the update forward
         Cgs2bArgs b{c->Q, c->ldq, c->n, v, k, c->sm.coef0, 1};
         const int Gb = grid_rows(c, c->grid_stream_max);
         chk(timed(c, AA_K_CGS2B, k + 1,
-                  [&] { return launch_cgs2b(b, c->sm, tail(TAIL_CGS2_Z, k), Gb, st); }));
+                  [&] { return launch_cgs2b(b, c->sm, tail(TAIL_CGS2_Z, k), Gb, st, pend); }));
         UpdArgs uc = u;
         uc.v = v; uc.out = slotk; uc.j0 = 0; uc.nc = k; uc.c1 = c->sm.coef0; uc.c2 = c->sm.coef1;
         uc.nrm = 1;
@@ -290,7 +298,7 @@ aa_status qr_add_impl(aa_ctx* c, const double* v, const double* f = nullptr,
           uc.rhsv = f;
           tn.rhs = 1;
         }
-        chk(timed(c, AA_K_UPDATE, k + 2 + zf, [&] { return launch_update(uc, c->sm, tn, G, st); }));
+        chk(timed(c, AA_K_UPDATE, k + 2 + zf, [&] { return launch_update(uc, c->sm, tn, G, st, pend); }));
         c->syncs_add += first_done ? 2 : 3;
         break;
       }
@@ -305,7 +313,7 @@ aa_status qr_add_impl(aa_ctx* c, const double* v, const double* f = nullptr,
         }
         if (!first_done)
           chk(timed(c, AA_K_DOTS, k + 1 + zf,
-                    [&] { return launch_dots(d, c->sm, ti, G, st); }));
+                    [&] { return launch_dots(d, c->sm, ti, G, st, pend); }));
         UpdArgs ub = u;
         ub.v = v; ub.out = slotk; ub.j0 = 0; ub.nc = k; ub.c1 = c->sm.coef0; ub.nrm = 1;
         ub.rev = 1;  // after a forward pass over the same columns
@@ -313,7 +321,7 @@ aa_status qr_add_impl(aa_ctx* c, const double* v, const double* f = nullptr,
           ub.rhsv = f;
           tn.rhs = 1;
         }
-        chk(timed(c, AA_K_UPDATE, k + 2 + zf, [&] { return launch_update(ub, c->sm, tn, G, st); }));
+        chk(timed(c, AA_K_UPDATE, k + 2 + zf, [&] { return launch_update(ub, c->sm, tn, G, st, pend); }));
         c->syncs_add += first_done ? 1 : 2;
         break;
       }
@@ -331,7 +339,7 @@ aa_status qr_add_impl(aa_ctx* c, const double* v, const double* f = nullptr,
           ta.rhs = 1; ta.zoff = k + d.ny;
         }
         if (!first_done)
-          chk(timed(c, AA_K_DOTS, k + 1 + zf, [&] { return launch_dots(d, c->sm, ta, G, st); }));
+          chk(timed(c, AA_K_DOTS, k + 1 + zf, [&] { return launch_dots(d, c->sm, ta, G, st, pend); }));
         UpdArgs ub = u;
         ub.v = v; ub.out = slotk; ub.c1 = Rcol; ub.nrm = 1;
         ub.rev = 1;  // after a forward pass over the same columns
@@ -345,7 +353,7 @@ aa_status qr_add_impl(aa_ctx* c, const double* v, const double* f = nullptr,
           ub.j0 = 0; ub.nc = k;
         }
         chk(timed(c, AA_K_UPDATE, k + (reorth ? 3 : 2) + zf,
-                  [&] { return launch_update(ub, c->sm, tn, G, st); }));
+                  [&] { return launch_update(ub, c->sm, tn, G, st, pend); }));
         c->syncs_add += first_done ? 1 : 2;
         break;
       }
@@ -365,13 +373,13 @@ aa_status qr_add_impl(aa_ctx* c, const double* v, const double* f = nullptr,
           d.z = f; d.nz = k; d.xz = 1;
           tl.rhs = 1; tl.zoff = 2 * k; tl.idx = 3 * k;
         }
-        chk(timed(c, AA_K_DOTS, k + 1 + zf, [&] { return launch_dots(d, c->sm, tl, G, st); }));
+        chk(timed(c, AA_K_DOTS, k + 1 + zf, [&] { return launch_dots(d, c->sm, tl, G, st, pend); }));
         UpdArgs ub = u;
         ub.v = v; ub.out = slotk; ub.c1 = c->sm.coef0; ub.s = c->sm.coef1;
         ub.dcgs2_p = p; ub.reorth = 1; ub.j0 = 0; ub.nc = p;
         ub.pdiv = c->sm.scal + S_RHO; ub.odiv = c->sm.scal + S_RKK;
         ub.rev = 1;  // after a forward pass over the same columns
-        chk(timed(c, AA_K_UPDATE, k + 3, [&] { return launch_update(ub, c->sm, tail(TAIL_NONE, k), G, st); }));
+        chk(timed(c, AA_K_UPDATE, k + 3, [&] { return launch_update(ub, c->sm, tail(TAIL_NONE, k), G, st, pend); }));
         c->syncs_add += 1;
         if (e != hipSuccess) return AA_EHIP;
         c->k = k + 1;
@@ -381,6 +389,13 @@ aa_status qr_add_impl(aa_ctx* c, const double* v, const double* f = nullptr,
         return AA_EINVAL;
     }
   }
+  if (pend && c->sm.pend && k > 0) {
+    *scol = k;
+    if (e != hipSuccess) return AA_EHIP;
+    c->k = k + 1;
+    return AA_OK;
+  }
+  chk(launch_pending(c->sm, pend, st));
   ScaleArgs sa{k == 0 ? v : slotk, slotk, c->n, c->sm.R, k, c->sm.cap, c->sm.stop, c->sm.status};
   chk(timed(c, AA_K_SCALE, 2, [&] { return launch_scale(sa, c->sm, st); }));
   if (e != hipSuccess) return AA_EHIP;
@@ -392,7 +407,10 @@ aa_status qr_add_impl(aa_ctx* c, const double* v, const double* f = nullptr,
 // row of ICWY's T from its first reduction before anything reads it, so the
 // Gram leaves the last rotated column out (at m = 50: 48 columns, 6 MFMA block
 // pairs per 4 rows instead of 10).  The standalone QRDelete refreshes all of T.
-aa_status qr_delete_impl(aa_ctx* c, bool refresh_next) {
+//
+// pend (inside a step): the history pass has computed the rotations (R after
+// them in Rg; not with the T transform) and its reduction may be pending.
+aa_status qr_delete_impl(aa_ctx* c, bool refresh_next, Pend* pend = nullptr) {
   const int k = c->k;
   if (k <= 0) return AA_ESTATE;
   if (k == 1) {
@@ -402,8 +420,14 @@ aa_status qr_delete_impl(aa_ctx* c, bool refresh_next) {
   // ICWY with AA_ICWY_T_TRANSFORM: T follows the rotations in the Givens
   // kernel (no reduction); otherwise the rotation pass refreshes it.
   const bool transform = c->variant == AA_ICWY && (c->flags & AA_ICWY_T_TRANSFORM);
-  hipError_t e = timed(c, AA_K_GIVENS, 0,
-                       [&] { return launch_givens(c->sm, k, c->stream, transform); });
+  hipError_t e = hipSuccess;
+  const bool commit = pend && !transform;
+  if (!commit) {
+    e = launch_pending(c->sm, pend, c->stream);  // the stopping test, before R changes
+    if (e == hipSuccess)
+      e = timed(c, AA_K_GIVENS, 0,
+                [&] { return launch_givens(c->sm, k, c->stream, transform); });
+  }
   if (e != hipSuccess) return AA_EHIP;
   const bool gram = c->variant == AA_ICWY && !transform;
   const int drop = gram && refresh_next ? 1 : 0;
@@ -417,7 +441,9 @@ aa_status qr_delete_impl(aa_ctx* c, bool refresh_next) {
   }
   const int G = grid_rows(c, gmax);
   e = timed(c, AA_K_ROTATE, 2 * k - 1,
-            [&] { return launch_rotate(r, c->sm, tail(TAIL_GRAM, ng), G, c->stream); });
+            [&] {
+              return launch_rotate(r, c->sm, tail(TAIL_GRAM, ng), G, c->stream, pend, commit);
+            });
   if (e != hipSuccess) return AA_EHIP;
   if (gram) c->syncs_del += 1;
   c->k = k - 1;
@@ -459,12 +485,11 @@ Tail first_pass_tail(const aa_ctx* c, int k, bool rhs) {
 // Gram row of the last column, Q^T f).  The finalize rearranges them into
 // that pass's layout and runs its tail; qr_add_impl then continues from the
 // second pass.  One pass over Q and one reduction fewer per iteration.
-aa_status fused_delete_add(aa_ctx* c, const double* v, const double* f, bool* rhs_done) {
+aa_status fused_delete_add(aa_ctx* c, const double* v, const double* f, bool* rhs_done, Pend* pend,
+                           int* scol) {
   const int k = c->k, kk = k - 1;
   const int naug = f ? 2 : 1;
   const hipStream_t st = c->stream;
-  hipError_t e = timed(c, AA_K_GIVENS, 0, [&] { return launch_givens(c->sm, k, st); });
-  if (e != hipSuccess) return AA_EHIP;
   RotArgs r{c->Q, c->ldq, c->n, k, c->sm.givens, 1, v, f, naug};
   const int na = kk + naug;
   const int64_t pairs = (int64_t)na * (na - 1) / 2;
@@ -474,19 +499,27 @@ aa_status fused_delete_add(aa_ctx* c, const double* v, const double* f, bool* rh
   tg.inner = tg.op;
   tg.op = TAIL_GRAM_ADD;
   tg.gram_t = c->variant == AA_ICWY ? 1 : 0;
-  e = timed(c, AA_K_ROTATE, 2 * k - 1 + naug,
-            [&] { return launch_rotate(r, c->sm, tg, grid_rows(c, gmax), st); });
+  const hipError_t e = timed(c, AA_K_ROTATE, 2 * k - 1 + naug, [&] {
+    return launch_rotate(r, c->sm, tg, grid_rows(c, gmax), st, pend, true);
+  });
   if (e != hipSuccess) return AA_EHIP;
   c->syncs_del += 1;
   c->k = kk;
-  return qr_add_impl(c, v, f, rhs_done, true);
+  return qr_add_impl(c, v, f, rhs_done, true, pend, scol);
 }
 
-aa_status rhs_impl(aa_ctx* c, const double* f) {
+// scol >= 0: that column is divided by R_kk and stored in the same pass.
+aa_status rhs_impl(aa_ctx* c, const double* f, Pend* pend = nullptr, int scol = -1) {
   DotsArgs d{c->Q, c->ldq, c->n, f, c->k, nullptr, 0, 0};
+  if (scol >= 0) {  // the last column
+    d.nx = scol;
+    d.w = c->Q + (int64_t)scol * c->ldq;
+    d.wdiv = c->sm.R + scol + (size_t)scol * c->sm.cap;
+  }
   const int G = grid_stream(c);
-  hipError_t e = timed(c, AA_K_DOTS, c->k + 1,
-                       [&] { return launch_dots(d, c->sm, tail(TAIL_RHS, c->k), G, c->stream); });
+  hipError_t e = timed(c, AA_K_DOTS, c->k + 1 + (scol >= 0 ? 1 : 0), [&] {
+    return launch_dots(d, c->sm, tail(TAIL_RHS, c->k), G, c->stream, pend);
+  });
   c->syncs_rhs += 1;
   return hip_ok(e);
 }
@@ -667,6 +700,10 @@ aa_status aa_init(aa_ctx** ctx, int64_t n, int m, int variant, unsigned flags,
   c->sm.status = (int*)(base + L.off_status);
   c->sm.partials = (double*)(base + L.off_part);
   c->sm.npart = (int64_t)kPartials;
+  if (!(flags & AA_QR_ONLY)) {
+    c->sm.pend = (double*)(base + L.off_pend);
+    c->sm.Rg = (double*)(base + L.off_Rg);
+  }
   c->sm.cap = m;
   c->sm.stop = nullptr;  // set only while an AA step is enqueued
   c->stop_dev = (StopState*)(base + L.off_stop);
@@ -715,6 +752,15 @@ struct StepScope {
   ~StepScope() { c->sm.stop = nullptr; }
 };
 
+// Longest vectors whose small reductions wait for their consumer and whose
+// column w is divided by R_kk in the pass that reads it next.  There an
+// iteration is a chain of launches: us an iteration without and with, 32^3 m =
+// 10 61.3 / 54.9, 64^3 m = 3 (MGS) 64.2 / 53.2, 700^2 m = 10 111 / 100.  Beyond,
+// hundreds of partials a value cost every workgroup what the finalize launch
+// did (1000^2 137 / 137, 1.5 M rows 1112 -> 1212 us a solve), and the division
+// costs a read stream more than a pass of its own (256^3: 39.6 -> 40.2 ms).
+constexpr int64_t kWaitMaxN = 1 << 19;
+
 // One iteration of Alg. 1 enqueued kernel by kernel (host sequencing).
 static aa_status step_enqueue(aa_ctx* c, const double* x, const double* g,
                               double* x_next) {
@@ -742,28 +788,54 @@ static aa_status step_enqueue(aa_ctx* c, const double* x, const double* g,
   tr.stop_mode = c->stop_mode;
   tr.stop_tol = c->stop_tol;
   tr.m_i = c->m_i;
-  if (timed(c, AA_K_HISTORY, 8,
-            [&] { return launch_history(h, c->sm, tr, G, st); }) != hipSuccess)
+  // Reductions wait for the pass that uses them (not while profiling, which
+  // times passes and finalizes apart); an extra workgroup of the history pass
+  // computes QRDelete's rotations; the division by R_kk joins the next pass.
+  Pend wait{};
+  Pend* pend = &wait;
+  struct Slots {  // without slots every reduction is finalized at once
+    aa_ctx* c;
+    double* keep;
+    explicit Slots(aa_ctx* cc) : c(cc), keep(cc->sm.pend) {
+      if (c->prof_on || c->n > kWaitMaxN) c->sm.pend = nullptr;
+    }
+    ~Slots() { c->sm.pend = keep; }
+  } slots(c);
+  int scol = -1;
+  const bool del = i > m && c->k > 1;
+  const bool transform = c->variant == AA_ICWY && (c->flags & AA_ICWY_T_TRANSFORM);
+  const bool fuse_del = i > m && fuse_delete_ok(c->variant) && (c->flags & AA_FUSE_DELETE) &&
+                        c->k >= 2 && c->k - 1 + ((c->flags & AA_FUSE_RHS) ? 2 : 1) <= 64;
+  const int givens_k = fuse_del || (del && !transform) ? c->k : 0;
+  if (timed(c, AA_K_HISTORY, 8, [&] {
+        return launch_history(h, c->sm, tr, G, st, pend, givens_k);
+      }) != hipSuccess)
     return AA_EHIP;
   aa_status s = AA_OK;
   bool rhs_done = false;
   const bool fuse_rhs = (c->flags & AA_FUSE_RHS) != 0;
-  if (i > m && fuse_delete_ok(c->variant) && (c->flags & AA_FUSE_DELETE) && c->k >= 2 &&
-      c->k - 1 + (fuse_rhs ? 2 : 1) <= 64) {
+  if (fuse_del) {
     // QRDelete + QRAdd of Delta f_{i-1} with their first reductions merged
-    s = fused_delete_add(c, c->W, fuse_rhs ? c->f_prev : nullptr, &rhs_done);
+    s = fused_delete_add(c, c->W, fuse_rhs ? c->f_prev : nullptr, &rhs_done, pend, &scol);
   } else {
-    if (i > m) s = qr_delete_impl(c, true);  // Alg. 2: QRDelete when the window is full
+    if (i > m) s = qr_delete_impl(c, true, pend);  // Alg. 2: QRDelete when the window is full
     if (s == AA_OK)  // Alg. 2: QRAdd of Delta f_{i-1} (optionally also R gamma = Q^T f_i)
-      s = qr_add_impl(c, c->W, fuse_rhs ? c->f_prev : nullptr, &rhs_done);
+      s = qr_add_impl(c, c->W, fuse_rhs ? c->f_prev : nullptr, &rhs_done, false, pend, &scol);
   }
-  if (s == AA_OK && !rhs_done) s = rhs_impl(c, c->f_prev);  // R gamma = Q^T f_i
+  if (s == AA_OK && !rhs_done) {  // R gamma = Q^T f_i
+    s = rhs_impl(c, c->f_prev, pend, scol);
+    scol = -1;
+  }
   if (s != AA_OK) return s;
   XupdArgs xa{c->ring, c->ldq, m, (int)((i - m_i) % m), m_i, g, x, x_next, c->n, c->sm.gamma};
+  if (scol >= 0) {
+    xa.scol = c->Q + (int64_t)scol * c->ldq;
+    xa.sdiv = c->sm.R + scol + (size_t)scol * c->sm.cap;
+  }
   Tail tx = tail(TAIL_STEP, c->k);
   tx.m_i = m_i;
-  if (timed(c, AA_K_XUPDATE, m_i + 3,
-            [&] { return launch_xupdate(xa, c->sm, tx, G, st); }) != hipSuccess)
+  if (timed(c, AA_K_XUPDATE, m_i + 3 + (scol >= 0 ? 2 : 0),
+            [&] { return launch_xupdate(xa, c->sm, tx, G, st, pend); }) != hipSuccess)
     return AA_EHIP;
   c->m_i = m_i;
   c->iter = i + 1;

@@ -21,6 +21,8 @@ constexpr int kMaxRed = 3 * kMaxCols + 4;  // reductions of one streaming pass
 constexpr int kMaxPairs = (kMaxCols - 1) * (kMaxCols - 2) / 2;  // Gram after delete
 constexpr int kMaxRedAll = kMaxPairs > kMaxRed ? kMaxPairs : kMaxRed;
 constexpr int kFinWG = 1024;         // threads of the finalize kernel
+constexpr int kPendRed = 512;        // most values of a reduction that waits for its
+constexpr int kPendMax = 8192;       // consumer (see Pend), and most partials
 
 // Scalar slots in the small device block.
 // S_RHO, S_RKK: the lagged DCGS-2's divisors of its update pass (the norm of
@@ -68,10 +70,14 @@ struct Small {
   double* coef0;    // cap
   double* coef1;    // cap
   double* gamma;    // cap
+  double* Rg;       // cap x cap: R after the rotations, until the rotation pass
+                    // commits it (contexts only)
   double* givens;   // 2 * cap: cosines then sines
   double* scal;     // S_COUNT scalars
   int* status;      // latched aa_status
   double* partials; // reduction partials, [nred][grid]
+  double* pend;     // two slots of kPendMax partials for reductions that wait
+                    // for their consumer (contexts only; null: none wait)
   int cap;
   int64_t npart;    // doubles the partials buffer holds (0: not stated; the
                     // finalize then sums the partials in one workgroup)
@@ -123,6 +129,9 @@ struct DotsArgs {
   int xx;
   const double* z; int nz;
   int xz;
+  double* w = nullptr;           // one right-hand side: divide this column by
+  const double* wdiv = nullptr;  // *wdiv, store it, and reduce w^T x last (the
+                                 // QRAdd's scale pass); null: none
 };
 
 // out = v - sum_{j0 <= j < j0+nc} Q_j (c1[j] + c2[j]) evaluated as
@@ -195,7 +204,19 @@ struct XupdArgs {
   const double* ring; int64_t ldq; int m; int slot0; int mi;
   const double* g; const double* x; double* x_next; int64_t n;
   const double* gamma;
+  double* scol = nullptr;        // also divide this column by *sdiv (the QRAdd's
+  const double* sdiv = nullptr;  // scale pass); null: none
 };
+
+// A reduction whose partials its consumer sums (every workgroup the same sums,
+// then the dense tail) instead of a finalize launch between them.
+struct Pend {
+  int on;                 // 0: nothing pending
+  Tail t;
+  int nred, G;            // values, workgroups that published
+  const double* partials; // [nred][G]
+};
+
 
 // ---- batched / fused workgroup-level step (aa_batch.hip) ---------------------
 
@@ -326,15 +347,30 @@ hipError_t launch_batch_init(BInst* inst, int count, unsigned* counter, hipStrea
 void set_profile_mid(hipEvent_t e);
 bool profile_mid_used();
 
-hipError_t launch_dots(const DotsArgs&, const Small&, const Tail&, int grid, hipStream_t);
-hipError_t launch_update(const UpdArgs&, const Small&, const Tail&, int grid, hipStream_t);
-hipError_t launch_cgs2b(const Cgs2bArgs&, const Small&, const Tail&, int grid, hipStream_t);
+// pend (AA steps): on entry the reduction this pass completes before it runs, on
+// return its own, if small enough for the next pass to complete; null, or a
+// large one: a finalize launch follows the pass.
+hipError_t launch_dots(const DotsArgs&, const Small&, const Tail&, int grid, hipStream_t,
+                       Pend* pend = nullptr);
+hipError_t launch_update(const UpdArgs&, const Small&, const Tail&, int grid, hipStream_t,
+                         Pend* pend = nullptr);
+hipError_t launch_cgs2b(const Cgs2bArgs&, const Small&, const Tail&, int grid, hipStream_t,
+                        Pend* pend = nullptr);
+// Completes a pending reduction with a finalize launch.
+hipError_t launch_pending(const Small&, Pend* pend, hipStream_t);
 // transform: also rotate ICWY's T like the columns (AA_ICWY_T_TRANSFORM)
 hipError_t launch_givens(const Small&, int k, hipStream_t, bool transform = false);
-hipError_t launch_rotate(const RotArgs&, const Small&, const Tail&, int grid, hipStream_t);
+// commit: R after the rotations is in Small::Rg (launch_history with givens_k)
+// and becomes R in this pass
+hipError_t launch_rotate(const RotArgs&, const Small&, const Tail&, int grid, hipStream_t,
+                         Pend* pend = nullptr, bool commit = false);
 hipError_t launch_scale(const ScaleArgs&, const Small&, hipStream_t);
-hipError_t launch_history(const HistArgs&, const Small&, const Tail&, int grid, hipStream_t);
-hipError_t launch_xupdate(const XupdArgs&, const Small&, const Tail&, int grid, hipStream_t);
+// givens_k > 1: one more workgroup computes QRDelete's rotations of givens_k
+// columns beside the pass, R after them into Small::Rg
+hipError_t launch_history(const HistArgs&, const Small&, const Tail&, int grid, hipStream_t,
+                          Pend* pend = nullptr, int givens_k = 0);
+hipError_t launch_xupdate(const XupdArgs&, const Small&, const Tail&, int grid, hipStream_t,
+                          Pend* pend = nullptr);
 hipError_t launch_init_small(const Small&, hipStream_t);
 // (reads, writes) in {(1,0), (4,0), (8,0), (1,1), (2,1), (3,1), (8,1), (1,2)}
 hipError_t launch_probe(int reads, int writes, const double* src, int64_t ld, double* dst,

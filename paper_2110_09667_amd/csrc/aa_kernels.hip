@@ -22,9 +22,10 @@ namespace aa {
 // workgroup's entries of the partials ([value][workgroup]); k_finalize, the
 // next kernel on the stream, reduces them (the kernel boundary orders the
 // writes before the reads, so no fence or atomic is needed here).
-__device__ void publish(const Small& sm, int nred, const double* acc, int acc_stride) {
+__device__ void publish(const Small& sm, int nred, const double* acc, int acc_stride,
+                        int G = gridDim.x) {
   __syncthreads();
-  const int G = gridDim.x, b = blockIdx.x;
+  const int b = blockIdx.x;
   for (int c = threadIdx.x; c < nred; c += kWG) {
     double s = acc[c];
 #pragma unroll
@@ -122,8 +123,63 @@ __global__ __launch_bounds__(kFinWG) void k_finalize(Small sm, Tail t, int nred,
   run_tail(sm, ti, red2);
 }
 
-__global__ __launch_bounds__(kWG) void k_dots(DotsArgs a, Small sm) {
-  if (aa_stopped(sm)) return;
+// Completes a pending reduction inside its consumer: every workgroup sums the
+// partials (four values a wave at a time) and runs the tail, the first one as
+// its writer.  Returns true when the iteration has ended.  At n = 32768 a
+// finalize launch is 3 us on the GPU and as much on the host; this is 1 to 1.5 us
+// of each workgroup's time, while the partials are few.
+__device__ inline bool complete(const Small& sm, const Pend& p) {
+  __shared__ double red[kPendRed];
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, nw = blockDim.x >> 6;
+  if (p.t.op == TAIL_GRAM) {
+    // T is read by the next kernel only: each workgroup sums its share of the
+    // pairs
+    for (int c = blockIdx.x * nw + w; c < p.nred; c += gridDim.x * nw) {
+      const double s = sum_partials(p.partials + (size_t)c * p.G, p.G, lane);
+      int a = (int)((1.0 + sqrt(1.0 + 8.0 * c)) / 2.0);
+      while (a * (a - 1) / 2 > c) --a;
+      while ((a + 1) * a / 2 <= c) ++a;
+      if (lane == 0) sm.T[a + (size_t)(c - a * (a - 1) / 2) * sm.cap] = s;
+    }
+    return false;
+  }
+  for (int c0 = 4 * w; c0 < p.nred; c0 += 4 * nw) {
+    double s[4] = {0.0, 0.0, 0.0, 0.0};
+    for (int g = lane; g < p.G; g += 4 * 64) {  // sixteen loads in flight
+      double v[4][4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const bool in = c0 + u < p.nred && g + q * 64 < p.G;
+          v[u][q] = p.partials[in ? (size_t)(c0 + u) * p.G + g + q * 64 : 0];
+          if (!in) v[u][q] = 0.0;
+        }
+#pragma unroll
+      for (int u = 0; u < 4; ++u) s[u] += (v[u][0] + v[u][1]) + (v[u][2] + v[u][3]);
+    }
+    const double r = multi_reduce<4>(s);
+    if (lane < 4 && c0 + lane < p.nred) red[c0 + lane] = r;
+  }
+  __syncthreads();
+  run_tail(sm, p.t, red, blockIdx.x == 0);
+  if (p.t.op == TAIL_RES) return sm.stop && stop_hit(sm, p.t, red[0]);
+  __syncthreads();
+  return p.t.op == TAIL_NORM && aa_stopped(sm);  // a breakdown
+}
+
+// PRO: the instance with a pending reduction to complete (kernels run without
+// one carry none of its code).
+template <bool PRO>
+__device__ __forceinline__ bool ended(const Small& sm, const Pend& p) {
+  if (aa_stopped(sm)) return true;
+  if constexpr (PRO) return complete(sm, p);
+  return false;
+}
+
+template <bool PRO>
+__global__ __launch_bounds__(kWG) void k_dots(DotsArgs a, Small sm, Pend p) {
+  if (ended<PRO>(sm, p)) return;
   __shared__ double s_acc[kWaves * kMaxRed];
   lds_zero(s_acc, kWaves * kMaxRed);
   __syncthreads();
@@ -133,15 +189,9 @@ __global__ __launch_bounds__(kWG) void k_dots(DotsArgs a, Small sm) {
 
 // Block dot products with per-lane register accumulators (dots_reg_body):
 // KQ-column buckets, one to three right-hand sides.
-#ifndef AA_DOTS_REG
-#define AA_DOTS_REG 1
-#endif
-#ifndef AA_DOTS_REG3
-#define AA_DOTS_REG3 AA_DOTS_REG
-#endif
-template <int KQ, int NR>
-__global__ __launch_bounds__(kWG) void k_dots_reg(DotsArgs a, Small sm) {
-  if (aa_stopped(sm)) return;
+template <int KQ, int NR, bool PRO>
+__global__ __launch_bounds__(kWG) void k_dots_reg(DotsArgs a, Small sm, Pend p) {
+  if (ended<PRO>(sm, p)) return;
   constexpr int STR = NR * KQ + 2;  // nx + ny + nz + xx + xz <= NR KQ + 2
   __shared__ double s_acc[kWaves * STR];
   lds_zero(s_acc, kWaves * STR);
@@ -150,8 +200,9 @@ __global__ __launch_bounds__(kWG) void k_dots_reg(DotsArgs a, Small sm) {
   publish(sm, dots_nred(a), s_acc, STR);
 }
 
-__global__ __launch_bounds__(kWG) void k_update(UpdArgs a, Small sm) {
-  if (aa_stopped(sm)) return;
+template <bool PRO>
+__global__ __launch_bounds__(kWG) void k_update(UpdArgs a, Small sm, Pend p) {
+  if (ended<PRO>(sm, p)) return;
   __shared__ double s_c1[kMaxCols], s_c2[kMaxCols], s_s[kMaxCols];
   __shared__ double s_acc[kWaves * 4];
   update_coefs(a, s_c1, s_c2, s_s);
@@ -166,9 +217,9 @@ __global__ __launch_bounds__(kWG) void k_update(UpdArgs a, Small sm) {
 #ifndef AA_CGS2B_PAIR_MAX
 #define AA_CGS2B_PAIR_MAX 32
 #endif
-template <int KMAX>
-__global__ __launch_bounds__(kWG) void k_cgs2b(Cgs2bArgs a, Small sm) {
-  if (aa_stopped(sm)) return;
+template <int KMAX, bool PRO>
+__global__ __launch_bounds__(kWG) void k_cgs2b(Cgs2bArgs a, Small sm, Pend p) {
+  if (ended<PRO>(sm, p)) return;
   __shared__ double s_s[KMAX];
   __shared__ double s_acc[kWaves * KMAX];
   for (int j = threadIdx.x; j < KMAX; j += kWG) s_s[j] = (j < a.k) ? a.s[j] : 0.0;
@@ -192,9 +243,18 @@ __global__ __launch_bounds__(64) void k_givens(Small sm, int k, int transform) {
   }
 }
 
-template <int CH>
-__global__ __launch_bounds__(kWG) void k_rotate(RotArgs a, Small sm) {
-  if (aa_stopped(sm)) return;
+// The first workgroup of a rotation pass stores R as the history pass's extra
+// workgroup left it (no kernel in between reads R).
+__device__ __forceinline__ void commit_r(const Small& sm, int k, int commit) {
+  if (commit && blockIdx.x == 0)
+    for (int i = threadIdx.x; i < k * k; i += blockDim.x)
+      sm.R[i % k + (size_t)(i / k) * sm.cap] = sm.Rg[i % k + (size_t)(i / k) * sm.cap];
+}
+
+template <int CH, bool PRO>
+__global__ __launch_bounds__(kWG) void k_rotate(RotArgs a, Small sm, Pend p, int commit) {
+  if (ended<PRO>(sm, p)) return;
+  commit_r(sm, a.k, commit);
   __shared__ double s_c[kMaxCols], s_s[kMaxCols];
   givens_coefs(a, sm.cap, s_c, s_s, kMaxCols);
   __syncthreads();
@@ -229,9 +289,10 @@ constexpr int kRotChWide = AA_ROT_CH_WIDE;
 #endif
 constexpr int kRotChMid = AA_ROT_CH_MID;
 
-template <int KMAX, int WAVES>
-__global__ __launch_bounds__(64 * WAVES) void k_rotate_gram(RotArgs a, Small sm) {
-  if (aa_stopped(sm)) return;
+template <int KMAX, int WAVES, bool PRO>
+__global__ __launch_bounds__(64 * WAVES) void k_rotate_gram(RotArgs a, Small sm, Pend p, int commit) {
+  if (ended<PRO>(sm, p)) return;
+  commit_r(sm, a.k, commit);
   // staging rows, then the per-wave pair sums: gram_lds_doubles(gram_cols(a), WAVES)
   extern __shared__ double s_buf[];
   __shared__ double s_c[KMAX], s_s[KMAX];
@@ -277,8 +338,11 @@ __host__ __device__ constexpr int gram_split_lds_doubles(int na) {
              : kWaves * (na * (na - 1) / 2);
 }
 
-__global__ __launch_bounds__(kWG) void k_rotate_gram_split(RotArgs a, Small sm) {
-  if (aa_stopped(sm)) return;
+template <int, bool PRO>
+__global__ __launch_bounds__(kWG) void k_rotate_gram_split_t(RotArgs a, Small sm, Pend p,
+                                                             int commit) {
+  if (ended<PRO>(sm, p)) return;
+  commit_r(sm, a.k, commit);
   extern __shared__ double s_buf[];
   __shared__ double s_c[64], s_s[64];
   const int na = gram_cols(a), np = na * (na - 1) / 2;
@@ -296,9 +360,11 @@ __global__ __launch_bounds__(kWG) void k_rotate_gram_split(RotArgs a, Small sm) 
 // by one butterfly reduction, then the usual per-workgroup partials.
 constexpr int kGramSmall = 8;
 
-template <int NAMAX>
-__global__ __launch_bounds__(kWG) void k_rotate_gram_small(RotArgs a, Small sm) {
-  if (aa_stopped(sm)) return;
+template <int NAMAX, bool PRO>
+__global__ __launch_bounds__(kWG) void k_rotate_gram_small(RotArgs a, Small sm, Pend p,
+                                                           int commit) {
+  if (ended<PRO>(sm, p)) return;
+  commit_r(sm, a.k, commit);
   constexpr int NR = NAMAX == 4 ? 8 : 32;  // NAMAX (NAMAX - 1) / 2 pairs, padded
   __shared__ double s_c[NAMAX], s_s[NAMAX];
   __shared__ double s_acc[kWaves * NR];
@@ -318,17 +384,27 @@ __global__ __launch_bounds__(kWG) void k_scale(ScaleArgs a) {
   scale_body(a.in, a.out, a.n, a.R[a.kk + (size_t)a.kk * a.cap], blockIdx.x, gridDim.x);
 }
 
-__global__ __launch_bounds__(kWG) void k_history(HistArgs a, Small sm) {
+// givens_k > 1: the last workgroup computes QRDelete's rotations meanwhile (from
+// R, which the pass does not touch; the stopping test, which would leave R as
+// it is, has not been taken yet: R after them goes to Rg).
+__global__ __launch_bounds__(kWG) void k_history(HistArgs a, Small sm, int givens_k) {
+  extern __shared__ double s_H[];
   if (aa_stopped(sm)) return;
+  const int G = gridDim.x - (givens_k > 1 ? 1 : 0);
+  if ((int)blockIdx.x == G) {
+    givens_body(sm, givens_k, s_H, sm.Rg);
+    return;
+  }
   __shared__ double s_acc[kWaves * 2];
   lds_zero(s_acc, kWaves * 2);
   __syncthreads();
-  history_body(a, blockIdx.x, gridDim.x, s_acc + (threadIdx.x >> 6) * 2);
-  publish(sm, a.first ? 2 : 1, s_acc, 2);
+  history_body(a, blockIdx.x, G, s_acc + (threadIdx.x >> 6) * 2);
+  publish(sm, a.first ? 2 : 1, s_acc, 2, G);
 }
 
-__global__ __launch_bounds__(kWG) void k_xupdate(XupdArgs a, Small sm) {
-  if (aa_stopped(sm)) {
+template <bool PRO>
+__global__ __launch_bounds__(kWG) void k_xupdate(XupdArgs a, Small sm, Pend p) {
+  if (ended<PRO>(sm, p)) {
     // the iteration has ended: x_next = x, except in the step that broke down
     // (breakdown latched, not yet recorded as the end), which returns G(x_i)
     const double* src = sm.stop->done == 0 ? a.g : a.x;
@@ -524,98 +600,130 @@ static hipError_t launch_finalize(const Small& sm, const Tail& t, int nred, int 
   return hipGetLastError();
 }
 
+// Whether a reduction may wait for its consumer: tails that several workgroups
+// may run at once (run_tail's writer), few values and partials.  The folded
+// solve is not one (it overwrites its own input), nor are the tails that end a
+// step or rearrange a Gram.
+static bool deferrable(const Tail& t, int nred, int grid) {
+  switch (t.op) {
+    case TAIL_MGS_R: case TAIL_CGS2_S: case TAIL_CGS2_Z: case TAIL_ICWY: case TAIL_DCGS2:
+    case TAIL_RHS: case TAIL_RES: case TAIL_GRAM:
+      break;
+    case TAIL_NORM:
+      if (t.rhs) return false;
+      break;
+    default:
+      return false;
+  }
+  return nred <= kPendRed && (int64_t)nred * grid <= kPendMax;
+}
+
+// Launches a pass that completes `pend` (if any) and reduces nred values from
+// `grid` workgroups with tail t: leaves them pending, or finalizes them.
+// launch(pro, small, pending): pro a true_type / false_type.
+template <class Launch>
+static hipError_t pass(const Small& sm, const Tail& t, int nred, int grid, hipStream_t st,
+                       Pend* pend, Launch&& launch) {
+  const Pend in = pend ? *pend : Pend{};
+  Small s = sm;
+  const bool wait = pend && nred > 0 && sm.pend && deferrable(t, nred, grid);
+  // two slots in turn: the workgroups still reading the one, this pass's own
+  if (wait) s.partials = in.partials == sm.pend ? sm.pend + kPendMax : sm.pend;
+  if (in.on) launch(std::true_type{}, s, in);
+  else launch(std::false_type{}, s, in);
+  if (pend) *pend = Pend{};
+  if (nred == 0) return hipGetLastError();  // nothing reduced: no Sync
+  if (wait) {
+    *pend = Pend{1, t, nred, grid, s.partials};
+    return hipGetLastError();
+  }
+  return launch_finalize(sm, t, nred, grid, st);
+}
+
+hipError_t launch_pending(const Small& sm, Pend* pend, hipStream_t st) {
+  if (!pend || !pend->on) return hipSuccess;
+  const Pend p = *pend;
+  *pend = Pend{};
+  Small s = sm;
+  s.partials = const_cast<double*>(p.partials);
+  s.npart = 0;
+  return launch_finalize(s, p.t, p.nred, p.G, st);
+}
+
+#define AA_KERNEL(...) reinterpret_cast<const void*>(&__VA_ARGS__)
+
 hipError_t launch_dots(const DotsArgs& a, const Small& sm, const Tail& t, int grid,
-                       hipStream_t st) {
+                       hipStream_t st, Pend* pend) {
   (void)hipGetLastError();  // drop a stale error left by an earlier call
   // every vector the counts name must exist
   if (!a.x || (a.ny > 0 && !a.y) || (a.nz > 0 && !a.z) || (a.xz && a.nz < 1))
     return hipErrorInvalidValue;
-  // one round of resident workgroups at most; the finalize sums `grid` partials
-  auto clamp_launch = [&](const void* kern, auto launch) {
-    const int g = clamp_resident(grid, kern, kWG, 0);
-    launch(g);
-    return g;
-  };
   int nq = a.nx > a.ny ? a.nx : a.ny;
   if (a.nz > nq) nq = a.nz;
   const int nr = a.nz > 0 ? 3 : (a.ny > 0 ? 2 : 1);  // right-hand sides
-  if (AA_DOTS_REG && nr == 1 && nq <= 8)
-    grid = clamp_launch(reinterpret_cast<const void*>(&k_dots_reg<8, 1>), [&](int g) {
-      hipLaunchKernelGGL((k_dots_reg<8, 1>), dim3(g), dim3(kWG), 0, st, a, sm);
-    });
-  else if (AA_DOTS_REG && nr == 1 && nq <= 16)
-    grid = clamp_launch(reinterpret_cast<const void*>(&k_dots_reg<16, 1>), [&](int g) {
-      hipLaunchKernelGGL((k_dots_reg<16, 1>), dim3(g), dim3(kWG), 0, st, a, sm);
-    });
-  else if (AA_DOTS_REG && nr == 1 && nq <= 32)
-    grid = clamp_launch(reinterpret_cast<const void*>(&k_dots_reg<32, 1>), [&](int g) {
-      hipLaunchKernelGGL((k_dots_reg<32, 1>), dim3(g), dim3(kWG), 0, st, a, sm);
-    });
-  else if (AA_DOTS_REG && nr == 1 && nq <= 64)
-    grid = clamp_launch(reinterpret_cast<const void*>(&k_dots_reg<64, 1>), [&](int g) {
-      hipLaunchKernelGGL((k_dots_reg<64, 1>), dim3(g), dim3(kWG), 0, st, a, sm);
-    });
-  else if (AA_DOTS_REG && nr == 2 && nq <= 8)
-    grid = clamp_launch(reinterpret_cast<const void*>(&k_dots_reg<8, 2>), [&](int g) {
-      hipLaunchKernelGGL((k_dots_reg<8, 2>), dim3(g), dim3(kWG), 0, st, a, sm);
-    });
-  else if (AA_DOTS_REG && nr == 2 && nq <= 16)
-    grid = clamp_launch(reinterpret_cast<const void*>(&k_dots_reg<16, 2>), [&](int g) {
-      hipLaunchKernelGGL((k_dots_reg<16, 2>), dim3(g), dim3(kWG), 0, st, a, sm);
-    });
-  else if (AA_DOTS_REG && nr == 2 && nq <= 32)
-    grid = clamp_launch(reinterpret_cast<const void*>(&k_dots_reg<32, 2>), [&](int g) {
-      hipLaunchKernelGGL((k_dots_reg<32, 2>), dim3(g), dim3(kWG), 0, st, a, sm);
-    });
-  else if (AA_DOTS_REG3 && nr == 3 && nq <= 8)
-    grid = clamp_launch(reinterpret_cast<const void*>(&k_dots_reg<8, 3>), [&](int g) {
-      hipLaunchKernelGGL((k_dots_reg<8, 3>), dim3(g), dim3(kWG), 0, st, a, sm);
-    });
-  else if (AA_DOTS_REG3 && nr == 3 && nq <= 16)
-    grid = clamp_launch(reinterpret_cast<const void*>(&k_dots_reg<16, 3>), [&](int g) {
-      hipLaunchKernelGGL((k_dots_reg<16, 3>), dim3(g), dim3(kWG), 0, st, a, sm);
-    });
-  else if (AA_DOTS_REG3 && nr == 3 && nq <= 32)
-    grid = clamp_launch(reinterpret_cast<const void*>(&k_dots_reg<32, 3>), [&](int g) {
-      hipLaunchKernelGGL((k_dots_reg<32, 3>), dim3(g), dim3(kWG), 0, st, a, sm);
-    });
-  else
-    grid = clamp_launch(reinterpret_cast<const void*>(&k_dots), [&](int g) {
-      hipLaunchKernelGGL(k_dots, dim3(g), dim3(kWG), 0, st, a, sm);
-    });
-  return launch_finalize(sm, t, a.nx + a.ny + a.nz + (a.xx ? 1 : 0) + (a.xz ? 1 : 0), grid, st);
+  if (a.w && (nr != 1 || nq > 64 || !a.wdiv)) return hipErrorInvalidValue;
+  const int nred = a.nx + a.ny + a.nz + (a.xx ? 1 : 0) + (a.xz ? 1 : 0) + (a.w ? 1 : 0);
+  const bool pro = pend && pend->on;
+  // one round of resident workgroups at most; the finalize sums `grid` partials
+  auto go = [&](const void* kp, const void* kn, auto launch) {
+    const int g = clamp_resident(grid, pro ? kp : kn, kWG, 0);
+    return pass(sm, t, nred, g, st, pend,
+                [&](auto P, const Small& s, const Pend& p) { launch(P, s, p, g); });
+  };
+#define AA_DOTS(KQ, NR)                                                                       \
+  return go(AA_KERNEL(k_dots_reg<KQ, NR, true>), AA_KERNEL(k_dots_reg<KQ, NR, false>),        \
+            [&](auto P, const Small& s, const Pend& p, int g) {                               \
+              hipLaunchKernelGGL((k_dots_reg<KQ, NR, decltype(P)::value>), dim3(g), dim3(kWG), \
+                                 0, st, a, s, p);                                             \
+            });
+  if (nr == 1) {
+    if (nq <= 8) AA_DOTS(8, 1)
+    if (nq <= 16) AA_DOTS(16, 1)
+    if (nq <= 32) AA_DOTS(32, 1)
+    if (nq <= 64) AA_DOTS(64, 1)
+  } else if (nr == 2) {
+    if (nq <= 8) AA_DOTS(8, 2)
+    if (nq <= 16) AA_DOTS(16, 2)
+    if (nq <= 32) AA_DOTS(32, 2)
+  } else {
+    if (nq <= 8) AA_DOTS(8, 3)
+    if (nq <= 16) AA_DOTS(16, 3)
+    if (nq <= 32) AA_DOTS(32, 3)
+  }
+#undef AA_DOTS
+  return go(AA_KERNEL(k_dots<true>), AA_KERNEL(k_dots<false>),
+            [&](auto P, const Small& s, const Pend& p, int g) {
+              hipLaunchKernelGGL((k_dots<decltype(P)::value>), dim3(g), dim3(kWG), 0, st, a, s, p);
+            });
 }
 
 hipError_t launch_update(const UpdArgs& a, const Small& sm, const Tail& t, int grid,
-                         hipStream_t st) {
+                         hipStream_t st, Pend* pend) {
   (void)hipGetLastError();  // drop a stale error left by an earlier call
-  grid = clamp_resident(grid, reinterpret_cast<const void*>(&k_update), kWG, 0);
-  hipLaunchKernelGGL(k_update, dim3(grid), dim3(kWG), 0, st, a, sm);
-  if (update_nred(a) == 0) return hipGetLastError();  // nothing reduced: no Sync
-  return launch_finalize(sm, t, update_nred(a), grid, st);
+  grid = clamp_resident(grid, pend && pend->on ? AA_KERNEL(k_update<true>) : AA_KERNEL(k_update<false>),
+                        kWG, 0);
+  return pass(sm, t, update_nred(a), grid, st, pend, [&](auto P, const Small& s, const Pend& p) {
+    hipLaunchKernelGGL((k_update<decltype(P)::value>), dim3(grid), dim3(kWG), 0, st, a, s, p);
+  });
 }
 
 hipError_t launch_cgs2b(const Cgs2bArgs& a, const Small& sm, const Tail& t, int grid,
-                        hipStream_t st) {
+                        hipStream_t st, Pend* pend) {
   (void)hipGetLastError();  // drop a stale error left by an earlier call
-  auto go = [&](const void* kern, auto launch) {
-    grid = clamp_resident(grid, kern, kWG, 0);
-    launch();
-  };
-  if (a.k <= 8) {
-    go(reinterpret_cast<const void*>(&k_cgs2b<8>),
-       [&] { hipLaunchKernelGGL(k_cgs2b<8>, dim3(grid), dim3(kWG), 0, st, a, sm); });
-  } else if (a.k <= 16) {
-    go(reinterpret_cast<const void*>(&k_cgs2b<16>),
-       [&] { hipLaunchKernelGGL(k_cgs2b<16>, dim3(grid), dim3(kWG), 0, st, a, sm); });
-  } else if (a.k <= 32) {
-    go(reinterpret_cast<const void*>(&k_cgs2b<32>),
-       [&] { hipLaunchKernelGGL(k_cgs2b<32>, dim3(grid), dim3(kWG), 0, st, a, sm); });
-  } else {
-    go(reinterpret_cast<const void*>(&k_cgs2b<64>),
-       [&] { hipLaunchKernelGGL(k_cgs2b<64>, dim3(grid), dim3(kWG), 0, st, a, sm); });
+  const bool pro = pend && pend->on;
+#define AA_CGS2B(K)                                                                            \
+  {                                                                                            \
+    grid = clamp_resident(grid, pro ? AA_KERNEL(k_cgs2b<K, true>) : AA_KERNEL(k_cgs2b<K, false>), \
+                          kWG, 0);                                                             \
+    return pass(sm, t, a.k, grid, st, pend, [&](auto P, const Small& s, const Pend& p) {       \
+      hipLaunchKernelGGL((k_cgs2b<K, decltype(P)::value>), dim3(grid), dim3(kWG), 0, st, a, s, p); \
+    });                                                                                        \
   }
-  return launch_finalize(sm, t, a.k, grid, st);
+  if (a.k <= 8) AA_CGS2B(8)
+  if (a.k <= 16) AA_CGS2B(16)
+  if (a.k <= 32) AA_CGS2B(32)
+  AA_CGS2B(64)
+#undef AA_CGS2B
 }
 
 hipError_t launch_givens(const Small& sm, int k, hipStream_t st, bool transform) {
@@ -625,59 +733,46 @@ hipError_t launch_givens(const Small& sm, int k, hipStream_t st, bool transform)
 }
 
 hipError_t launch_rotate(const RotArgs& a, const Small& sm, const Tail& t, int grid,
-                         hipStream_t st) {
+                         hipStream_t st, Pend* pend, bool commit) {
   (void)hipGetLastError();  // drop a stale error left by an earlier call
+  const bool pro = pend && pend->on;
+  const int cm = commit ? 1 : 0;
+  // one round of resident workgroups at most (the finalize sums `grid`
+  // partials per value)
+#define AA_ROT(NRED, THREADS, LDS, ...)                                                          \
+  {                                                                                              \
+    const size_t lds = LDS;                                                                      \
+    if (NRED > 0)                                                                                \
+      grid = clamp_resident(grid, pro ? AA_KERNEL(__VA_ARGS__, true>) : AA_KERNEL(__VA_ARGS__, false>), \
+                            THREADS, lds);                                                       \
+    return pass(sm, t, NRED, grid, st, pend, [&](auto P, const Small& s, const Pend& p) {        \
+      hipLaunchKernelGGL((__VA_ARGS__, decltype(P)::value>), dim3(grid), dim3(THREADS), lds, st, \
+                         a, s, p, cm);                                                           \
+    });                                                                                          \
+  }
   if (a.gram) {
     // The kernel instance must hold every rotated column (its Givens
     // coefficient arrays) and every staged one: w = max(k - 1, Gram columns).
     // The Gram's own column count na sizes the dynamic LDS (fewer columns,
     // more resident workgroups) and picks the 64-column variant.
-    const int na = gram_cols(a), w = a.k - 1 + a.naug;
-    // one round of resident workgroups at most (the finalize sums `grid`
-    // partials per value)
-    auto go = [&](const void* kern, int threads, size_t lds, auto launch) {
-      grid = clamp_resident(grid, kern, threads, lds);
-      launch(grid, threads, lds);
-    };
-    if (w <= 4) {
-      go(reinterpret_cast<const void*>(&k_rotate_gram_small<4>), kWG, 0, [&](int g, int th, size_t l) {
-        hipLaunchKernelGGL(k_rotate_gram_small<4>, dim3(g), dim3(th), l, st, a, sm);
-      });
-    } else if (w <= kGramSmall) {
-      go(reinterpret_cast<const void*>(&k_rotate_gram_small<kGramSmall>), kWG, 0,
-         [&](int g, int th, size_t l) {
-           hipLaunchKernelGGL(k_rotate_gram_small<kGramSmall>, dim3(g), dim3(th), l, st, a, sm);
-         });
-    } else if (w <= 16) {
-      go(reinterpret_cast<const void*>(&k_rotate_gram<16, kWaves>), kWG,
-         sizeof(double) * (size_t)gram_lds_doubles(na, kWaves), [&](int g, int th, size_t l) {
-           hipLaunchKernelGGL((k_rotate_gram<16, kWaves>), dim3(g), dim3(th), l, st, a, sm);
-         });
-    } else if (w <= 32) {
-      go(reinterpret_cast<const void*>(&k_rotate_gram<32, kWaves>), kWG,
-         sizeof(double) * (size_t)gram_lds_doubles(na, kWaves), [&](int g, int th, size_t l) {
-           hipLaunchKernelGGL((k_rotate_gram<32, kWaves>), dim3(g), dim3(th), l, st, a, sm);
-         });
-    } else if (w <= 64 && na < kGramSplitMin) {
-      go(reinterpret_cast<const void*>(&k_rotate_gram<64, 2>), 128,
-         sizeof(double) * (size_t)gram_lds_doubles(na, 2), [&](int g, int th, size_t l) {
-           hipLaunchKernelGGL((k_rotate_gram<64, 2>), dim3(g), dim3(th), l, st, a, sm);
-         });
-    } else if (w <= 64) {  // na >= kGramSplitMin > 32, as the half staging needs
-      go(reinterpret_cast<const void*>(&k_rotate_gram_split), kWG,
-         sizeof(double) * (size_t)gram_split_lds_doubles(na), [&](int g, int th, size_t l) {
-           hipLaunchKernelGGL(k_rotate_gram_split, dim3(g), dim3(th), l, st, a, sm);
-         });
-    } else {
-      return hipErrorInvalidValue;  // at most 64 rotated or staged columns
-    }
-    return launch_finalize(sm, t, na * (na - 1) / 2, grid, st);
+    const int na = gram_cols(a), w = a.k - 1 + a.naug, np = na * (na - 1) / 2;
+    if (w <= 4) AA_ROT(np, kWG, 0, k_rotate_gram_small<4)
+    if (w <= kGramSmall) AA_ROT(np, kWG, 0, k_rotate_gram_small<kGramSmall)
+    if (w <= 16)
+      AA_ROT(np, kWG, sizeof(double) * (size_t)gram_lds_doubles(na, kWaves),
+             k_rotate_gram<16, kWaves)
+    if (w <= 32)
+      AA_ROT(np, kWG, sizeof(double) * (size_t)gram_lds_doubles(na, kWaves),
+             k_rotate_gram<32, kWaves)
+    if (w <= 64 && na < kGramSplitMin)
+      AA_ROT(np, 128, sizeof(double) * (size_t)gram_lds_doubles(na, 2), k_rotate_gram<64, 2)
+    if (w <= 64)  // na >= kGramSplitMin > 32, as the half staging needs
+      AA_ROT(np, kWG, sizeof(double) * (size_t)gram_split_lds_doubles(na), k_rotate_gram_split_t<0)
+    return hipErrorInvalidValue;  // at most 64 rotated or staged columns
   }
-  if (a.n >= AA_ROT_LONG_N)
-    hipLaunchKernelGGL(k_rotate<AA_ROT_CH_LONG>, dim3(grid), dim3(kWG), 0, st, a, sm);
-  else
-    hipLaunchKernelGGL(k_rotate<kRotChPair>, dim3(grid), dim3(kWG), 0, st, a, sm);
-  return hipGetLastError();
+  if (a.n >= AA_ROT_LONG_N) AA_ROT(0, kWG, 0, k_rotate<AA_ROT_CH_LONG)
+  AA_ROT(0, kWG, 0, k_rotate<kRotChPair)
+#undef AA_ROT
 }
 
 hipError_t launch_scale(const ScaleArgs& a, const Small& sm, hipStream_t st) {
@@ -691,19 +786,25 @@ hipError_t launch_scale(const ScaleArgs& a, const Small& sm, hipStream_t st) {
 }
 
 hipError_t launch_history(const HistArgs& a, const Small& sm, const Tail& t, int grid,
-                          hipStream_t st) {
+                          hipStream_t st, Pend* pend, int givens_k) {
   (void)hipGetLastError();  // drop a stale error left by an earlier call
-  grid = clamp_resident(grid, reinterpret_cast<const void*>(&k_history), kWG, 0);
-  hipLaunchKernelGGL(k_history, dim3(grid), dim3(kWG), 0, st, a, sm);
-  return launch_finalize(sm, t, a.first ? 2 : 1, grid, st);
+  grid = clamp_resident(grid, AA_KERNEL(k_history), kWG, 0);
+  const bool rot = givens_k > 1 && sm.Rg;
+  const size_t lds = rot ? sizeof(double) * (size_t)(givens_k * givens_k) : 0;
+  return pass(sm, t, a.first ? 2 : 1, grid, st, pend, [&](auto, const Small& s, const Pend&) {
+    hipLaunchKernelGGL(k_history, dim3(grid + (rot ? 1 : 0)), dim3(kWG), lds, st, a, s,
+                       rot ? givens_k : 0);
+  });
 }
 
 hipError_t launch_xupdate(const XupdArgs& a, const Small& sm, const Tail& t, int grid,
-                          hipStream_t st) {
+                          hipStream_t st, Pend* pend) {
   (void)hipGetLastError();  // drop a stale error left by an earlier call
-  grid = clamp_resident(grid, reinterpret_cast<const void*>(&k_xupdate), kWG, 0);
-  hipLaunchKernelGGL(k_xupdate, dim3(grid), dim3(kWG), 0, st, a, sm);
-  return launch_finalize(sm, t, 1, grid, st);
+  grid = clamp_resident(grid, pend && pend->on ? AA_KERNEL(k_xupdate<true>) : AA_KERNEL(k_xupdate<false>),
+                        kWG, 0);
+  return pass(sm, t, 1, grid, st, pend, [&](auto P, const Small& s, const Pend& p) {
+    hipLaunchKernelGGL((k_xupdate<decltype(P)::value>), dim3(grid), dim3(kWG), 0, st, a, s, p);
+  });
 }
 
 hipError_t launch_probe(int reads, int writes, const double* src, int64_t ld, double* dst,

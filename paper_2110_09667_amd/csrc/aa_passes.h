@@ -66,7 +66,21 @@ __device__ __forceinline__ void rhs_backsolve(const Small& sm, int k1, double x,
   if (lane < k1) sm.gamma[lane] = gam;
 }
 
-__device__ inline void run_tail(const Small& sm, const Tail& t, const double* red) {
+// The stopping test at the start of an iteration, ||f_i||^2 = res2 (reading A2:
+// the residual against ||f_0||, or the previous step's length).
+__device__ __forceinline__ bool stop_hit(const Small& sm, const Tail& t, double res2) {
+  return t.stop_mode == kStopResidual
+             ? sqrt(res2) <= t.stop_tol * sqrt(sm.scal[S_RES0])
+             : (t.stop_mode == kStopStep && sqrt(sm.scal[S_STEP]) < t.stop_tol);
+}
+
+// writer: whether this workgroup stores what only one may store.  Several
+// workgroups may run a tail on the same values at once (a reduction's consumer
+// summing the partials itself): what they all store is the same, and the
+// updates in place (R's column k-1 of DCGS-2, the folded solve, the stop state)
+// are the writer's.
+__device__ inline void run_tail(const Small& sm, const Tail& t, const double* red,
+                                bool writer = true) {
   const int tid = threadIdx.x, lane = tid & 63;
   const int nthr = blockDim.x;
   const int cap = sm.cap;
@@ -92,7 +106,7 @@ __device__ inline void run_tail(const Small& sm, const Tail& t, const double* re
           if (!(nv > kBreakdownRel * sqrt(col)) || !isfinite(nv)) *sm.status = AA_EBREAKDOWN;
         }
       }
-      if (t.rhs) {
+      if (t.rhs && writer) {
         // c_k = q_k^T f = (w^T f) / R_kk; c_0..c_{k-1} were stashed in gamma
         // by the first pass of this QRAdd.  Then R gamma = c.
         __syncthreads();
@@ -159,7 +173,7 @@ __device__ inline void run_tail(const Small& sm, const Tail& t, const double* re
         for (int i = tid; i < p; i += nthr) {
           const double s = red[k + i];
           sm.coef1[i] = s;
-          R[i + (size_t)p * cap] += scale * s;
+          if (writer) R[i + (size_t)p * cap] += scale * s;
         }
       }
       if (t.rhs) {
@@ -179,15 +193,12 @@ __device__ inline void run_tail(const Small& sm, const Tail& t, const double* re
       rhs_backsolve(sm, k, lane < k ? red[lane] : 0.0);
       break;
     case TAIL_RES:
-      if (tid == 0) {
+      if (tid == 0 && writer) {
         sm.scal[S_RES] = red[0];
         // the stopping test at the start of this iteration (reading A2):
         // the residual against ||f_0||, or the previous step's length
         if (sm.stop && sm.stop->done == 0) {
-          const bool hit = t.stop_mode == kStopResidual
-                               ? sqrt(red[0]) <= t.stop_tol * sqrt(sm.scal[S_RES0])
-                               : (t.stop_mode == kStopStep && sqrt(sm.scal[S_STEP]) < t.stop_tol);
-          if (hit) {
+          if (stop_hit(sm, t, red[0])) {
             sm.stop->iter = sm.stop->cur;
             sm.stop->k = t.k;
             sm.stop->m_i = t.m_i;
@@ -332,7 +343,7 @@ __device__ __forceinline__ void lds_zero(double* p, int n) {
 // ---------------------------------------------------------------------------
 
 __device__ __forceinline__ int dots_nred(const DotsArgs& a) {
-  return a.nx + a.ny + a.nz + (a.xx ? 1 : 0) + (a.xz ? 1 : 0);
+  return a.nx + a.ny + a.nz + (a.xx ? 1 : 0) + (a.xz ? 1 : 0) + (a.w ? 1 : 0);
 }
 
 __device__ inline void dots_body(const DotsArgs& a, int64_t t0, int64_t ts, double* acc) {
@@ -428,7 +439,8 @@ __device__ inline void dots_reg_body(const DotsArgs& a, int64_t t0, int64_t ts, 
   for (int r = 0; r < NR; ++r)
 #pragma unroll
     for (int i = 0; i < KQ; ++i) s[r][i] = 0.0;
-  double sxx = 0.0, sxz = 0.0;
+  double sxx = 0.0, sxz = 0.0, sw = 0.0;
+  const double wdiv = NR == 1 && a.w ? *a.wdiv : 1.0;
   // The QRAdd's first pass of ICWY and DCGS-2 dots Q with [v, q_{k-1}], and
   // q_{k-1} is Q's last column: take that column from the right-hand side
   // already in registers instead of reading it twice (the pass then moves
@@ -473,6 +485,21 @@ __device__ inline void dots_reg_body(const DotsArgs& a, int64_t t0, int64_t ts, 
           for (int r = 0; r < NR; ++r) s[r][j0 + c] += dot2(q[c], rv[r]);
       }
     }
+    if constexpr (NR == 1) {
+      // the QRAdd's w: q_k = w / R_kk, stored and used here (the scale pass
+      // without its read and its launch)
+      if (a.w) {
+        double2 q[kPairs];
+        ld2<F>(q, a.w, b2, a.n);
+#pragma unroll
+        for (int i = 0; i < kPairs; ++i) {
+          q[i].x /= wdiv;
+          q[i].y /= wdiv;
+        }
+        st2<F>(q, a.w, b2, a.n);
+        sw += dot2(q, rv[0]);
+      }
+    }
   });
   const int cnt[3] = {a.nx, a.ny, a.nz};
   int off = 0;
@@ -489,6 +516,10 @@ __device__ inline void dots_reg_body(const DotsArgs& a, int64_t t0, int64_t ts, 
   if (a.xz) {
     const double p = wave_sum(sxz);
     if (lane == 0) acc[a.nx + a.ny + a.nz + (a.xx ? 1 : 0)] = p;
+  }
+  if (NR == 1 && a.w) {
+    const double p = wave_sum(sw);
+    if (lane == 0) acc[dots_nred(a) - 1] = p;
   }
 }
 
@@ -782,10 +813,11 @@ __device__ inline void cgs2b_stream_body(const Cgs2bArgs& a, const double* s_s, 
 // QRDelete (Alg. 2): Givens rotations from R, then one sweep over Q
 // ---------------------------------------------------------------------------
 
-// H = R_{:,1:k-1}; rotation j zeroes H_{j+1,j}; R <- the (k-1)x(k-1) triangle.
+// H = R_{:,1:k-1}; rotation j zeroes H_{j+1,j}; R (or Rout) <- the (k-1)x(k-1)
+// triangle.
 // Any block size; every thread must call (barriers inside).  H: k*k doubles
 // of LDS.
-__device__ inline void givens_body(const Small& sm, int k, double* H) {
+__device__ inline void givens_body(const Small& sm, int k, double* H, double* Rout = nullptr) {
   const int tid = threadIdx.x, nthr = blockDim.x;
   const int cap = sm.cap;
   const int nc = k - 1;
@@ -818,7 +850,7 @@ __device__ inline void givens_body(const Small& sm, int k, double* H) {
   __syncthreads();
   for (int idx = tid; idx < k * k; idx += nthr) {
     const int i = idx % k, j = idx / k;
-    sm.R[i + (size_t)j * cap] = (i < nc && j < nc && i <= j) ? H[i + j * k] : 0.0;
+    (Rout ? Rout : sm.R)[i + (size_t)j * cap] = (i < nc && j < nc && i <= j) ? H[i + j * k] : 0.0;
   }
 }
 
@@ -1420,9 +1452,20 @@ __device__ inline void xupdate_body(const XupdArgs& a, const double* s_g, const 
                                     int64_t t0, int64_t ts, double* acc) {
   const int lane = threadIdx.x & 63;
   double sdx = 0.0;  // this lane's share of ||x_{i+1} - x_i||^2
+  const double sdiv = a.scol ? *a.sdiv : 1.0;
   for_tiles(a.n, t0, ts, [&](int64_t b2, auto full) {
     constexpr bool F = decltype(full)::value;
     double2 gv[kPairs], xv[kPairs], sum[kPairs];
+    if (a.scol) {  // the QRAdd's w -> q_k = w / R_kk
+      double2 q[kPairs];
+      ld2<F>(q, a.scol, b2, a.n);
+#pragma unroll
+      for (int i = 0; i < kPairs; ++i) {
+        q[i].x /= sdiv;
+        q[i].y /= sdiv;
+      }
+      st2<F>(q, a.scol, b2, a.n);
+    }
     ld2<F>(gv, a.g, b2, a.n);
     ld2<F>(xv, a.x, b2, a.n);
     zero2(sum);
