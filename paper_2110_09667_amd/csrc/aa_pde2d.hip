@@ -75,11 +75,10 @@ struct Lev {
 struct Pcg {
   double* sc;        // S_RR0, S_RHO_PREV
   int* ist;          // I_DONE, I_ITERS, I_CONV
-  double* p_rr;      // partials of r.r (k_init, k_update), kMaxWG each
+  double* p_rr;      // partials of r.r (k_init, k_down), kMaxWG each
   double* p_rho;     // partials of r.z (the cycle's last kernel on the fine grid)
   double* p_pq;      // partials of p.q (k_dir)
-  int np_fine;       // partials of the fine-grid vector kernels (their workgroups)
-  int np_rho;        // partials of r.z: np_fine, or 1 from the coarse kernel
+  int np_fine;       // partials of the fine-grid kernels (their workgroups)
   double tol2;
   int max_iter;
   int fixed;         // >= 0: exactly this many iterations
@@ -240,7 +239,7 @@ __global__ __launch_bounds__(kBX) void k_down(Lev L, Lev C, DownFine f, Pcg a, i
         pv[v] = f.p[p < 0 ? 0 : p];
       }
       if (t == (int)blockIdx.x) {
-        const double rho = sum_parts(a.p_rho, a.np_rho);
+        const double rho = sum_parts(a.p_rho, a.np_fine);
         alpha = rho / sum_parts(a.p_pq, a.np_fine);
         // rho for the next iteration's beta (k_dir read the previous one already)
         if (blockIdx.x == 0 && threadIdx.x == 0) a.sc[S_RHO_PREV] = rho;
@@ -371,8 +370,8 @@ __global__ __launch_bounds__(kBX) void k_up(Lev L, const double* r, const double
 // the levels from 64 points per side down: one workgroup, arrays in LDS
 // --------------------------------------------------------------------------
 
-// LDS levels 0 .. nlev-1 (each half the one before it); with nmat > 0 the
-// level after them (nmat points per side, at most 8) and everything below it
+// LDS levels 0 .. nlev-1 (each half the one before it; none in a solve whose
+// second level is the matrix); with nmat > 0 the level after them (nmat points per side, at most 8) and everything below it
 // is the matrix `mat` (nmat^2 square, symmetric up to rounding) applied to its
 // scaled right-hand side.
 struct CoarseArgs {
@@ -394,6 +393,7 @@ struct CoarseArgs {
 struct CoarseLds {
   double* buf;
   const CoarseArgs& c;
+  double *mb, *mz;  // the matrix's right-hand side and result, kMatN^2 each
   __device__ double* b(int l) const { return buf + c.off[l]; }
   __device__ double* z(int l) const { return buf + (c.off[l] + c.off[l + 1]) / 2; }
 };
@@ -420,7 +420,7 @@ __device__ __forceinline__ void gs_colour(const double* b, double* z, int N, int
 // matv: this thread's share of the matrix (row t / 16, columns t % 16, + 16, ...)
 __device__ __forceinline__ void coarse_cycle(const CoarseLds& A, const double (&matv)[4]) {
   const CoarseArgs& c = A.c;
-  __shared__ double mb[kMatN * kMatN], mz[kMatN * kMatN];
+  double *mb = A.mb, *mz = A.mz;
   for (int l = 0; l < c.nlev; ++l) {
     const int N = c.N[l], S = N + 2;
     double *b = A.b(l), *z = A.z(l);
@@ -490,13 +490,13 @@ __device__ __forceinline__ void load_mat(const CoarseArgs& c, double (&matv)[4])
 
 // One workgroup: bound by its barrier phases (5 a level, 64 and 32 and 16
 // points per side at N = 1024, then the matrix in 2 instead of another 16).
-__global__ __launch_bounds__(kCoarseWG) void k_coarse(CoarseArgs c, Pcg a, int k, int check,
-                                                      int dot) {
+__global__ __launch_bounds__(kCoarseWG) void k_coarse(CoarseArgs c, Pcg a, int k, int check) {
   __shared__ double buf[kCoarseLds];
   double matv[4];
   load_mat(c, matv);
   if (check ? pcg_check(a, k) : a.ist[I_DONE] != 0) return;
-  const CoarseLds A{buf, c};
+  __shared__ double mb[kMatN * kMatN], mz[kMatN * kMatN];
+  const CoarseLds A{buf, c, mb, mz};
   const int t = threadIdx.x, N = c.N[0], S = N + 2;
   for (int e = t; e < c.off[c.nlev]; e += kCoarseWG) buf[e] = 0.0;
   __syncthreads();
@@ -511,24 +511,17 @@ __global__ __launch_bounds__(kCoarseWG) void k_coarse(CoarseArgs c, Pcg a, int k
   }
   __syncthreads();
   coarse_cycle(A, matv);
-  double acc = 0.0;
   for (int j = t >> 6; j < N; j += kCoarseWG / 64) {
     const int i = t & 63;
-    if (i < N) {
-      const int p = (j + 1) * S + i + 1;
-      const double z = A.z(0)[p];
-      c.z_out[j * N + i] = z;
-      if (dot) acc = fma(A.b(0)[p], z, acc);
-    }
+    if (i < N) c.z_out[j * N + i] = A.z(0)[(j + 1) * S + i + 1];
   }
-  if (dot) partial_store(acc / c.scale, a.p_rho);
 }
 
 // The matrix of the last levels: workgroup e runs their cycle (c.nmat = 0) on
 // the e-th unit vector and stores column e.
 __global__ __launch_bounds__(kCoarseWG) void k_matrix(CoarseArgs c, double* mat) {
   __shared__ double buf[kCoarseLds];
-  const CoarseLds A{buf, c};
+  const CoarseLds A{buf, c, buf, buf};  // (no matrix below these levels)
   const int N = c.N[0], S = N + 2, n2 = N * N;
   for (int e = threadIdx.x; e < kCoarseLds; e += kCoarseWG) buf[e] = 0.0;
   __syncthreads();
@@ -557,18 +550,21 @@ __device__ __forceinline__ double c_term(int problem, double u) {
   return 100.0 * (u - u * u);  // AA_PDE_HEAT_NL2
 }
 
-// r = rhs(u) (heat: c(u) - b; Bratu: lambda e^u; plain solve: d_rhs), x = 0,
-// r.r; resets the solve state
+// r = rhs(u) at one point (heat: c(u) - b; Bratu: lambda e^u; plain solve: u)
+__device__ __forceinline__ double rhs_at(int problem, double lambda, const double* b, double u,
+                                         int64_t p) {
+  if (problem == AA_PDE_BRATU) return lambda * exp(u);
+  return problem == 0 ? u : c_term(problem, u) - b[p];
+}
+
+// r = rhs(u), x = 0, r.r; resets the solve state
 __global__ __launch_bounds__(kBX) void k_init(int problem, double lambda, const double* b,
                                               const double* u, double* x, double* r, int N,
                                               Pcg a) {
   double acc = 0.0;
   const int64_t n = (int64_t)N * N;
   for (int64_t p = (int64_t)blockIdx.x * kBX + threadIdx.x; p < n; p += (int64_t)gridDim.x * kBX) {
-    double v;
-    if (problem == AA_PDE_BRATU) v = lambda * exp(u[p]);
-    else if (problem == 0) v = u[p];
-    else v = c_term(problem, u[p]) - b[p];
+    const double v = rhs_at(problem, lambda, b, u[p], p);
     r[p] = v;
     x[p] = 0.0;
     acc = fma(v, v, acc);
@@ -602,7 +598,7 @@ __global__ __launch_bounds__(kBX) void k_dir(const double* z, const double* p_pr
       zv[u] = z[p < 0 ? 0 : p];
       pv[u] = first ? 0.0 : p_prev[p < 0 ? 0 : p];
     }
-    if (t == (int)blockIdx.x && !first) beta = sum_parts(a.p_rho, a.np_rho) / a.sc[S_RHO_PREV];
+    if (t == (int)blockIdx.x && !first) beta = sum_parts(a.p_rho, a.np_fine) / a.sc[S_RHO_PREV];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const int e = threadIdx.x + u * kBX;
@@ -627,23 +623,149 @@ __global__ __launch_bounds__(kBX) void k_dir(const double* z, const double* p_pr
   partial_store(acc, a.p_pq);
 }
 
-// alpha = rho_k / (p.q); x += alpha p; r -= alpha q; r.r (grids whose whole
-// cycle runs in k_coarse: there is no k_down to take this)
-__global__ __launch_bounds__(kBX) void k_update(const double* p_cur, const double* q, double* x,
-                                                double* r, int N, Pcg a) {
-  if (a.ist[I_DONE]) return;
-  const double rho = sum_parts(a.p_rho, a.np_rho);
-  const double alpha = rho / sum_parts(a.p_pq, a.np_fine);
-  // rho_k for the next iteration's beta (k_dir read the previous one already)
-  if (blockIdx.x == 0 && threadIdx.x == 0) a.sc[S_RHO_PREV] = rho;
-  double acc = 0.0;
-  for (int p = blockIdx.x * kBX + threadIdx.x; p < N * N; p += gridDim.x * kBX) {
-    x[p] = fma(alpha, p_cur[p], x[p]);
-    const double rv = fma(-alpha, q[p], r[p]);
-    r[p] = rv;
-    acc = fma(rv, rv, acc);
+// --------------------------------------------------------------------------
+// whole solves of small grids: one workgroup
+// --------------------------------------------------------------------------
+
+constexpr int kSmallN = 96;  // its z and the levels below it fill the LDS (131 KB)
+
+// The PCG solve of an N x N grid, N <= 96: r, p and A p of a thread's points in
+// registers, z (and p, for q = A p) of the fine grid and every coarser level in
+// LDS, the last levels the matrix.  One launch instead of 4 an iteration (and
+// none enqueued past the end); bound by its barriers, about 30 an iteration.
+// A thread takes the points `t % W` of each colour of the rows t / W, t / W +
+// 1024 / W, ...: W = 32 and two rows up to 64 points per side, W = 64 and six
+// rows up to 96.  A solve (launches / this): N = 16 195 / 77 us, 31 (56
+// iterations) 957 / 264, 64 300 / 161, 96 331 / 302.
+template <int W, int RP>
+__global__ __launch_bounds__(kCoarseWG) void k_solve_small(int problem, double lambda,
+                                                           const double* b, const double* u,
+                                                           double* xo, int N, int coarse,
+                                                           CoarseArgs c, Pcg a) {
+  extern __shared__ double z0[];  // (N + 2)^2, bordered; then the coarser levels
+  __shared__ double mb[kMatN * kMatN], mz[kMatN * kMatN], lds[16];
+  const int t = threadIdx.x, S = N + 2, Nc = N / 2;
+  const CoarseLds A{z0 + S * S, c, mb, mz};
+  double matv[4];
+  load_mat(c, matv);
+  const double h = 1.0 / (double)(N + 1), H2 = h * h, ih2 = 1.0 / H2;
+  double r[2][RP], p[2][RP], v[2][RP];
+  // body(i, j, offset in z0, r, p, A p) over this thread's points of one colour
+  // (indices are formed anew in each phase: kept for all of them, a dozen
+  // points' worth would push r, p and A p out of the registers)
+  auto points = [&](int col, auto&& body) {
+    int own = t;
+    asm volatile("" : "+v"(own));
+#pragma unroll
+    for (int q = 0; q < RP; ++q) {
+      const int j = own / W + q * (kCoarseWG / W), i = 2 * (own % W) + ((j + col) & 1);
+      if (i < N && j < N) body(i, j, (j + 1) * S + i + 1, r[col][q], p[col][q], v[col][q]);
+    }
+  };
+  auto nb = [&](int o) { return ((z0[o - 1] + z0[o + 1]) + z0[o - S]) + z0[o + S]; };
+  for (int e = t; e < S * S + c.off[c.nlev]; e += kCoarseWG) z0[e] = 0.0;
+  __syncthreads();
+#pragma unroll 1
+  for (int e = t; e < N * N; e += kCoarseWG)
+    z0[(e / N + 1) * S + e % N + 1] = rhs_at(problem, lambda, b, u[e], e);
+  __syncthreads();
+  double rr = 0.0;
+#pragma unroll
+  for (int col = 0; col < 2; ++col)
+    points(col, [&](int, int, int o, double& rv, double& pv, double&) {
+      rv = z0[o];
+      pv = 0.0;
+      rr = fma(rv, rv, rr);
+    });
+  rr = block_sum(rr, lds);
+  const double rr0 = rr;
+  double rho_prev = 0.0;
+  const int last = a.fixed >= 0 ? a.fixed : a.max_iter;
+  int k = 0;
+  while (k < last && (a.fixed >= 0 || !(rr <= a.tol2 * rr0))) {
+    // the cycle: every diagonal entry of the fine grid is 4
+    points(0, [&](int, int, int o, double& rv, double&, double&) { z0[o] = H2 * rv * 0.25; });
+    __syncthreads();
+    points(1, [&](int, int, int o, double& rv, double&, double&) {
+      z0[o] = (H2 * rv + nb(o)) * 0.25;
+    });
+    __syncthreads();
+    if (coarse) {
+      for (int J = t / W; J < Nc; J += kCoarseWG / W) {
+        const int I = t % W;
+        if (I < Nc) {
+          const double v = restrict_red(z0 + (2 * J + 2) * S + 2 * I + 2, S, 2 * I + 1, 2 * J + 1, N);
+          if (c.nlev == 0) {
+            mb[J * Nc + I] = v;
+          } else {
+            const int o = (J + 1) * (Nc + 2) + I + 1;
+            A.b(0)[o] = v;
+            if (((I + J) & 1) == 0) A.z(0)[o] = v * inv_diag(I, J, Nc, c.i1[0], c.i2[0]);
+          }
+        }
+      }
+      __syncthreads();
+      coarse_cycle(A, matv);
+      const double* zc = A.z(0);
+      points(0, [&](int i, int j, int o, double&, double&, double&) {
+        z0[o] += interp_red(i, j, [&](int I, int J) {
+          return c.nlev == 0 ? (I >= 0 && J >= 0 ? mz[J * Nc + I] : 0.0)
+                             : zc[(J + 1) * (Nc + 2) + I + 1];
+        });
+      });
+      __syncthreads();
+      points(1, [&](int, int, int o, double& rv, double&, double&) {
+        z0[o] = (H2 * rv + nb(o)) * 0.25;
+      });
+      __syncthreads();
+    }
+    points(0, [&](int, int, int o, double& rv, double&, double&) {
+      z0[o] = (H2 * rv + nb(o)) * 0.25;
+    });
+    // each thread reads back its own points only
+    double acc = 0.0;
+#pragma unroll
+    for (int col = 0; col < 2; ++col)
+      points(col, [&](int, int, int o, double& rv, double&, double&) {
+        acc = fma(rv, z0[o], acc);
+      });
+    const double rho = block_sum(acc, lds);
+    const double beta = k == 0 ? 0.0 : rho / rho_prev;
+    rho_prev = rho;
+#pragma unroll
+    for (int col = 0; col < 2; ++col)
+      points(col, [&](int, int, int o, double&, double& pv, double&) {
+        pv = fma(beta, pv, z0[o]);
+        z0[o] = pv;  // p, for q = A p (z is not needed any more)
+      });
+    __syncthreads();
+    acc = 0.0;
+#pragma unroll
+    for (int col = 0; col < 2; ++col)
+      points(col, [&](int, int, int o, double&, double& pv, double& q) {
+        q = (4.0 * pv - nb(o)) * ih2;
+        acc = fma(pv, q, acc);
+      });
+    const double alpha = rho / block_sum(acc, lds);
+    acc = 0.0;
+#pragma unroll
+    for (int col = 0; col < 2; ++col)
+      points(col, [&](int i, int j, int, double& rv, double& pv, double& q) {
+        double* xp = xo + j * N + i;
+        *xp = fma(alpha, pv, k == 0 ? 0.0 : *xp);
+        rv = fma(-alpha, q, rv);
+        acc = fma(rv, rv, acc);
+      });
+    rr = block_sum(acc, lds);
+    ++k;
   }
-  partial_store(acc, a.p_rr);
+  if (k == 0)
+    for (int e = t; e < N * N; e += kCoarseWG) xo[e] = 0.0;
+  if (t == 0) {
+    a.ist[I_DONE] = 1;
+    a.ist[I_ITERS] = k;
+    a.ist[I_CONV] = a.fixed >= 0 || rr <= a.tol2 * rr0 ? 1 : 0;
+  }
 }
 
 __global__ void k_reset(int* ist) {
@@ -763,7 +885,6 @@ Pcg pcg_args(const aa_pde2d* c) {
   a.p_rho = c->p_rho;
   a.p_pq = c->p_pq;
   a.np_fine = tile_grid(c->N);
-  a.np_rho = c->first_lds == 0 ? 1 : a.np_fine;  // r.z from the coarse kernel
   a.tol2 = c->tol * c->tol;
   a.max_iter = c->max_iter;
   a.fixed = c->fixed;
@@ -815,13 +936,6 @@ void launch_up(const aa_pde2d* c, int l, const double* r, const Pcg& a, int dot)
 hipError_t launch_vcycle(const aa_pde2d* c, const Pcg& a, int k, int pcg, double* x) {
   const int fl = c->first_lds;
   const double* r = c->r[k & 1];
-  if (fl == 0) {
-    r = c->r[0];  // updated in place
-    if (k > 0)
-      hipLaunchKernelGGL(k_update, dim3(a.np_fine), dim3(kBX), 0, c->st,
-                         (const double*)c->p[(k + 1) & 1], (const double*)c->q, x, c->r[0], c->N,
-                         a);
-  }
   for (int l = 0; l < fl; ++l) {
     const DownFine f{c->r[l == 0 && k > 0 ? (k + 1) & 1 : 0], c->r[k & 1], c->p[(k + 1) & 1], c->q,
                      x};
@@ -837,8 +951,7 @@ hipError_t launch_vcycle(const aa_pde2d* c, const Pcg& a, int k, int pcg, double
   ca.in = fl == 0 ? r : c->lev[fl].b;
   if (fl == 0) ca.scale = c->lev[0].H2;
   ca.z_out = c->lev[fl].z;
-  hipLaunchKernelGGL(k_coarse, dim3(1), dim3(kCoarseWG), 0, c->st, ca, a, k, pcg && fl <= 1,
-                     pcg && fl == 0);
+  hipLaunchKernelGGL(k_coarse, dim3(1), dim3(kCoarseWG), 0, c->st, ca, a, k, pcg && fl <= 1);
   for (int l = fl - 1; l > 0; --l) launch_up<false>(c, l, nullptr, a, 0);
   if (fl > 0) launch_up<true>(c, 0, r, a, pcg);
   return hipGetLastError();
@@ -863,12 +976,40 @@ hipError_t launch_iteration(const aa_pde2d* c, const Pcg& a, int k, double* x) {
 
 aa_status hipst(hipError_t e) { return e == hipSuccess ? AA_OK : AA_EHIP; }
 
+// the whole solve of a small grid in one launch
+hipError_t launch_small(const aa_pde2d* c, const Pcg& a, int problem, const double* b,
+                        const double* u, double* x) {
+  const int N = c->N, coarse = c->nlev > 1 ? 1 : 0;
+  const int to = c->first_mat;  // levels 1 .. to-1 in LDS, then the matrix
+  const CoarseArgs ca = coarse_args(c, coarse, coarse ? to : 0,
+                                    coarse && to < c->nlev ? c->lev[to].N : 0);
+  const size_t lds = sizeof(double) * (size_t)((N + 2) * (N + 2) + ca.off[ca.nlev]);
+  if (N <= 64)
+    hipLaunchKernelGGL((k_solve_small<32, 2>), dim3(1), dim3(kCoarseWG), lds, c->st, problem,
+                       c->lambda, b, u, x, N, coarse, ca, a);
+  else
+    hipLaunchKernelGGL((k_solve_small<64, 6>), dim3(1), dim3(kCoarseWG), lds, c->st, problem,
+                       c->lambda, b, u, x, N, coarse, ca, a);
+  return hipGetLastError();
+}
+
 // the PCG solve of A x = rhs(problem, u): enqueue iterations, read the state
 // now and then (a first batch sized by the previous solve)
 aa_status solve(aa_pde2d* c, int problem, const double* b, const double* u, double* x) {
   (void)hipGetLastError();
   const Pcg a = pcg_args(c);
   const int N = c->N;
+  if (N <= kSmallN) {
+    hipError_t e = launch_small(c, a, problem, b, u, x);
+    int st[3] = {0, 0, 0};
+    if (e == hipSuccess)
+      e = hipMemcpyAsync(st, c->ist, sizeof(st), hipMemcpyDeviceToHost, c->st);
+    if (e == hipSuccess) e = hipStreamSynchronize(c->st);
+    if (e != hipSuccess || !st[I_DONE]) return AA_EHIP;
+    c->last_iters = c->predicted = st[I_ITERS];
+    c->last_conv = st[I_CONV];
+    return AA_OK;
+  }
   hipLaunchKernelGGL(k_init, dim3(a.np_fine), dim3(kBX), 0, c->st, problem, c->lambda, b, u, x,
                      c->r[0], N, a);
   hipError_t e = hipGetLastError();
