@@ -24,7 +24,8 @@
 // and post-smoothing), each a tile per workgroup with its halo recomputed in
 // LDS; the levels from 64 points down run in one kernel of one workgroup with
 // every array in LDS, the last ones (at most 8 points per side) as one
-// precomputed matrix.  On the fine grid k_down also takes the conjugate
+// precomputed matrix.  Grids of at most 96 points per side are solved by one
+// launch of one workgroup (k_solve_small).  On the fine grid k_down also takes the conjugate
 // gradient's update of x and r, and k_up gives r.z.  A PCG iteration at N =
 // 1024 is 10 launches (23 when each half-sweep, each restriction and each
 // vector update was one); the whole working set (~60 MB) stays in the Infinity
@@ -53,8 +54,6 @@ constexpr int kCoarseN = 32;       // the hierarchy must reach this many points 
 constexpr int kLdsN = 64;          // levels of at most this many points per side in LDS
 constexpr int kMatN = 8;           // levels of at most this many as one matrix
 constexpr int kCoarseWG = 1024;    // threads of the coarse kernel
-// b and z of the LDS levels with a border of zeros (66, 34, 18, 10, ... per side)
-constexpr int kCoarseLds = 2 * (66 * 66 + 34 * 34 + 18 * 18 + 10 * 10 + 6 * 6 + 4 * 4 + 3 * 3);
 constexpr int kMaxLevels = 32;
 
 // integer state words
@@ -121,16 +120,17 @@ __device__ __forceinline__ double restrict_red(const double* e, int S, int ic, i
 // in index order (per thread, then the fixed tree of block_sum)
 // --------------------------------------------------------------------------
 
-__device__ double block_sum(double v, double* lds4) {
+// the sum over the workgroup (4 or 16 waves), in every lane.  lds: 16 doubles
+// that nobody reads any more.
+__device__ __forceinline__ double block_sum(double v, double* lds) {
   v = wave_sum(v);
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const bool four = blockDim.x == kBX;
+  if (lane == 0) lds[w] = v;
   __syncthreads();
-  if (lane == 0) lds4[w] = v;
-  __syncthreads();
-  double s = 0.0;
-  const int nw = blockDim.x >> 6;
-  for (int k = 0; k < nw; ++k) s += lds4[k];
-  return s;
+  v = lds[lane & (four ? 3 : 15)];
+  if (!four) v = add_xor<4>(add_xor<8>(v));
+  return add_xor<1>(add_xor<2>(v));
 }
 
 // this workgroup's sum of v, stored as its partial
@@ -140,7 +140,9 @@ __device__ void partial_store(double v, double* parts) {
   if (threadIdx.x == 0) parts[blockIdx.x] = s;
 }
 
-// the sum of np partials, in one fixed order (every workgroup gets the same)
+// the sum of np partials, in one fixed order (every workgroup gets the same);
+// a kernel's sums have a SLOT each
+template <int SLOT>
 __device__ double sum_parts(const double* parts, int np) {
   __shared__ double lds[16];
   double acc = 0.0;
@@ -153,7 +155,7 @@ __device__ double sum_parts(const double* parts, int np) {
 // true when the solve has ended.
 __device__ __forceinline__ bool pcg_check(const Pcg& a, int k) {
   if (a.ist[I_DONE]) return true;
-  const double rr = sum_parts(a.p_rr, a.np_fine);
+  const double rr = sum_parts<0>(a.p_rr, a.np_fine);
   const double rr0 = k == 0 ? rr : a.sc[S_RR0];
   if (k == 0 && blockIdx.x == 0 && threadIdx.x == 0) a.sc[S_RR0] = rr;
   bool stop;
@@ -239,8 +241,8 @@ __global__ __launch_bounds__(kBX) void k_down(Lev L, Lev C, DownFine f, Pcg a, i
         pv[v] = f.p[p < 0 ? 0 : p];
       }
       if (t == (int)blockIdx.x) {
-        const double rho = sum_parts(a.p_rho, a.np_fine);
-        alpha = rho / sum_parts(a.p_pq, a.np_fine);
+        const double rho = sum_parts<1>(a.p_rho, a.np_fine);
+        alpha = rho / sum_parts<2>(a.p_pq, a.np_fine);
         // rho for the next iteration's beta (k_dir read the previous one already)
         if (blockIdx.x == 0 && threadIdx.x == 0) a.sc[S_RHO_PREV] = rho;
       }
@@ -371,168 +373,290 @@ __global__ __launch_bounds__(kBX) void k_up(Lev L, const double* r, const double
 // --------------------------------------------------------------------------
 
 // LDS levels 0 .. nlev-1 (each half the one before it; none in a solve whose
-// second level is the matrix); with nmat > 0 the level after them (nmat points per side, at most 8) and everything below it
-// is the matrix `mat` (nmat^2 square, symmetric up to rounding) applied to its
-// scaled right-hand side.
+// second level is the matrix); with nmat > 0 the level after them (nmat points
+// per side, at most 8) and everything below it is the matrix `mat` (nmat^2
+// square, symmetric up to rounding) applied to its scaled right-hand side.
+constexpr int kLdsLev = 4;  // 8, 4, 2, 1 in k_matrix; 64, 32, 16 otherwise
+
 struct CoarseArgs {
   const double* in;    // right-hand side of the first LDS level (global)
   double scale;        // b = scale * in
   double* z_out;       // its post-smoothed correction (global)
-  int N[kMaxLevels];   // sizes of the LDS levels
-  double i1[kMaxLevels];
-  double i2[kMaxLevels];
-  int off[kMaxLevels + 1];  // where a level's b and z start in LDS
+  int N[kLdsLev];      // sizes of the LDS levels
+  double inv[kLdsLev][3];    // 1 / diagonal inside, on the last row or column, in the corner
+  int off[kLdsLev + 1];      // where a level's b and z start in LDS
+  unsigned half[kLdsLev];    // div_small of (N + 1) / 2
+  unsigned full[kLdsLev];    // div_small of N
+  unsigned full_mat;         // div_small of nmat
   int nlev;
   int nmat;
   const double* mat;   // [out][in]
 };
 
-// The cycle on the LDS levels, right-hand side b and red e = b / d of level 0
-// in place.  Arrays have a border of zeros (row stride N + 2).  A thread takes
-// the colour's point `slot` of rows t / 32, t / 32 + 32, ...: no divisions.
-struct CoarseLds {
-  double* buf;
-  const CoarseArgs& c;
-  double *mb, *mz;  // the matrix's right-hand side and result, kMatN^2 each
-  __device__ double* b(int l) const { return buf + c.off[l]; }
-  __device__ double* z(int l) const { return buf + (c.off[l] + c.off[l + 1]) / 2; }
+// e / d as (e m) >> 20 with m = div_small(d): exact while e d < 2^20 (here e <
+// 2560 and d <= 64)
+inline unsigned div_small(int d) { return (unsigned)(((1 << 20) + d - 1) / d); }
+__device__ __forceinline__ int div_by(int e, unsigned m) {
+  return (int)(((unsigned)e * m) >> 20);
+}
+
+// Bordered arrays: a border of zeros, rows of an even number of doubles.
+__host__ __device__ constexpr int row_of(int N) { return N + 2 + (N & 1); }
+__host__ __device__ constexpr int area_of(int N) { return row_of(N) * (N + 2); }
+constexpr int kCoarseLds = 2 * (area_of(kLdsN) + area_of(kLdsN / 2) + area_of(kLdsN / 4));
+
+// A slot is one red and one black point.  Even slots of a level take the rows
+// 0, 2, ..., odd slots the rows 1, 3, ..., where the colour's columns have the
+// other parity: 16 neighbouring lanes (128 bytes, what the LDS delivers in a
+// cycle) read 16 different banks, where a row alone, every second double,
+// conflicts two ways.  A point's word: offset | edges << 20 (edges: how many of
+// "last column", "last row" it is in, the index into `inv`), -1 outside.
+struct Slot {
+  int red, blk;
+  int cc;  // offset of the coarse point (I, J) = (i / 2, j / 2) of either
 };
 
-// body(i, j, offset) over the points of one colour (0: i + j even)
-template <class Body>
-__device__ __forceinline__ void colour_points(int N, int colour, Body&& body) {
-  const int s = threadIdx.x & 31, S = N + 2;
-  for (int j = threadIdx.x >> 5; j < N; j += (int)(blockDim.x >> 5)) {
-    const int i = 2 * s + ((j + colour) & 1);
-    if (i < N) body(i, j, (j + 1) * S + i + 1);
+__device__ __forceinline__ Slot slot_of(int e, int N, unsigned half) {
+  const int S = row_of(N), par = e & 1, h = e >> 1;
+  const int J = div_by(h, half), s = h - J * ((N + 1) >> 1), j = 2 * J + par;
+  auto word = [&](int i) {
+    return i < N && j < N ? ((j + 1) * S + i + 1) | ((i == N - 1) + (j == N - 1)) << 20 : -1;
+  };
+  return Slot{word(2 * s + par), word(2 * s + 1 - par), (J + 1) * row_of(N >> 1) + s + 1};
+}
+
+// What is formed from v is formed anew from here on.  A solve in one workgroup
+// forms the same offsets in every iteration: kept for all phases they would
+// push its vectors out of the registers.
+__device__ __forceinline__ void fresh(int& v) { asm volatile("" : "+v"(v)); }
+
+__device__ __forceinline__ double four(const double* z, int S) {
+  return ((z[-1] + z[1]) + z[-S]) + z[S];
+}
+
+// Sum of the interpolated corrections at the four red neighbours of a black
+// point (N even), zc at its coarse point.  Two of the neighbours are coarse
+// points, across the direction of the other two, which are means of four; the
+// one after the point lies outside the grid on the last column or row (`edge`).
+// par 0: j even, i odd, the means lie along x; par 1: along y.
+__device__ __forceinline__ double interp_around(const double* zc, int Sc, int par, bool edge) {
+  const int u = par ? Sc : 1, v = par ? 1 : Sc;
+  const double here = zc[0] + zc[-v];
+  const double before = zc[-u] + zc[-u - v], after = zc[u] + zc[u - v];
+  return here + 0.25 * ((before + here) + (edge ? 0.0 : after + here));
+}
+
+// Scaled right-hand sides of the next level, n points per side, from the black
+// values of one of N = 2 n (restrict_red with x and y exchanged in every second
+// row: lanes of both rows then read different banks).  put(J n + I, I, J, value)
+template <class Put>
+__device__ __forceinline__ void restrict_level(const double* z, int N, int n, unsigned full,
+                                               Put&& put) {
+  int t = threadIdx.x;
+  fresh(t);
+  const int S = row_of(N), par = t & 1;
+  const int u = par ? S : 1, v = par ? 1 : S;
+  const int points = 2 * n * ((n + 1) >> 1);
+  for (int e = t; e < points; e += kCoarseWG) {
+    const int h = e >> 1, Jp = div_by(h, full), I = h - Jp * n, J = 2 * Jp + par;
+    if (J < n) {
+      const bool xl = I == n - 1, yl = J == n - 1, ul = par ? yl : xl, vl = par ? xl : yl;
+      const double* q = z + (2 * J + 2) * S + 2 * I + 2;
+      const double in = (ul ? 1.25 : 1.5) * (q[-v] + q[v]) + (vl ? 1.25 : 1.5) * (q[-u] + q[u]);
+      double out = (q[-v - 2 * u] + q[v - 2 * u]) + (q[-2 * v - u] + q[-2 * v + u]);
+      if (!ul) out += q[-v + 2 * u] + q[v + 2 * u];
+      if (!vl) out += q[2 * v - u] + q[2 * v + u];
+      put(J * n + I, I, J, in + 0.25 * out);
+    }
   }
 }
 
-// Gauss-Seidel on one colour of a bordered level
-__device__ __forceinline__ void gs_colour(const double* b, double* z, int N, int colour, double i1,
-                                          double i2) {
-  const int S = N + 2;
-  colour_points(N, colour, [&](int i, int j, int c) {
-    z[c] = (b[c] + (((z[c - 1] + z[c + 1]) + z[c - S]) + z[c + S])) * inv_diag(i, j, N, i1, i2);
-  });
-}
+struct MatLds {
+  double in[kMatN * kMatN];
+  double out[area_of(kMatN)];          // bordered
+  double inv[kLdsLev * 3];             // CoarseArgs::inv
+};
 
-// matv: this thread's share of the matrix (row t / 16, columns t % 16, + 16, ...)
-__device__ __forceinline__ void coarse_cycle(const CoarseLds& A, const double (&matv)[4]) {
-  const CoarseArgs& c = A.c;
-  double *mb = A.mb, *mz = A.mz;
-  for (int l = 0; l < c.nlev; ++l) {
-    const int N = c.N[l], S = N + 2;
-    double *b = A.b(l), *z = A.z(l);
-    gs_colour(b, z, N, 1, c.i1[l], c.i2[l]);  // black, after red = b / d
-    __syncthreads();
-    const bool last = l + 1 == c.nlev;
-    if (last && c.nmat == 0) break;
-    const int Nc = N / 2;
-    for (int J = threadIdx.x >> 5; J < Nc; J += (int)(blockDim.x >> 5)) {
-      const int I = threadIdx.x & 31;
-      if (I < Nc) {
-        const double v = restrict_red(z + (2 * J + 2) * S + 2 * I + 2, S, 2 * I + 1, 2 * J + 1, N);
-        if (last) {
-          mb[J * Nc + I] = v;
-        } else {
-          const int cc = (J + 1) * (Nc + 2) + I + 1;
-          A.b(l + 1)[cc] = v;
-          if (((I + J) & 1) == 0)
-            A.z(l + 1)[cc] = v * inv_diag(I, J, Nc, c.i1[l + 1], c.i2[l + 1]);
+// This workgroup's slots, matrix share (row t / 16, columns t % 16, + 16, ...)
+// and arrays.  LV levels at most, NS slots a thread on the first of them.
+template <int LV, int NS>
+struct Coarse {
+  const CoarseArgs& c;
+  double* buf;
+  MatLds& m;
+  Slot slot[LV][NS];
+  double mat[4];
+
+  __device__ double* b(int l) const { return buf + c.off[l]; }
+  __device__ double* z(int l) const { return buf + (c.off[l] + c.off[l + 1]) / 2; }
+
+  // (the caller clears buf, and a barrier comes before the first cycle)
+  __device__ __forceinline__ Coarse(const CoarseArgs& c_, double* buf_, MatLds& m_)
+      : c(c_), buf(buf_), m(m_) {
+    const int t = threadIdx.x, n2 = c.nmat * c.nmat, row = t >> 4;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int col = (t & 15) + 16 * q;
+      mat[q] = row < n2 && col < n2 ? c.mat[row * n2 + col] : 0.0;
+    }
+#pragma unroll
+    for (int l = 0; l < LV; ++l) {
+#pragma unroll
+      for (int q = 0; q < (l ? 1 : NS); ++q)
+        slot[l][q] = slot_of(t + q * kCoarseWG, c.N[l], c.half[l]);
+      if (t < 3) m.inv[3 * l + t] = t == 0 ? c.inv[l][0] : t == 1 ? c.inv[l][1] : c.inv[l][2];
+    }
+    for (int e = t; e < area_of(kMatN); e += kCoarseWG) m.out[e] = 0.0;
+  }
+
+  // this thread's points of one colour of level l: body(offset, 1 / d, edges,
+  // offset of the coarse point)
+  template <class Body>
+  __device__ __forceinline__ void colour(int l, int col, Body&& body) const {
+#pragma unroll
+    for (int q = 0; q < (l ? 1 : NS); ++q) {
+      int w = col ? slot[l][q].blk : slot[l][q].red, cc = slot[l][q].cc;
+      fresh(w);
+      fresh(cc);
+      if (w >= 0) body(w & 0xfffff, m.inv[3 * l + (w >> 20)], w >> 20, cc);
+    }
+  }
+
+  // the right-hand sides of level l (the matrix: l = nlev) from the level above it
+  __device__ __forceinline__ void restrict_to(int l, const double* zf, int N) const {
+    const int n = N / 2;
+    if (l >= LV || l == c.nlev) {
+      restrict_level(zf, N, n, c.full_mat, [&](int p, int, int, double v) { m.in[p] = v; });
+    } else {
+      double *bl = b(l), *zl = z(l);
+      restrict_level(zf, N, n, c.full[l], [&](int, int I, int J, double v) {
+        const int o = (J + 1) * row_of(n) + I + 1;
+        bl[o] = v;
+        if (((I + J) & 1) == 0) zl[o] = v * m.inv[3 * l + (I == n - 1) + (J == n - 1)];
+      });
+    }
+  }
+
+  // The cycle on the LDS levels and the matrix; of level 0 the right-hand side
+  // b and the red e = b / d are in place, its result is z(0).  The correction is
+  // added to the red values only where the black sweep reads them: the red
+  // sweep that follows needs none of their values.
+  __device__ __forceinline__ void cycle() const {
+#pragma unroll
+    for (int l = 0; l < LV; ++l) {
+      if (l < c.nlev) {
+        const double* bl = b(l);
+        double* zl = z(l);
+        colour(l, 1, [&](int o, double inv, int, int) {
+          zl[o] = (bl[o] + four(zl + o, row_of(c.N[l]))) * inv;
+        });
+        __syncthreads();
+        const bool last = l + 1 == c.nlev;
+        if (!last || c.nmat) {
+          restrict_to(l + 1, zl, c.N[l]);
+          __syncthreads();
         }
       }
     }
-    __syncthreads();
-  }
-  if (c.nmat) {
-    const int n2 = c.nmat * c.nmat, row = threadIdx.x >> 4;
-    double v = 0.0;
+    if (c.nmat) {
+      int t = threadIdx.x;
+      fresh(t);
+      const int n = c.nmat, row = t >> 4;
+      double v = 0.0;
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int col = (threadIdx.x & 15) + 16 * q;
-      if (col < n2) v = fma(matv[q], mb[col], v);
+      for (int q = 0; q < 4; ++q) {
+        const int col = (t & 15) + 16 * q;
+        if (col < n * n) v = fma(mat[q], m.in[col], v);
+      }
+      v = add_xor<1>(add_xor<2>(add_xor<4>(add_xor<8>(v))));
+      const int J = div_by(row, c.full_mat);
+      if (row < n * n && (t & 15) == 0) m.out[(J + 1) * row_of(n) + row - J * n + 1] = v;
+      __syncthreads();
     }
 #pragma unroll
-    for (int o = 8; o >= 1; o >>= 1) v += __shfl_xor(v, o, 64);
-    if (row < n2 && (threadIdx.x & 15) == 0) mz[row] = v;
-    __syncthreads();
-  }
-  for (int l = c.nlev - 1; l >= 0; --l) {
-    const int N = c.N[l];
-    double *b = A.b(l), *z = A.z(l);
-    const bool last = l + 1 == c.nlev;
-    if (!last || c.nmat) {
-      const int Nc = N / 2;
-      const double* zc = last ? nullptr : A.z(l + 1);
-      colour_points(N, 0, [&](int i, int j, int p) {
-        z[p] += interp_red(i, j, [&](int I, int J) {
-          return last ? (I >= 0 && J >= 0 ? mz[J * Nc + I] : 0.0) : zc[(J + 1) * (Nc + 2) + I + 1];
+    for (int l = LV - 1; l >= 0; --l) {
+      if (l < c.nlev) {
+        const double* bl = b(l);
+        double* zl = z(l);
+        const int S = row_of(c.N[l]), last = l + 1 == c.nlev;
+        if (!last || c.nmat) {
+          const double* zc = last ? m.out : z(l + 1 < LV ? l + 1 : l);
+          const int Sc = row_of(c.N[l] / 2), par = threadIdx.x & 1;
+          colour(l, 1, [&](int o, double inv, int edges, int cc) {
+            zl[o] = (bl[o] + (four(zl + o, S) + interp_around(zc + cc, Sc, par, edges != 0))) *
+                    inv;
+          });
+          __syncthreads();
+        }
+        colour(l, 0, [&](int o, double inv, int, int) {
+          zl[o] = (bl[o] + four(zl + o, S)) * inv;
         });
-      });
-      __syncthreads();
-      gs_colour(b, z, N, 1, c.i1[l], c.i2[l]);
-      __syncthreads();
+        __syncthreads();
+      }
     }
-    gs_colour(b, z, N, 0, c.i1[l], c.i2[l]);
-    __syncthreads();
   }
-}
+};
 
-__device__ __forceinline__ void load_mat(const CoarseArgs& c, double (&matv)[4]) {
-  const int n2 = c.nmat * c.nmat, row = threadIdx.x >> 4;
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const int col = (threadIdx.x & 15) + 16 * q;
-    matv[q] = row < n2 && col < n2 ? c.mat[row * n2 + col] : 0.0;
-  }
-}
-
-// One workgroup: bound by its barrier phases (5 a level, 64 and 32 and 16
-// points per side at N = 1024, then the matrix in 2 instead of another 16).
+// One workgroup: bound by its barrier phases (4 a level: 64, 32 and 16 points
+// per side at N = 1024, then the matrix in 2) and the instructions and LDS
+// reads between them: 9.3 us (14.4 with 5 a level, indices formed in each, and
+// two-way bank conflicts).
 __global__ __launch_bounds__(kCoarseWG) void k_coarse(CoarseArgs c, Pcg a, int k, int check) {
   __shared__ double buf[kCoarseLds];
-  double matv[4];
-  load_mat(c, matv);
+  __shared__ MatLds m;
+  const int t = threadIdx.x, N = c.N[0];
+  const Coarse<3, 2> A(c, buf, m);
+  // grid index of this thread's red points: every load in flight before the test
+  int at[2];
+  double br[2], bb[2];
+#pragma unroll
+  for (int q = 0; q < 2; ++q) {
+    const Slot& s = A.slot[0][q];
+    const int e = t + q * kCoarseWG, par = e & 1, h = e >> 1;
+    const int J = div_by(h, c.half[0]), i = h - J * ((N + 1) >> 1);
+    at[q] = (2 * J + par) * N + 2 * i + par;
+    br[q] = c.in[s.red >= 0 ? at[q] : 0];
+    bb[q] = c.in[s.blk >= 0 ? at[q] + 1 - 2 * par : 0];
+  }
   if (check ? pcg_check(a, k) : a.ist[I_DONE] != 0) return;
-  __shared__ double mb[kMatN * kMatN], mz[kMatN * kMatN];
-  const CoarseLds A{buf, c, mb, mz};
-  const int t = threadIdx.x, N = c.N[0], S = N + 2;
   for (int e = t; e < c.off[c.nlev]; e += kCoarseWG) buf[e] = 0.0;
   __syncthreads();
-  for (int j = t >> 6; j < N; j += kCoarseWG / 64) {
-    const int i = t & 63;
-    if (i < N) {
-      const int p = (j + 1) * S + i + 1;
-      const double v = c.scale * c.in[j * N + i];
-      A.b(0)[p] = v;
-      if (((i + j) & 1) == 0) A.z(0)[p] = v * inv_diag(i, j, N, c.i1[0], c.i2[0]);
+#pragma unroll
+  for (int q = 0; q < 2; ++q) {
+    const Slot& s = A.slot[0][q];
+    if (s.red >= 0) {
+      const double v = c.scale * br[q];
+      A.b(0)[s.red & 0xfffff] = v;
+      A.z(0)[s.red & 0xfffff] = v * m.inv[s.red >> 20];
     }
+    if (s.blk >= 0) A.b(0)[s.blk & 0xfffff] = c.scale * bb[q];
   }
   __syncthreads();
-  coarse_cycle(A, matv);
-  for (int j = t >> 6; j < N; j += kCoarseWG / 64) {
-    const int i = t & 63;
-    if (i < N) c.z_out[j * N + i] = A.z(0)[(j + 1) * S + i + 1];
+  A.cycle();
+#pragma unroll
+  for (int q = 0; q < 2; ++q) {
+    const Slot& s = A.slot[0][q];
+    if (s.red >= 0) c.z_out[at[q]] = A.z(0)[s.red & 0xfffff];
+    if (s.blk >= 0) c.z_out[at[q] + 1 - 2 * (t & 1)] = A.z(0)[s.blk & 0xfffff];
   }
 }
 
 // The matrix of the last levels: workgroup e runs their cycle (c.nmat = 0) on
 // the e-th unit vector and stores column e.
 __global__ __launch_bounds__(kCoarseWG) void k_matrix(CoarseArgs c, double* mat) {
-  __shared__ double buf[kCoarseLds];
-  const CoarseLds A{buf, c, buf, buf};  // (no matrix below these levels)
-  const int N = c.N[0], S = N + 2, n2 = N * N;
-  for (int e = threadIdx.x; e < kCoarseLds; e += kCoarseWG) buf[e] = 0.0;
+  __shared__ double buf[2 * (area_of(8) + area_of(4) + area_of(2) + area_of(1))];
+  __shared__ MatLds m;
+  const Coarse<4, 1> A(c, buf, m);
+  const int N = c.N[0], S = row_of(N), n2 = N * N;
+  for (int e = threadIdx.x; e < c.off[c.nlev]; e += kCoarseWG) buf[e] = 0.0;
   __syncthreads();
   if (threadIdx.x == 0) {
     const int i = blockIdx.x % N, j = blockIdx.x / N, p = (j + 1) * S + i + 1;
     A.b(0)[p] = 1.0;
-    if (((i + j) & 1) == 0) A.z(0)[p] = inv_diag(i, j, N, c.i1[0], c.i2[0]);
+    if (((i + j) & 1) == 0) A.z(0)[p] = m.inv[(i == N - 1) + (j == N - 1)];
   }
   __syncthreads();
-  const double none[4] = {0.0, 0.0, 0.0, 0.0};
-  coarse_cycle(A, none);
+  A.cycle();
   for (int r = threadIdx.x; r < n2; r += kCoarseWG)
     mat[(size_t)r * n2 + blockIdx.x] = A.z(0)[(r / N + 1) * S + r % N + 1];
 }
@@ -598,7 +722,7 @@ __global__ __launch_bounds__(kBX) void k_dir(const double* z, const double* p_pr
       zv[u] = z[p < 0 ? 0 : p];
       pv[u] = first ? 0.0 : p_prev[p < 0 ? 0 : p];
     }
-    if (t == (int)blockIdx.x && !first) beta = sum_parts(a.p_rho, a.np_fine) / a.sc[S_RHO_PREV];
+    if (t == (int)blockIdx.x && !first) beta = sum_parts<1>(a.p_rho, a.np_fine) / a.sc[S_RHO_PREV];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const int e = threadIdx.x + u * kBX;
@@ -629,112 +753,115 @@ __global__ __launch_bounds__(kBX) void k_dir(const double* z, const double* p_pr
 
 constexpr int kSmallN = 96;  // its z and the levels below it fill the LDS (131 KB)
 
-// The PCG solve of an N x N grid, N <= 96: r, p and A p of a thread's points in
-// registers, z (and p, for q = A p) of the fine grid and every coarser level in
-// LDS, the last levels the matrix.  One launch instead of 4 an iteration (and
-// none enqueued past the end); bound by its barriers, about 30 an iteration.
-// A thread takes the points `t % W` of each colour of the rows t / W, t / W +
-// 1024 / W, ...: W = 32 and two rows up to 64 points per side, W = 64 and six
-// rows up to 96.  A solve (launches / this): N = 16 195 / 77 us, 31 (56
-// iterations) 957 / 264, 64 300 / 161, 96 331 / 302.
-template <int W, int RP>
+// The PCG solve of an N x N grid, N <= 96: r, p and A p of a thread's RP slots
+// in registers, z (and p, for q = A p) of the fine grid and every coarser level
+// in LDS, the last levels the matrix.  One launch instead of 4 an iteration (and
+// none enqueued past the end).  Bound by its 20 to 30 barriers an iteration and
+// by the instructions between them, 16 cycles each on the four SIMDs with all 16
+// waves: so points are enumerated without gaps, and a slot's word is kept.  A
+// solve (launches per level / this): N = 16 195 / 60 us, 31 (56 iterations) 957
+// / 166, 64 300 / 104, 96 331 / 191 (161 and 302 with rows of 32 and 64 lanes,
+// the reds corrected in a phase of their own and every second double read).
+// More than two slots a thread: x in global memory and A p formed twice, which
+// frees 20 to 40 registers (96 points: 215 us with A p kept and spills).
+template <int RP>
 __global__ __launch_bounds__(kCoarseWG) void k_solve_small(int problem, double lambda,
                                                            const double* b, const double* u,
-                                                           double* xo, int N, int coarse,
+                                                           double* xo, int N, unsigned half,
                                                            CoarseArgs c, Pcg a) {
-  extern __shared__ double z0[];  // (N + 2)^2, bordered; then the coarser levels
-  __shared__ double mb[kMatN * kMatN], mz[kMatN * kMatN], lds[16];
-  const int t = threadIdx.x, S = N + 2, Nc = N / 2;
-  const CoarseLds A{z0 + S * S, c, mb, mz};
-  double matv[4];
-  load_mat(c, matv);
+  extern __shared__ double z0[];  // bordered; then the coarser levels
+  __shared__ MatLds m;
+  __shared__ double lds[3][16];
+  constexpr bool XREG = RP <= 2;  // x in registers (with more slots they would spill)
+  const int t = threadIdx.x, S = row_of(N), par = t & 1, side = 1 - 2 * par;
+  const bool coarse = c.nlev + c.nmat > 0;
+  const Coarse<3, 2> A(c, z0 + area_of(N), m);
   const double h = 1.0 / (double)(N + 1), H2 = h * h, ih2 = 1.0 / H2;
-  double r[2][RP], p[2][RP], v[2][RP];
-  // body(i, j, offset in z0, r, p, A p) over this thread's points of one colour
-  // (indices are formed anew in each phase: kept for all of them, a dozen
-  // points' worth would push r, p and A p out of the registers)
+  double r[2][RP], p[2][RP], v[2][XREG ? RP : 1], x[2][XREG ? RP : 1];
+  // offset of the red point, black is `side` next to it; bit 16: there is a red
+  // point, 17: a black one, 18: the black one on the last row or column
+  int word[RP];
+#pragma unroll
+  for (int q = 0; q < RP; ++q) {
+    const Slot s = slot_of(t + q * kCoarseWG, N, half);
+    const int o = s.red >= 0 ? s.red & 0xfffff : (s.blk & 0xfffff) - side;
+    word[q] = (s.red < 0 && s.blk < 0 ? 0 : o) | (s.red >= 0) << 16 | (s.blk >= 0) << 17 |
+              (s.blk >= 1 << 20) << 18;
+  }
+  // body(slot, offset, r, p, A p) over this thread's points of one colour
   auto points = [&](int col, auto&& body) {
-    int own = t;
-    asm volatile("" : "+v"(own));
 #pragma unroll
     for (int q = 0; q < RP; ++q) {
-      const int j = own / W + q * (kCoarseWG / W), i = 2 * (own % W) + ((j + col) & 1);
-      if (i < N && j < N) body(i, j, (j + 1) * S + i + 1, r[col][q], p[col][q], v[col][q]);
+      int w = word[q];
+      fresh(w);
+      if (w >> (16 + col) & 1) body(q, (w & 0xffff) + col * side, r[col][q], p[col][q], v[col][XREG ? q : 0]);
     }
   };
-  auto nb = [&](int o) { return ((z0[o - 1] + z0[o + 1]) + z0[o - S]) + z0[o + S]; };
-  for (int e = t; e < S * S + c.off[c.nlev]; e += kCoarseWG) z0[e] = 0.0;
-  __syncthreads();
-#pragma unroll 1
-  for (int e = t; e < N * N; e += kCoarseWG)
-    z0[(e / N + 1) * S + e % N + 1] = rhs_at(problem, lambda, b, u[e], e);
-  __syncthreads();
+  // grid index of a point
+  auto grid = [&](int col, int q) {
+    int e = t + q * kCoarseWG;
+    fresh(e);
+    const int J = div_by(e >> 1, half), i = (e >> 1) - J * ((N + 1) >> 1);
+    return (2 * J + par) * N + 2 * i + (col ? 1 - par : par);
+  };
+  for (int e = t; e < area_of(N) + c.off[c.nlev]; e += kCoarseWG) z0[e] = 0.0;
   double rr = 0.0;
 #pragma unroll
   for (int col = 0; col < 2; ++col)
-    points(col, [&](int, int, int o, double& rv, double& pv, double&) {
-      rv = z0[o];
+    points(col, [&](int q, int, double& rv, double& pv, double&) {
+      const int g = grid(col, q);
+      rv = rhs_at(problem, lambda, b, u[g], g);
       pv = 0.0;
       rr = fma(rv, rv, rr);
+      if (XREG) x[col][XREG ? q : 0] = 0.0;
     });
-  rr = block_sum(rr, lds);
+  rr = block_sum(rr, lds[0]);
   const double rr0 = rr;
   double rho_prev = 0.0;
   const int last = a.fixed >= 0 ? a.fixed : a.max_iter;
   int k = 0;
   while (k < last && (a.fixed >= 0 || !(rr <= a.tol2 * rr0))) {
     // the cycle: every diagonal entry of the fine grid is 4
-    points(0, [&](int, int, int o, double& rv, double&, double&) { z0[o] = H2 * rv * 0.25; });
+    points(0, [&](int, int o, double& rv, double&, double&) { z0[o] = H2 * rv * 0.25; });
     __syncthreads();
-    points(1, [&](int, int, int o, double& rv, double&, double&) {
-      z0[o] = (H2 * rv + nb(o)) * 0.25;
+    points(1, [&](int, int o, double& rv, double&, double&) {
+      z0[o] = (H2 * rv + four(z0 + o, S)) * 0.25;
     });
     __syncthreads();
     if (coarse) {
-      for (int J = t / W; J < Nc; J += kCoarseWG / W) {
-        const int I = t % W;
-        if (I < Nc) {
-          const double v = restrict_red(z0 + (2 * J + 2) * S + 2 * I + 2, S, 2 * I + 1, 2 * J + 1, N);
-          if (c.nlev == 0) {
-            mb[J * Nc + I] = v;
-          } else {
-            const int o = (J + 1) * (Nc + 2) + I + 1;
-            A.b(0)[o] = v;
-            if (((I + J) & 1) == 0) A.z(0)[o] = v * inv_diag(I, J, Nc, c.i1[0], c.i2[0]);
-          }
+      A.restrict_to(0, z0, N);
+      __syncthreads();
+      A.cycle();
+      const double* zc = c.nlev ? A.z(0) : m.out;
+      const int Sc = row_of(N >> 1);
+#pragma unroll
+      for (int q = 0; q < RP; ++q) {
+        int w = word[q], e = t + q * kCoarseWG;
+        fresh(w);
+        fresh(e);
+        if (w >> 17 & 1) {
+          const int o = (w & 0xffff) + side, J = div_by(e >> 1, half);
+          const int cc = (J + 1) * Sc + (e >> 1) - J * ((N + 1) >> 1) + 1;
+          z0[o] = (H2 * r[1][q] +
+                   (four(z0 + o, S) + interp_around(zc + cc, Sc, par, w >> 18 & 1))) * 0.25;
         }
       }
       __syncthreads();
-      coarse_cycle(A, matv);
-      const double* zc = A.z(0);
-      points(0, [&](int i, int j, int o, double&, double&, double&) {
-        z0[o] += interp_red(i, j, [&](int I, int J) {
-          return c.nlev == 0 ? (I >= 0 && J >= 0 ? mz[J * Nc + I] : 0.0)
-                             : zc[(J + 1) * (Nc + 2) + I + 1];
-        });
-      });
-      __syncthreads();
-      points(1, [&](int, int, int o, double& rv, double&, double&) {
-        z0[o] = (H2 * rv + nb(o)) * 0.25;
-      });
-      __syncthreads();
     }
-    points(0, [&](int, int, int o, double& rv, double&, double&) {
-      z0[o] = (H2 * rv + nb(o)) * 0.25;
+    points(0, [&](int, int o, double& rv, double&, double&) {
+      z0[o] = (H2 * rv + four(z0 + o, S)) * 0.25;
     });
     // each thread reads back its own points only
     double acc = 0.0;
 #pragma unroll
     for (int col = 0; col < 2; ++col)
-      points(col, [&](int, int, int o, double& rv, double&, double&) {
-        acc = fma(rv, z0[o], acc);
-      });
-    const double rho = block_sum(acc, lds);
+      points(col, [&](int, int o, double& rv, double&, double&) { acc = fma(rv, z0[o], acc); });
+    const double rho = block_sum(acc, lds[1]);
     const double beta = k == 0 ? 0.0 : rho / rho_prev;
     rho_prev = rho;
 #pragma unroll
     for (int col = 0; col < 2; ++col)
-      points(col, [&](int, int, int o, double&, double& pv, double&) {
+      points(col, [&](int, int o, double&, double& pv, double&) {
         pv = fma(beta, pv, z0[o]);
         z0[o] = pv;  // p, for q = A p (z is not needed any more)
       });
@@ -742,25 +869,35 @@ __global__ __launch_bounds__(kCoarseWG) void k_solve_small(int problem, double l
     acc = 0.0;
 #pragma unroll
     for (int col = 0; col < 2; ++col)
-      points(col, [&](int, int, int o, double&, double& pv, double& q) {
-        q = (4.0 * pv - nb(o)) * ih2;
+      points(col, [&](int, int o, double&, double& pv, double& q) {
+        q = (4.0 * pv - four(z0 + o, S)) * ih2;
         acc = fma(pv, q, acc);
       });
-    const double alpha = rho / block_sum(acc, lds);
+    const double alpha = rho / block_sum(acc, lds[2]);
     acc = 0.0;
 #pragma unroll
     for (int col = 0; col < 2; ++col)
-      points(col, [&](int i, int j, int, double& rv, double& pv, double& q) {
-        double* xp = xo + j * N + i;
-        *xp = fma(alpha, pv, k == 0 ? 0.0 : *xp);
-        rv = fma(-alpha, q, rv);
+      points(col, [&](int q, int o, double& rv, double& pv, double& qv) {
+        if (XREG) {
+          double& xv = x[col][XREG ? q : 0];
+          xv = fma(alpha, pv, xv);
+        } else {
+          double* xp = xo + grid(col, q);
+          *xp = fma(alpha, pv, k == 0 ? 0.0 : *xp);
+        }
+        rv = fma(-alpha, XREG ? qv : (4.0 * pv - four(z0 + o, S)) * ih2, rv);
         acc = fma(rv, rv, acc);
       });
-    rr = block_sum(acc, lds);
+    rr = block_sum(acc, lds[0]);
     ++k;
   }
-  if (k == 0)
-    for (int e = t; e < N * N; e += kCoarseWG) xo[e] = 0.0;
+  if (XREG || k == 0) {
+#pragma unroll
+    for (int col = 0; col < 2; ++col)
+      points(col, [&](int q, int, double&, double&, double&) {
+        xo[grid(col, q)] = XREG ? x[col][XREG ? q : 0] : 0.0;
+      });
+  }
   if (t == 0) {
     a.ist[I_DONE] = 1;
     a.ist[I_ITERS] = k;
@@ -897,11 +1034,16 @@ CoarseArgs coarse_args(const aa_pde2d* c, int from, int to, int nmat) {
   ca.scale = 1.0;
   ca.nlev = to - from;
   for (int l = from; l < to; ++l) {
-    ca.N[l - from] = c->lev[l].N;
-    ca.i1[l - from] = c->lev[l].i1;
-    ca.i2[l - from] = c->lev[l].i2;
-    ca.off[l - from + 1] = ca.off[l - from] + 2 * (c->lev[l].N + 2) * (c->lev[l].N + 2);
+    const int n = c->lev[l].N, q = l - from;
+    ca.N[q] = n;
+    ca.inv[q][0] = 0.25;
+    ca.inv[q][1] = c->lev[l].i1;
+    ca.inv[q][2] = c->lev[l].i2;
+    ca.half[q] = div_small((n + 1) / 2);
+    ca.full[q] = div_small(n);
+    ca.off[q + 1] = ca.off[q] + 2 * area_of(n);
   }
+  if (nmat) ca.full_mat = div_small(nmat);
   ca.nmat = nmat;
   ca.mat = c->mat;
   return ca;
@@ -983,13 +1125,21 @@ hipError_t launch_small(const aa_pde2d* c, const Pcg& a, int problem, const doub
   const int to = c->first_mat;  // levels 1 .. to-1 in LDS, then the matrix
   const CoarseArgs ca = coarse_args(c, coarse, coarse ? to : 0,
                                     coarse && to < c->nlev ? c->lev[to].N : 0);
-  const size_t lds = sizeof(double) * (size_t)((N + 2) * (N + 2) + ca.off[ca.nlev]);
-  if (N <= 64)
-    hipLaunchKernelGGL((k_solve_small<32, 2>), dim3(1), dim3(kCoarseWG), lds, c->st, problem,
-                       c->lambda, b, u, x, N, coarse, ca, a);
+  const size_t lds = sizeof(double) * (size_t)(area_of(N) + ca.off[ca.nlev]);
+  const int slots = 2 * ((N + 1) / 2) * ((N + 1) / 2);
+  const unsigned half = div_small((N + 1) / 2);
+  auto go = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3(1), dim3(kCoarseWG), lds, c->st, problem, c->lambda, b, u, x, N,
+                       half, ca, a);
+  };
+  if (slots <= kCoarseWG)
+    go(k_solve_small<1>);
+  else if (slots <= 2 * kCoarseWG)
+    go(k_solve_small<2>);
+  else if (slots <= 3 * kCoarseWG)
+    go(k_solve_small<3>);
   else
-    hipLaunchKernelGGL((k_solve_small<64, 6>), dim3(1), dim3(kCoarseWG), lds, c->st, problem,
-                       c->lambda, b, u, x, N, coarse, ca, a);
+    go(k_solve_small<5>);
   return hipGetLastError();
 }
 

@@ -40,3 +40,20 @@ def test_solve_at_tile_edges(N):
         ctx.solve(to_dev(rhs), x)
         assert ctx.last() == (iters, True) and conv
         assert rel_inf(x.cpu().numpy(), ref.reshape(-1)) <= 1e-11
+
+
+@pytest.mark.parametrize("N", [1, 2, 9, 32, 44, 46, 64, 68, 76, 80, 92, 96, 100])
+def test_solve_at_the_slot_counts_of_one_workgroup(N):
+    """One, two, three and five points of each colour a thread, the levels below
+    down to the matrix or an odd last one, and the first size with its own
+    launches; tolerances of the solves above."""
+    import torch
+    device()
+    from paper_2110_09667_amd import aa
+    rhs = W.normal(N, 5, N * N)
+    ctx = aa.PDE2D(N, aa.PDE_BRATU)
+    x = torch.full((N * N,), np.nan, dtype=torch.float64, device="cuda")
+    ref, iters, conv = P.pcg(rhs.reshape(N, N), 1.0 / (N + 1), 1e-10, 200)[:3]
+    ctx.solve(to_dev(rhs), x)
+    assert ctx.last() == (iters, True) and conv
+    assert rel_inf(x.cpu().numpy(), ref.reshape(-1)) <= 1e-11
