@@ -89,73 +89,65 @@ __device__ __forceinline__ double inv_diag(int i, int j, int N, double i1, doubl
   return x ? (y ? i2 : i1) : (y ? i1 : 0.25);
 }
 
-// bilinear interpolation at a red point (i + j even): a coarse point itself
-// (both odd), or the mean of four (both even; index -1 is the boundary).
-// at(I, J) returns the coarse value.
-template <class At>
-__device__ __forceinline__ double interp_red(int i, int j, At&& at) {
-  const int I = i >> 1, J = j >> 1;
-  if (i & 1) return at(I, J);
-  return 0.25 * ((at(I - 1, J - 1) + at(I, J - 1)) + (at(I - 1, J) + at(I, J)));
-}
-
-// scaled right-hand side of coarse point (I, J) from the pre-smoothed black
-// values e around fine point (2 I + 1, 2 J + 1) of an N x N grid: its own
-// residual plus a quarter of its four corners' (a corner outside the grid has
-// none), each the sum of four black values.  e points at that fine point, with
-// row stride S; values one point outside the grid are zero, further out none
-// is read.
-__device__ __forceinline__ double restrict_red(const double* e, int S, int ic, int jc, int N) {
-  const double wx = ic + 1 < N ? 1.5 : 1.25;  // of (ic, jc +- 1)
-  const double wy = jc + 1 < N ? 1.5 : 1.25;  // of (ic +- 1, jc)
-  const double in = wx * (e[-S] + e[S]) + wy * (e[-1] + e[1]);
-  double out = (e[-S - 2] + e[S - 2]) + (e[-2 * S - 1] + e[-2 * S + 1]);
-  if (ic + 1 < N) out += e[-S + 2] + e[S + 2];
-  if (jc + 1 < N) out += e[2 * S - 1] + e[2 * S + 1];
-  return in + 0.25 * out;
-}
-
 // --------------------------------------------------------------------------
 // reductions: each workgroup stores its sum; the consumers add the partials
 // in index order (per thread, then the fixed tree of block_sum)
 // --------------------------------------------------------------------------
 
-// the sum over the workgroup (4 or 16 waves), in every lane.  lds: 16 doubles
-// that nobody reads any more.
+// the sum over the workgroup (NT threads, 4 or 16 waves), in every lane.  lds:
+// 16 doubles that nobody reads any more.
+template <int NT>
 __device__ __forceinline__ double block_sum(double v, double* lds) {
   v = wave_sum(v);
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const bool four = blockDim.x == kBX;
   if (lane == 0) lds[w] = v;
   __syncthreads();
-  v = lds[lane & (four ? 3 : 15)];
-  if (!four) v = add_xor<4>(add_xor<8>(v));
+  v = lds[lane & (NT / 64 - 1)];
+  if constexpr (NT == 1024) v = add_xor<4>(add_xor<8>(v));
   return add_xor<1>(add_xor<2>(v));
 }
 
 // this workgroup's sum of v, stored as its partial
 __device__ void partial_store(double v, double* parts) {
   __shared__ double lds[16];
-  const double s = block_sum(v, lds);
+  const double s = block_sum<kBX>(v, lds);
   if (threadIdx.x == 0) parts[blockIdx.x] = s;
 }
 
-// the sum of np partials, in one fixed order (every workgroup gets the same);
-// a kernel's sums have a SLOT each
-template <int SLOT>
-__device__ double sum_parts(const double* parts, int np) {
-  __shared__ double lds[16];
-  double acc = 0.0;
-  for (int k = threadIdx.x; k < np; k += blockDim.x) acc += parts[k];
-  return block_sum(acc, lds);
-}
+// The sum of np <= kMaxWG partials, in one fixed order (every workgroup gets the
+// same): all of a thread's loads in flight at once, and before the kernel's
+// other loads where their consumer comes last (one load and wait a turn, four
+// turns a sum: 15.6 us in k_down at N = 1024, now 13.5).  A kernel's
+// sums have a SLOT each.
+template <int NT>
+struct Parts {
+  double v[kMaxWG / NT];
+  __device__ __forceinline__ Parts(const double* parts, int np) {
+#pragma unroll
+    for (int q = 0; q < kMaxWG / NT; ++q) {
+      const int e = threadIdx.x + q * NT;
+      const double w = parts[e < np ? e : 0];
+      v[q] = e < np ? w : 0.0;
+    }
+  }
+  template <int SLOT>
+  __device__ __forceinline__ double sum() const {
+    __shared__ double lds[16];
+    double acc = 0.0;
+#pragma unroll
+    for (int q = 0; q < kMaxWG / NT; ++q) acc += v[q];
+    return block_sum<NT>(acc, lds);
+  }
+};
 
 // The stopping test before iteration k (every workgroup decides alike; the
 // first records it, and at k = 0 keeps r.r of the right-hand side).  Returns
 // true when the solve has ended.
+template <int NT>
 __device__ __forceinline__ bool pcg_check(const Pcg& a, int k) {
+  const Parts<NT> parts(a.p_rr, a.np_fine);
   if (a.ist[I_DONE]) return true;
-  const double rr = sum_parts<0>(a.p_rr, a.np_fine);
+  const double rr = parts.template sum<0>();
   const double rr0 = k == 0 ? rr : a.sc[S_RR0];
   if (k == 0 && blockIdx.x == 0 && threadIdx.x == 0) a.sc[S_RR0] = rr;
   bool stop;
@@ -179,10 +171,12 @@ __device__ __forceinline__ bool pcg_check(const Pcg& a, int k) {
 // grid-wide level kernels: one tile per workgroup and turn
 // --------------------------------------------------------------------------
 
-// Tiles of TX x TY fine points: 64 x 16 from 1024 points per side, where that
-// fills the chip's 1024 resident workgroups in one turn; 32 x 8 below (at 512
-// points 64 x 16 took 6.3 us down and 5.4 us up, 32 x 8 5.7 and 4.2 us).
-constexpr int kTileBig = 1024;
+// Tiles of TX x TY fine points.  32 x 8 up to 512 points per side, where they
+// are at most 1024, one turn of the workgroups the chip holds at once; 64 x 16
+// above (at 512 and 448 points both take the same time, at 256 a solve of 10
+// iterations takes 336 us with the small ones, 362 with the large; at 544 of 24
+// iterations 1244 and 1065, at 640 of 11 655 and 565).
+constexpr int kTileBig = 513;
 __host__ __device__ constexpr int tiles_of(int N, int T) { return (N + T - 1) / T; }
 
 // The PCG update that precedes a cycle on the fine grid: alpha = rho / p.q,
@@ -196,95 +190,144 @@ struct DownFine {
   double* x;
 };
 
-// Grid index of this thread's u-th point of a W x H tile whose first point is
-// (i, j), or -1 past the tile or outside the N x N grid.
-template <int W, int H>
-__device__ __forceinline__ int64_t tile_at(int u, int i, int j, int N) {
-  const int e = threadIdx.x + u * kBX;
-  i += e % W;
-  j += e / W;
-  return e < W * H && i >= 0 && j >= 0 && i < N && j < N ? (int64_t)j * N + i : -1;
+// A thread's points are pairs of neighbours (2 i, 2 i + 1) in a row, one red and
+// one black: 16-byte loads, half the indices, and the two colours lie in LDS
+// arrays of their own that every lane reads at a stride of one.  (Levels that
+// have a next one have an even number of points per side, and their arrays are
+// aligned to 256 bytes; only x is the caller's and read 8 bytes at a time.)
+// In row y of a tile the red point is the pair's second one when y is odd (a
+// tile starts two rows above an even row).
+//
+// Pair of this thread in turn u of a tile W2 pairs wide and H rows high whose
+// first point is (i, j).
+template <int W2, int H>
+struct Pair {
+  int y, s, i, j;
+  bool in;  // in the tile and in the grid
+  __device__ __forceinline__ Pair(int u, int i0, int j0, int N) {
+    const int e = threadIdx.x + u * kBX;
+    y = e / W2;
+    s = e - y * W2;
+    i = i0 + 2 * s;
+    j = j0 + y;
+    in = e < W2 * H && i >= 0 && j >= 0 && i < N && j < N;
+  }
+  __device__ __forceinline__ int64_t at(int N) const { return in ? (int64_t)j * N + i : 0; }
+};
+
+__device__ __forceinline__ double2 ld_pair(const double* p) {
+  return *reinterpret_cast<const double2*>(p);
+}
+__device__ __forceinline__ void st_pair(double* p, double x, double y) {
+  *reinterpret_cast<double2*>(p) = make_double2(x, y);
 }
 
 enum : int { DOWN_LEVEL = 0, DOWN_FIRST = 1, DOWN_UPDATE = 2 };
 
 // Pre-smoothing from zero (red, black) and restriction of one level: reads b
-// (level 0: r), writes the next level's b.  Bound by latency: one read of a
-// tile with a halo of two points, every load issued before the first use, two
-// LDS phases.  At N = 1024 the fine level with the update takes 17 us, the
-// levels of 512 to 128 points 3.6 to 5.7 us each; with separate kernels for the
-// update, the smoothing and the restriction they took 13 + 8 + 9 and 9 to 14.
+// (level 0: r), writes the next level's b.  Bound by latency and by the index
+// arithmetic (16 cycles an instruction with a CU's 16 waves): one read of a tile
+// with a halo of two points, every load issued before the first use, two LDS
+// phases.  At N = 1024 the fine level with the update takes 13.5 us, the
+// levels of 512 to 128 points 3.5 us each (one point a lane and turn, stride-two
+// reads: 15.8 and 4.2; separate kernels for the update, the smoothing and the
+// restriction: 13 + 8 + 9 and 9 to 14).
 template <int TX, int TY, int MODE>
 __global__ __launch_bounds__(kBX) void k_down(Lev L, Lev C, DownFine f, Pcg a, int k, int check) {
-  constexpr int W = TX + 5, H = TY + 5;  // points 2 I0 - 2 .. 2 I0 + TX + 2
-  constexpr int U = (H * W + kBX - 1) / kBX, V = TX * TY / kBX;
-  __shared__ double sb[H * W], se[H * W];
-  if (check ? pcg_check(a, k) : a.ist[I_DONE] != 0) return;
+  constexpr int W2 = TX / 2 + 3, H = TY + 5;  // from (i0 - 2, j0 - 2)
+  constexpr int U = (H * W2 + kBX - 1) / kBX;
+  __shared__ double sr[H * W2], sk[H * W2];
+  if (check ? pcg_check<kBX>(a, k) : a.ist[I_DONE] != 0) return;
   const int N = L.N, tx = tiles_of(N, TX), nt = tx * tiles_of(N, TY);
   const double* src = MODE == DOWN_LEVEL ? L.b : f.r_in;
   double acc = 0.0, alpha = 0.0;
+  const Parts<kBX> prho(a.p_rho, MODE == DOWN_UPDATE ? a.np_fine : 0);
+  const Parts<kBX> ppq(a.p_pq, MODE == DOWN_UPDATE ? a.np_fine : 0);
   for (int t = blockIdx.x; t < nt; t += gridDim.x) {
     const int i0 = t % tx * TX, j0 = t / tx * TY;
+    auto pair = [&](int u) { return Pair<W2, H>(u, i0 - 2, j0 - 2, N); };
+    auto inner = [&](const Pair<W2, H>& g) {
+      return g.in && g.s >= 1 && g.s <= TX / 2 && g.y >= 2 && g.y < TY + 2;
+    };
     // every load of the tile in flight at once, before the scalars they meet
-    double b[U], qv[U], xv[V], pv[V];
+    double2 b[U], qv[U], pv[U];
+    double x0[U], x1[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const int64_t p = tile_at<W, H>(u, i0 - 2, j0 - 2, N);
-      b[u] = src[p < 0 ? 0 : p];
-      if (MODE == DOWN_UPDATE) qv[u] = f.q[p < 0 ? 0 : p];
+      const auto g = pair(u);
+      const int64_t p = g.at(N);
+      b[u] = ld_pair(src + p);
+      if (MODE == DOWN_UPDATE) {
+        const int64_t o = inner(g) ? p : 0;
+        qv[u] = ld_pair(f.q + p);
+        pv[u] = ld_pair(f.p + o);
+        x0[u] = f.x[o];
+        x1[u] = f.x[o + 1];
+      }
     }
     if (MODE == DOWN_UPDATE) {
-#pragma unroll
-      for (int v = 0; v < V; ++v) {
-        const int64_t p = tile_at<TX, TY>(v, i0, j0, N);
-        xv[v] = f.x[p < 0 ? 0 : p];
-        pv[v] = f.p[p < 0 ? 0 : p];
-      }
       if (t == (int)blockIdx.x) {
-        const double rho = sum_parts<1>(a.p_rho, a.np_fine);
-        alpha = rho / sum_parts<2>(a.p_pq, a.np_fine);
+        const double rho = prho.template sum<1>();
+        alpha = rho / ppq.template sum<2>();
         // rho for the next iteration's beta (k_dir read the previous one already)
         if (blockIdx.x == 0 && threadIdx.x == 0) a.sc[S_RHO_PREV] = rho;
       }
-#pragma unroll
-      for (int v = 0; v < V; ++v) {
-        const int64_t p = tile_at<TX, TY>(v, i0, j0, N);
-        if (p >= 0) f.x[p] = fma(alpha, pv[v], xv[v]);
-      }
     }
+    double red[U], blk[U];  // the red e and the black b
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const int e = threadIdx.x + u * kBX, y = e / W, x = e % W, i = i0 + x - 2, j = j0 + y - 2;
-      const int64_t p = tile_at<W, H>(u, i0 - 2, j0 - 2, N);
-      double v = p >= 0 ? b[u] : 0.0;
-      if (MODE == DOWN_UPDATE && p >= 0) {
-        v = fma(-alpha, qv[u], v);
-        if (x >= 2 && y >= 2 && x < TX + 2 && y < TY + 2) {
-          f.r_out[p] = v;
-          acc = fma(v, v, acc);
+      const auto g = pair(u);
+      double2 v = b[u];
+      if (MODE == DOWN_UPDATE) {
+        v.x = fma(-alpha, qv[u].x, v.x);
+        v.y = fma(-alpha, qv[u].y, v.y);
+        if (inner(g)) {
+          const int64_t p = g.at(N);
+          f.x[p] = fma(alpha, pv[u].x, x0[u]);
+          f.x[p + 1] = fma(alpha, pv[u].y, x1[u]);
+          st_pair(f.r_out + p, v.x, v.y);
+          acc = fma(v.x, v.x, acc);
+          acc = fma(v.y, v.y, acc);
         }
       }
-      if (MODE != DOWN_LEVEL) v *= L.H2;
-      if (e < H * W) {
-        sb[e] = v;
-        se[e] = ((i + j) & 1) == 0 ? v * inv_diag(i, j, N, L.i1, L.i2) : 0.0;
+      if (MODE != DOWN_LEVEL) {
+        v.x *= L.H2;
+        v.y *= L.H2;
       }
+      const int odd = g.y & 1;
+      blk[u] = odd ? v.x : v.y;
+      red[u] = g.in ? (odd ? v.y : v.x) * inv_diag(g.i + odd, g.j, N, L.i1, L.i2) : 0.0;
+      const int e = threadIdx.x + u * kBX;
+      if (e < H * W2) sr[e] = red[u];
     }
     __syncthreads();
-    for (int e = threadIdx.x; e < (H - 2) * (W / 2); e += kBX) {
-      const int y = 1 + e / (W / 2), s = e % (W / 2);
-      const int x = 1 + 2 * s + (y & 1);  // i + j odd (i0, j0 even)
-      const int i = i0 + x - 2, j = j0 + y - 2, c = y * W + x;
-      if (x < W - 1 && i >= 0 && j >= 0 && i < N && j < N)
-        se[c] = (sb[c] + (((se[c - 1] + se[c + 1]) + se[c - W]) + se[c + W])) *
-                inv_diag(i, j, N, L.i1, L.i2);
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const auto g = pair(u);
+      const int e = threadIdx.x + u * kBX, odd = g.y & 1;
+      // (the first and last row, and a neighbour past either end of a row, are
+      // of no black point that the restriction reads)
+      if (g.y >= 1 && g.y <= H - 2)
+        sk[e] = g.in ? (blk[u] + (((red[u] + sr[odd ? e - 1 : e + 1]) + sr[e - W2]) + sr[e + W2])) *
+                           inv_diag(g.i + 1 - odd, g.j, N, L.i1, L.i2)
+                     : 0.0;
     }
     __syncthreads();
-    for (int e = threadIdx.x; e < TX / 2 * (TY / 2); e += kBX) {
-      const int Y = e / (TX / 2), X = e % (TX / 2), I = (i0 >> 1) + X, J = (j0 >> 1) + Y;
-      if (I < C.N && J < C.N)
-        C.b[(int64_t)J * C.N + I] =
-            restrict_red(se + (2 * Y + 3) * W + 2 * X + 3, W, 2 * I + 1, 2 * J + 1, N);
+    // full weighting: a red point's residual is the sum of its four black
+    // values; a coarse point takes its own and a quarter of its four corners'
+    // (points outside the grid are zero, and their residuals have no part)
+    if (threadIdx.x < TX / 2 * (TY / 2)) {
+      const int Y = threadIdx.x / (TX / 2), X = threadIdx.x % (TX / 2);
+      const int I = (i0 >> 1) + X, J = (j0 >> 1) + Y;
+      if (I < C.N && J < C.N) {
+        const double* m = sk + (2 * Y + 3) * W2 + X + 1;  // row 2 J + 1
+        const double wx = I + 1 < C.N ? 1.5 : 1.25, wy = J + 1 < C.N ? 1.5 : 1.25;
+        const double in = wx * (m[-W2] + m[W2]) + wy * (m[0] + m[1]);
+        double out = (m[-W2 - 1] + m[W2 - 1]) + (m[-2 * W2] + m[-2 * W2 + 1]);
+        out += m[-W2 + 1] + m[W2 + 1];
+        if (J + 1 < C.N) out += m[2 * W2] + m[2 * W2 + 1];
+        C.b[(int64_t)J * C.N + I] = in + 0.25 * out;
+      }
     }
     __syncthreads();
   }
@@ -293,74 +336,82 @@ __global__ __launch_bounds__(kBX) void k_down(Lev L, Lev C, DownFine f, Pcg a, i
 
 // Correction from the coarse level (ec, Nc per side) and post-smoothing (black,
 // red) of one level; on the fine grid b = H^2 r and rho = r.z is formed.
-// Four LDS phases on a tile with a halo of two points: 10 us on the fine grid at
-// N = 1024, 3.6 to 4.2 us on the levels of 512 to 128 points (two half-sweep
-// kernels: 8 + 12 and 9 to 13).
+// Three LDS phases on a tile with a halo of two points: 7.5 us on the fine grid
+// at N = 1024, 3.3 us on the levels of 512 to 128 points (one point a lane and
+// turn: 9.4 and 3.7; two half-sweep kernels: 8 + 12 and 9 to 13).
 template <int TX, int TY, bool FINE>
 __global__ __launch_bounds__(kBX) void k_up(Lev L, const double* r, const double* ec, int Nc,
                                             Pcg a, int dot) {
-  constexpr int W = TX + 4, H = TY + 4;
+  constexpr int W2 = TX / 2 + 2, H = TY + 4;       // from (i0 - 2, j0 - 2)
   constexpr int WC = TX / 2 + 3, HC = TY / 2 + 3;  // coarse points i0 / 2 - 2 ..
-  constexpr int U = (H * W + kBX - 1) / kBX, UC = (HC * WC + kBX - 1) / kBX;
-  __shared__ double sb[H * W], sz[H * W], sc[HC * WC];
+  constexpr int U = (H * W2 + kBX - 1) / kBX, UC = (HC * WC + kBX - 1) / kBX;
+  __shared__ double sr[H * W2], sk[H * W2], sc[HC * WC];
   if (a.ist[I_DONE]) return;
   const int N = L.N, tx = tiles_of(N, TX), nt = tx * tiles_of(N, TY);
   const double* src = FINE ? r : L.b;
   double acc = 0.0;
   for (int t = blockIdx.x; t < nt; t += gridDim.x) {
     const int i0 = t % tx * TX, j0 = t / tx * TY;
-    double b[U], cv[UC];
-#pragma unroll
-    for (int u = 0; u < UC; ++u) {
-      const int64_t p = tile_at<WC, HC>(u, i0 / 2 - 2, j0 / 2 - 2, Nc);
-      cv[u] = ec[p < 0 ? 0 : p];
-    }
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int64_t p = tile_at<W, H>(u, i0 - 2, j0 - 2, N);
-      b[u] = src[p < 0 ? 0 : p];
-    }
+    auto pair = [&](int u) { return Pair<W2, H>(u, i0 - 2, j0 - 2, N); };
+    double2 b[U];
+    double cv[UC];
 #pragma unroll
     for (int u = 0; u < UC; ++u) {
       const int e = threadIdx.x + u * kBX;
-      if (e < HC * WC) sc[e] = tile_at<WC, HC>(u, i0 / 2 - 2, j0 / 2 - 2, Nc) >= 0 ? cv[u] : 0.0;
+      const int I = i0 / 2 - 2 + e % WC, J = j0 / 2 - 2 + e / WC;
+      const bool in = e < HC * WC && I >= 0 && J >= 0 && I < Nc && J < Nc;
+      const double v = ec[in ? (int64_t)J * Nc + I : 0];
+      cv[u] = in ? v : 0.0;
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) b[u] = ld_pair(src + pair(u).at(N));
+#pragma unroll
+    for (int u = 0; u < UC; ++u) {
+      const int e = threadIdx.x + u * kBX;
+      if (e < HC * WC) sc[e] = cv[u];
+    }
+    __syncthreads();
+    double own[U], red[U], blk[U];  // the corrected red z, the red and the black b
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const auto g = pair(u);
+      const int e = threadIdx.x + u * kBX, odd = g.y & 1;
+      if (FINE) {
+        b[u].x *= L.H2;
+        b[u].y *= L.H2;
+      }
+      red[u] = odd ? b[u].y : b[u].x;
+      blk[u] = odd ? b[u].x : b[u].y;
+      own[u] = 0.0;
+      if (g.in) {  // a coarse point itself, or the mean of four
+        const double* q = sc + ((g.y >> 1) + 1) * WC + g.s + 1;
+        const double corr = odd ? q[0] : 0.25 * ((q[-WC - 1] + q[-WC]) + (q[-1] + q[0]));
+        own[u] = red[u] * inv_diag(g.i + odd, g.j, N, L.i1, L.i2) + corr;
+      }
+      if (e < H * W2) sr[e] = own[u];
     }
     __syncthreads();
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const int e = threadIdx.x + u * kBX, y = e / W, x = e % W, i = i0 + x - 2, j = j0 + y - 2;
-      if (e < H * W) {
-        const bool in = tile_at<W, H>(u, i0 - 2, j0 - 2, N) >= 0;
-        const double v = in ? (FINE ? L.H2 * b[u] : b[u]) : 0.0;
-        sb[e] = v;
-        // coarse point (I, J) is at sc[(J - j0 / 2 + 2) WC + I - i0 / 2 + 2]
-        sz[e] = in && ((i + j) & 1) == 0
-                    ? v * inv_diag(i, j, N, L.i1, L.i2) +
-                          interp_red(x, y, [&](int I, int J) { return sc[(J + 1) * WC + I + 1]; })
-                    : 0.0;
+      const auto g = pair(u);
+      const int e = threadIdx.x + u * kBX, odd = g.y & 1;
+      if (g.y >= 1 && g.y <= H - 2) {
+        own[u] = g.in ? (blk[u] + (((own[u] + sr[odd ? e - 1 : e + 1]) + sr[e - W2]) + sr[e + W2])) *
+                            inv_diag(g.i + 1 - odd, g.j, N, L.i1, L.i2)
+                      : 0.0;
+        sk[e] = own[u];
       }
     }
     __syncthreads();
-    for (int e = threadIdx.x; e < (H - 2) * (W / 2 - 1); e += kBX) {
-      const int y = 1 + e / (W / 2 - 1), s = e % (W / 2 - 1);
-      const int x = 1 + 2 * s + (y & 1);
-      const int i = i0 + x - 2, j = j0 + y - 2, c = y * W + x;
-      if (i >= 0 && j >= 0 && i < N && j < N)
-        sz[c] = (sb[c] + (((sz[c - 1] + sz[c + 1]) + sz[c - W]) + sz[c + W])) *
-                inv_diag(i, j, N, L.i1, L.i2);
-    }
-    __syncthreads();
 #pragma unroll
-    for (int u = 0; u < TX * TY / kBX; ++u) {
-      const int e = threadIdx.x + u * kBX;
-      const int y = e / TX, x = e % TX, i = i0 + x, j = j0 + y, c = (y + 2) * W + x + 2;
-      if (i < N && j < N) {
-        double z = sz[c];
-        if (((i + j) & 1) == 0)
-          z = (sb[c] + (((sz[c - 1] + sz[c + 1]) + sz[c - W]) + sz[c + W])) *
-              inv_diag(i, j, N, L.i1, L.i2);
-        L.z[(int64_t)j * N + i] = z;
-        if (FINE) acc = fma(sb[c], z, acc);
+    for (int u = 0; u < U; ++u) {
+      const auto g = pair(u);
+      const int e = threadIdx.x + u * kBX, odd = g.y & 1;
+      if (g.in && g.s >= 1 && g.s <= TX / 2 && g.y >= 2 && g.y < TY + 2) {
+        const double z = (red[u] + (((own[u] + sk[odd ? e + 1 : e - 1]) + sk[e - W2]) + sk[e + W2])) *
+                         inv_diag(g.i + odd, g.j, N, L.i1, L.i2);
+        st_pair(L.z + g.at(N), odd ? own[u] : z, odd ? z : own[u]);
+        if (FINE) acc = fma(red[u], z, fma(blk[u], own[u], acc));
       }
     }
     __syncthreads();
@@ -447,8 +498,10 @@ __device__ __forceinline__ double interp_around(const double* zc, int Sc, int pa
 }
 
 // Scaled right-hand sides of the next level, n points per side, from the black
-// values of one of N = 2 n (restrict_red with x and y exchanged in every second
-// row: lanes of both rows then read different banks).  put(J n + I, I, J, value)
+// values of one of N = 2 n: a coarse point's own residual (the sum of four black
+// values) and a quarter of its four corners' (a corner outside the grid has
+// none).  x and y are exchanged in every second row: lanes of both rows then
+// read different banks.  put(J n + I, I, J, value)
 template <class Put>
 __device__ __forceinline__ void restrict_level(const double* z, int N, int n, unsigned full,
                                                Put&& put) {
@@ -618,7 +671,7 @@ __global__ __launch_bounds__(kCoarseWG) void k_coarse(CoarseArgs c, Pcg a, int k
     br[q] = c.in[s.red >= 0 ? at[q] : 0];
     bb[q] = c.in[s.blk >= 0 ? at[q] + 1 - 2 * par : 0];
   }
-  if (check ? pcg_check(a, k) : a.ist[I_DONE] != 0) return;
+  if (check ? pcg_check<kCoarseWG>(a, k) : a.ist[I_DONE] != 0) return;
   for (int e = t; e < c.off[c.nlev]; e += kCoarseWG) buf[e] = 0.0;
   __syncthreads();
 #pragma unroll
@@ -701,45 +754,54 @@ __global__ __launch_bounds__(kBX) void k_init(int problem, double lambda, const 
   partial_store(acc, a.p_rr);
 }
 
-// p = z + beta p_prev (beta = rho_k / rho_{k-1}; p = z at k = 0), q = A p, p.q
+// p = z + beta p_prev (beta = rho_k / rho_{k-1}; p = z at k = 0), q = A p, p.q:
+// 8.4 us at N = 1024 (9.5 with one point a lane and turn)
 template <int TX, int TY>
 __global__ __launch_bounds__(kBX) void k_dir(const double* z, const double* p_prev,
                                              double* p_cur, double* q, int N, double ih2, Pcg a,
                                              int k) {
-  constexpr int W = TX + 2, H = TY + 2;
-  __shared__ double sp[H * W];
+  constexpr int W2 = TX / 2 + 2, H = TY + 2;  // from (i0 - 2, j0 - 1)
+  constexpr int U = (H * W2 + kBX - 1) / kBX;
+  __shared__ double2 sp[H * W2];
   if (a.ist[I_DONE]) return;
-  constexpr int U = (H * W + kBX - 1) / kBX;
   const bool first = k == 0;
   const int tx = tiles_of(N, TX), nt = tx * tiles_of(N, TY);
   double acc = 0.0, beta = 0.0;
+  const Parts<kBX> prho(a.p_rho, first ? 0 : a.np_fine);
+  const double rho_prev = first ? 1.0 : a.sc[S_RHO_PREV];
   for (int t = blockIdx.x; t < nt; t += gridDim.x) {
     const int i0 = t % tx * TX, j0 = t / tx * TY;
-    double zv[U], pv[U];
+    auto pair = [&](int u) { return Pair<W2, H>(u, i0 - 2, j0 - 1, N); };
+    double2 zv[U], pv[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const int64_t p = tile_at<W, H>(u, i0 - 1, j0 - 1, N);
-      zv[u] = z[p < 0 ? 0 : p];
-      pv[u] = first ? 0.0 : p_prev[p < 0 ? 0 : p];
+      const int64_t p = pair(u).at(N);
+      zv[u] = ld_pair(z + p);
+      pv[u] = first ? make_double2(0.0, 0.0) : ld_pair(p_prev + p);
     }
-    if (t == (int)blockIdx.x && !first) beta = sum_parts<1>(a.p_rho, a.np_fine) / a.sc[S_RHO_PREV];
+    if (t == (int)blockIdx.x && !first) beta = prho.template sum<1>() / rho_prev;
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const int e = threadIdx.x + u * kBX;
-      if (e < H * W)
-        sp[e] = tile_at<W, H>(u, i0 - 1, j0 - 1, N) >= 0 ? fma(beta, pv[u], zv[u]) : 0.0;
+      const bool in = pair(u).in;
+      pv[u].x = in ? fma(beta, pv[u].x, zv[u].x) : 0.0;
+      pv[u].y = in ? fma(beta, pv[u].y, zv[u].y) : 0.0;
+      if (e < H * W2) sp[e] = pv[u];
     }
     __syncthreads();
 #pragma unroll
-    for (int u = 0; u < TX * TY / kBX; ++u) {
+    for (int u = 0; u < U; ++u) {
+      const auto g = pair(u);
       const int e = threadIdx.x + u * kBX;
-      const int y = e / TX, x = e % TX, i = i0 + x, j = j0 + y, c = (y + 1) * W + x + 1;
-      if (i < N && j < N) {
-        const double pc = sp[c];
-        const double qv = (4.0 * pc - (((sp[c - 1] + sp[c + 1]) + sp[c - W]) + sp[c + W])) * ih2;
-        p_cur[(int64_t)j * N + i] = pc;
-        q[(int64_t)j * N + i] = qv;
-        acc = fma(pc, qv, acc);
+      if (g.in && g.s >= 1 && g.s <= TX / 2 && g.y >= 1 && g.y <= TY) {
+        const double2 c = pv[u], up = sp[e - W2], dn = sp[e + W2];
+        const double l = sp[e - 1].y, r = sp[e + 1].x;
+        const double q0 = (4.0 * c.x - (((l + c.y) + up.x) + dn.x)) * ih2;
+        const double q1 = (4.0 * c.y - (((c.x + r) + up.y) + dn.y)) * ih2;
+        const int64_t p = g.at(N);
+        st_pair(p_cur + p, c.x, c.y);
+        st_pair(q + p, q0, q1);
+        acc = fma(c.x, q0, fma(c.y, q1, acc));
       }
     }
     __syncthreads();
@@ -815,7 +877,7 @@ __global__ __launch_bounds__(kCoarseWG) void k_solve_small(int problem, double l
       rr = fma(rv, rv, rr);
       if (XREG) x[col][XREG ? q : 0] = 0.0;
     });
-  rr = block_sum(rr, lds[0]);
+  rr = block_sum<kCoarseWG>(rr, lds[0]);
   const double rr0 = rr;
   double rho_prev = 0.0;
   const int last = a.fixed >= 0 ? a.fixed : a.max_iter;
@@ -856,7 +918,7 @@ __global__ __launch_bounds__(kCoarseWG) void k_solve_small(int problem, double l
 #pragma unroll
     for (int col = 0; col < 2; ++col)
       points(col, [&](int, int o, double& rv, double&, double&) { acc = fma(rv, z0[o], acc); });
-    const double rho = block_sum(acc, lds[1]);
+    const double rho = block_sum<kCoarseWG>(acc, lds[1]);
     const double beta = k == 0 ? 0.0 : rho / rho_prev;
     rho_prev = rho;
 #pragma unroll
@@ -873,7 +935,7 @@ __global__ __launch_bounds__(kCoarseWG) void k_solve_small(int problem, double l
         q = (4.0 * pv - four(z0 + o, S)) * ih2;
         acc = fma(pv, q, acc);
       });
-    const double alpha = rho / block_sum(acc, lds[2]);
+    const double alpha = rho / block_sum<kCoarseWG>(acc, lds[2]);
     acc = 0.0;
 #pragma unroll
     for (int col = 0; col < 2; ++col)
@@ -888,7 +950,7 @@ __global__ __launch_bounds__(kCoarseWG) void k_solve_small(int problem, double l
         rv = fma(-alpha, XREG ? qv : (4.0 * pv - four(z0 + o, S)) * ih2, rv);
         acc = fma(rv, rv, acc);
       });
-    rr = block_sum(acc, lds[0]);
+    rr = block_sum<kCoarseWG>(acc, lds[0]);
     ++k;
   }
   if (XREG || k == 0) {

@@ -57,3 +57,33 @@ def test_solve_at_the_slot_counts_of_one_workgroup(N):
     ctx.solve(to_dev(rhs), x)
     assert ctx.last() == (iters, True) and conv
     assert rel_inf(x.cpu().numpy(), ref.reshape(-1)) <= 1e-11
+
+
+def test_cycle_with_more_tiles_than_workgroups():
+    import torch
+    device()
+    from paper_2110_09667_amd import aa
+    N = 1088
+    r = W.normal(N, 6, N * N)
+    ctx = aa.PDE2D(N, aa.PDE_BRATU)
+    z = torch.full((N * N,), np.nan, dtype=torch.float64, device="cuda")
+    ctx.vcycle(to_dev(r), z)
+    ref = P.vcycle(r.reshape(N, N), 1.0 / (N + 1)).reshape(-1)
+    assert rel_inf(z.cpu().numpy(), ref) <= 1e-13
+
+
+def test_solve_into_a_vector_aligned_to_eight_bytes():
+    """The caller's vectors need no more than the alignment of a double."""
+    import torch
+    device()
+    from paper_2110_09667_amd import aa
+    for N in (64, 96, 144, 544):
+        rhs = W.normal(N, 7, N * N)
+        ctx = aa.PDE2D(N, aa.PDE_BRATU)
+        buf = torch.full((2 * N * N + 3,), np.nan, dtype=torch.float64, device="cuda")
+        r, x = buf[1:1 + N * N], buf[N * N + 1 + N % 2:][:N * N]
+        r.copy_(to_dev(rhs))
+        ref, iters, conv = P.pcg(rhs.reshape(N, N), 1.0 / (N + 1), 1e-10, 200)[:3]
+        ctx.solve(r, x)
+        assert ctx.last() == (iters, True) and conv
+        assert rel_inf(x.cpu().numpy(), ref.reshape(-1)) <= 1e-11
