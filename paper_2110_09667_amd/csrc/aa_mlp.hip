@@ -92,7 +92,9 @@ struct FwdArgs {
 // The whole forward pass of 16 rows.  Latency bound (16 workgroups at 256
 // rows): a layer is 16 operand loads per lane in flight from the L2, the next
 // layer's issued before this one's activation function, so a layer costs about
-// one L2 round trip plus the GELU.  At 256 rows: 23 us, where the 64 x 64 GEMM
+// one L2 round trip plus the GELU.  At 256 rows: 17 us (23 with the features read
+// and stored one after another and each layer's bias read behind the next
+// layer's weights; two layers of weights in flight: 17.6), where the 64 x 64 GEMM
 // tiles and elementwise kernels before it took nine launches and 120 us.
 // (Rolling the layer loop, a third of the code, changed nothing: the weights
 // Adam has just rewritten come from beyond the L2.)
@@ -111,10 +113,30 @@ __global__ __launch_bounds__(kChainWG) void k_mlp_forward(FwdArgs a) {
         for (int s = 0; s < 8; ++s)
           b[nb][s] = ld_op(a.wt + layer_w(l), kH, n0 + 16 * nb + li, 32 * s + lk);
   };
+  // (every feature in flight before the first store, which may alias them for
+  // all the compiler knows)
+  static_assert(kRows * kIn % kChainWG == 0, "whole turns");
+  float xv[kRows * kIn / kChainWG];
+#pragma unroll
+  for (int u = 0; u < kRows * kIn / kChainWG; ++u) {
+    const int e = tid + u * kChainWG, r = e / kIn, c = e % kIn, row = r0 + r;
+    const bool in = row < a.batch && c < kNF;
+    const float v = a.x[in ? (size_t)row * kNF + c : 0];
+    xv[u] = in ? v : 0.f;
+  }
+  // (the biases too: loads return in order, and one issued in its layer would
+  // wait for the next layer's weights)
+  float bias[kLayers][2];
+#pragma unroll
+  for (int l = 0; l < kLayers - 1; ++l)
+#pragma unroll
+    for (int nb = 0; nb < 2; ++nb) bias[l][nb] = a.p[layer_b(l) + 32 * w + 16 * nb + li];
+  bias[kLayers - 1][0] = w < 4 ? a.p[layer_b(kLayers - 1) + 16 * w + li] : 0.f;
   load(0);
-  for (int e = tid; e < kRows * kIn; e += kChainWG) {
-    const int r = e / kIn, c = e % kIn, row = r0 + r;
-    const uint16_t v = row < a.batch && c < kNF ? f2bf(a.x[(size_t)row * kNF + c]) : (uint16_t)0;
+#pragma unroll
+  for (int u = 0; u < kRows * kIn / kChainWG; ++u) {
+    const int e = tid + u * kChainWG, r = e / kIn, c = e % kIn, row = r0 + r;
+    const uint16_t v = f2bf(xv[u]);
     act[0][r][c] = v;
     if (row < a.batch) a.h[0][(size_t)row * kIn + c] = v;
   }
@@ -127,11 +149,10 @@ __global__ __launch_bounds__(kChainWG) void k_mlp_forward(FwdArgs a) {
 #pragma unroll
     for (int nb = 0; nb < 2; ++nb) {
       const int n = 32 * w + 16 * nb + li;
-      const float bias = a.p[layer_b(l) + n];
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         const int rr = mfma_row(lane, r), row = r0 + rr;
-        const float z = acc[nb][r] + bias;
+        const float z = acc[nb][r] + bias[l][nb];
         const uint16_t hv = f2bf(gelu_f(z));
         act[(l + 1) & 1][rr][n] = hv;
         if (row < a.batch) {
@@ -153,7 +174,7 @@ __global__ __launch_bounds__(kChainWG) void k_mlp_forward(FwdArgs a) {
   for (int r = 0; r < 4; ++r) {
     const int row = r0 + mfma_row(lane, r);
     if (row < a.batch && n < kNO)
-      a.out[(size_t)row * kNO + n] = acc[0][r] + a.p[layer_b(kLayers - 1) + n];
+      a.out[(size_t)row * kNO + n] = acc[0][r] + bias[kLayers - 1][0];
   }
 }
 
@@ -168,7 +189,7 @@ struct BwdArgs {
 
 // The chain dZ_3 -> dZ_0 of 16 rows: dH = dZ_l W_l^T (W_l's rows have the
 // reduction index fastest), dZ_{l-1} = dH gelu'(z_{l-1}).  As the forward pass;
-// 16 us at 256 rows, 86 us as seven launches.
+// 14.7 us at 256 rows, 86 us as seven launches.
 __global__ __launch_bounds__(kChainWG) void k_mlp_backward(BwdArgs a) {
   __shared__ __align__(16) uint16_t act[2][kRows][kActS];
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
@@ -182,27 +203,38 @@ __global__ __launch_bounds__(kChainWG) void k_mlp_backward(BwdArgs a) {
         if (s < layer_out(l) / 32)
           b[nb][s] = ld_op(a.wb + layer_w(l), layer_out(l), 32 * w + 16 * nb + li, 32 * s + lk);
   };
-  load(kLayers - 1);
-  for (int e = tid; e < kRows * kOutP; e += kChainWG) {
-    const int r = e / kOutP, c = e % kOutP, row = r0 + r;
-    const float v = row < a.batch && c < kNO ? a.dout[(size_t)row * kNO + c] : 0.f;
-    act[1][r][c] = f2bf(v);
-    if (row < a.batch) {
-      a.dz[kLayers - 1][(size_t)row * kOutP + c] = v;
-      a.dzb[kLayers - 1][(size_t)row * kOutP + c] = f2bf(v);
-    }
-  }
-  __syncthreads();
+  float dv[kRows * kOutP / kChainWG];
 #pragma unroll
-  for (int l = kLayers - 1; l >= 1; --l) {
-    float zv[2][4];
+  for (int u = 0; u < kRows * kOutP / kChainWG; ++u) {
+    const int e = tid + u * kChainWG, r = e / kOutP, c = e % kOutP, row = r0 + r;
+    const bool in = row < a.batch && c < kNO;
+    const float v = a.dout[in ? (size_t)row * kNO + c : 0];
+    dv[u] = in ? v : 0.f;
+  }
+  load(kLayers - 1);
+  float zv[kLayers - 1][2][4];  // every layer's, in flight at once
+#pragma unroll
+  for (int l = kLayers - 1; l >= 1; --l)
 #pragma unroll
     for (int nb = 0; nb < 2; ++nb)
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         const int row = r0 + mfma_row(lane, r), n = 32 * w + 16 * nb + li;
-        zv[nb][r] = row < a.batch ? a.z[l - 1][(size_t)row * kH + n] : 0.f;
+        const float z = a.z[l - 1][row < a.batch ? (size_t)row * kH + n : 0];
+        zv[l - 1][nb][r] = row < a.batch ? z : 0.f;
       }
+#pragma unroll
+  for (int u = 0; u < kRows * kOutP / kChainWG; ++u) {
+    const int e = tid + u * kChainWG, r = e / kOutP, c = e % kOutP, row = r0 + r;
+    act[1][r][c] = f2bf(dv[u]);
+    if (row < a.batch) {
+      a.dz[kLayers - 1][(size_t)row * kOutP + c] = dv[u];
+      a.dzb[kLayers - 1][(size_t)row * kOutP + c] = f2bf(dv[u]);
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int l = kLayers - 1; l >= 1; --l) {
     v4f acc[2];
     if (l == kLayers - 1)
       mma_tile<kOutP / 32, 2>(act[l & 1], b, acc);
@@ -214,7 +246,7 @@ __global__ __launch_bounds__(kChainWG) void k_mlp_backward(BwdArgs a) {
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         const int rr = mfma_row(lane, r), row = r0 + rr, n = 32 * w + 16 * nb + li;
-        const float v = acc[nb][r] * gelu_grad_f(zv[nb][r]);
+        const float v = acc[nb][r] * gelu_grad_f(zv[l - 1][nb][r]);
         const uint16_t vb = f2bf(v);
         act[(l - 1) & 1][rr][n] = vb;
         if (row < a.batch) {
