@@ -93,7 +93,8 @@ size_t instance_bytes(int64_t n, int m, bool learned) {
 constexpr size_t kWidePartials = (size_t)(3 * AA_MAX_COLS + 4) * 8192;
 constexpr int64_t kWideTile = 1024;     // rows of a tile of the wide passes
 constexpr int64_t kWideChunks = 512;    // most chunks of an instance
-constexpr int64_t kWideMinN = 512;      // rows from which the cost model takes an instance
+constexpr int64_t kWideMinN = 512;      // rows from which the cost model takes an
+constexpr double kWideMinBytes = 0.7e6; // instance, and bytes of the largest
 constexpr int64_t kWideMaxN = 1 << 30;  // their row indices are 32 bits in the stencil
 
 int64_t wide_tiles(int64_t n) { return (n + kWideTile - 1) / kWideTile; }
@@ -167,19 +168,22 @@ double iter_bytes(const aa_batch* b, int j) {
 // The instances that gain from many workgroups: those with more bytes than a
 // threshold, the one that makes an iteration shortest in this model of both
 // kernels (fitted to 2D tables of 1 to 4096 instances of side 8 to 512).  The
-// persistent kernel takes 45 us and its bytes at 20 GB/s for an instance, the
-// batch as long as its largest (times 1.2 beside others), as its share of the
-// 512 resident workgroups (times 1.7) or as its bytes at 4.8 TB/s; the wide
-// passes take 4.5 us a launch, 0.05 us an instance and the bytes at 5.1 TB/s.
+// persistent kernel takes 45 us and its bytes at 20 GB/s (MGS, whose passes over
+// single columns stay in the L2, at 40) for an instance, the batch as long as its
+// largest (times 1.2 beside others), as its share of the 512 resident workgroups
+// (times 1.7) or as its bytes at 4.8 TB/s; the wide passes take 4.5 us a launch, 0.05 us an instance and the bytes at 5.1 TB/s.
 // Measured, us an iteration, persistent / wide: 8 instances of side 64 to 256
 // 1700 / 115, 32 of 32 to 128 (DCGS-2) 372 / 104, 2000 of 16 to 48 454 / 359,
-// 4096 of 32 to 512 20757 / 20047, one of side 32 60 / 62.
+// 4096 of 32 to 512 20757 / 20047; one of side 24, 48 and 64 at m = 5 46 / 53, 59
+// / 59 and 65 / 60, of side 32 at m = 20 92 / 89; MGS at m = 20 of side 64 136 /
+// 188, of side 96 256 / 183.
 void choose_wide(aa_batch* b) {
   std::vector<int> ord(b->count);
   std::iota(ord.begin(), ord.end(), 0);
   std::stable_sort(ord.begin(), ord.end(),
                    [&](int x, int y) { return iter_bytes(b, x) > iter_bytes(b, y); });
-  constexpr double kFixed = 45e-6, kOne = 20e9, kAll = 4.8e12, kResident = 512.0;
+  constexpr double kFixed = 45e-6, kAll = 4.8e12, kResident = 512.0;
+  const double kOne = b->variant == AA_MGS ? 40e9 : 20e9;
   constexpr double kLaunch = 4.5e-6, kInst = 0.05e-6, kWide = 5.1e12;
   double total = 0.0;
   for (int j : ord) total += iter_bytes(b, j);
@@ -200,8 +204,12 @@ void choose_wide(aa_batch* b) {
   double best = all, wide = 0.0;
   int take = 0;
   for (int i = 0; i < b->count; ++i) {
-    // below 512 rows (one pair a lane) a pass's workgroup is not even filled
-    if (b->n[ord[i]] < kWideMinN || b->n[ord[i]] >= kWideMaxN) break;
+    // below 512 rows (one pair a lane) a pass's workgroup is not even filled;
+    // where the largest has less than 0.7 MB (48^2 at m = 5) the launches cost
+    // more than its one workgroup
+    if (b->n[ord[i]] < kWideMinN || b->n[ord[i]] >= kWideMaxN ||
+        iter_bytes(b, ord[0]) < kWideMinBytes)
+      break;
     wide += iter_bytes(b, ord[i]);
     const double t = cost(wide, i + 1);
     if (t < best && t < (i + 1 < b->count ? 0.7 : 0.97) * all) {
