@@ -386,20 +386,19 @@ typedef struct {
 aa_status aa_batch_set_tiles(aa_batch *b, int pairs);
 
 /* Large instances on many workgroups.  The persistent kernel gives every
- * instance one workgroup, which streams some 20 GB/s; while thousands are
- * active that fills the chip, but once at most `active_max` instances are
- * active (0: a quarter of the compute units) the active instances with
- * n >= min_n leave the persistent kernel and run their iterations on the
- * single-instance grid-wide passes (up to 1024 workgroups each), one
- * instance after another, the remaining ones staying in the persistent
- * kernel.  A split instance keeps its memory, its state and the batch's
- * stopping test (relative residual, iteration cap); its partial sums are
- * taken in another order (results agree to rounding), and a breakdown ends
- * it in the iteration that detects it with x_{i+1} = G(x_i), as aa_step
- * does.  The policy is evaluated when aa_batch_run starts (a wait for the
- * stream); split iterations are enqueued by the host, not replayed as
- * graphs; the learned entry points and the autotuner return every instance
- * to the persistent kernel first.  min_n = 0 disables the split (and
+ * instance one workgroup, which streams some 20 GB/s.  Instances that a cost
+ * model expects to gain run their iterations on grid-wide passes over the
+ * chunks of all of them (plain iterations only; chosen by aa_batch_init).  This
+ * call sets the rule for the tail of a batch: once at most `active_max`
+ * instances are active (0: a quarter of the compute units) the active
+ * instances with n >= min_n join them, the remaining ones staying in the
+ * persistent kernel.  Such an instance keeps its memory, its state and the
+ * batch's stopping test (relative residual, iteration cap); its partial sums
+ * are taken in another order (results agree to rounding), and a breakdown of a
+ * split instance ends it in the iteration that detects it with x_{i+1} =
+ * G(x_i), as aa_step does.  The policy is evaluated when aa_batch_run starts (a
+ * wait for the stream); the learned entry points and the autotuner return
+ * every instance the policy took first.  min_n = 0 disables the split (and
  * returns split instances).  Default: min_n = 65536, active_max = 0. */
 aa_status aa_batch_set_split(aa_batch *b, int64_t min_n, int active_max);
 
