@@ -169,16 +169,23 @@ __device__ inline bool complete(const Small& sm, const Pend& p) {
 }
 
 // PRO: the instance with a pending reduction to complete (kernels run without
-// one carry none of its code).
+// one carry none of its code, and no argument for it: 100 bytes a launch were
+// 4 % of a window of 33 columns of 6042 rows by MGS, 1400 launches).
+struct NoPend {
+  NoPend(const Pend&) {}
+};
 template <bool PRO>
-__device__ __forceinline__ bool ended(const Small& sm, const Pend& p) {
+using PendArg = std::conditional_t<PRO, Pend, NoPend>;
+
+template <bool PRO>
+__device__ __forceinline__ bool ended(const Small& sm, const PendArg<PRO>& p) {
   if (aa_stopped(sm)) return true;
   if constexpr (PRO) return complete(sm, p);
   return false;
 }
 
 template <bool PRO>
-__global__ __launch_bounds__(kWG) void k_dots(DotsArgs a, Small sm, Pend p) {
+__global__ __launch_bounds__(kWG) void k_dots(DotsArgs a, Small sm, PendArg<PRO> p) {
   if (ended<PRO>(sm, p)) return;
   __shared__ double s_acc[kWaves * kMaxRed];
   lds_zero(s_acc, kWaves * kMaxRed);
@@ -190,7 +197,7 @@ __global__ __launch_bounds__(kWG) void k_dots(DotsArgs a, Small sm, Pend p) {
 // Block dot products with per-lane register accumulators (dots_reg_body):
 // KQ-column buckets, one to three right-hand sides.
 template <int KQ, int NR, bool PRO>
-__global__ __launch_bounds__(kWG) void k_dots_reg(DotsArgs a, Small sm, Pend p) {
+__global__ __launch_bounds__(kWG) void k_dots_reg(DotsArgs a, Small sm, PendArg<PRO> p) {
   if (ended<PRO>(sm, p)) return;
   constexpr int STR = NR * KQ + 2;  // nx + ny + nz + xx + xz <= NR KQ + 2
   __shared__ double s_acc[kWaves * STR];
@@ -201,7 +208,7 @@ __global__ __launch_bounds__(kWG) void k_dots_reg(DotsArgs a, Small sm, Pend p) 
 }
 
 template <bool PRO>
-__global__ __launch_bounds__(kWG) void k_update(UpdArgs a, Small sm, Pend p) {
+__global__ __launch_bounds__(kWG) void k_update(UpdArgs a, Small sm, PendArg<PRO> p) {
   if (ended<PRO>(sm, p)) return;
   __shared__ double s_c1[kMaxCols], s_c2[kMaxCols], s_s[kMaxCols];
   __shared__ double s_acc[kWaves * 4];
@@ -218,7 +225,7 @@ __global__ __launch_bounds__(kWG) void k_update(UpdArgs a, Small sm, Pend p) {
 #define AA_CGS2B_PAIR_MAX 32
 #endif
 template <int KMAX, bool PRO>
-__global__ __launch_bounds__(kWG) void k_cgs2b(Cgs2bArgs a, Small sm, Pend p) {
+__global__ __launch_bounds__(kWG) void k_cgs2b(Cgs2bArgs a, Small sm, PendArg<PRO> p) {
   if (ended<PRO>(sm, p)) return;
   __shared__ double s_s[KMAX];
   __shared__ double s_acc[kWaves * KMAX];
@@ -252,7 +259,7 @@ __device__ __forceinline__ void commit_r(const Small& sm, int k, int commit) {
 }
 
 template <int CH, bool PRO>
-__global__ __launch_bounds__(kWG) void k_rotate(RotArgs a, Small sm, Pend p, int commit) {
+__global__ __launch_bounds__(kWG) void k_rotate(RotArgs a, Small sm, PendArg<PRO> p, int commit) {
   if (ended<PRO>(sm, p)) return;
   commit_r(sm, a.k, commit);
   __shared__ double s_c[kMaxCols], s_s[kMaxCols];
@@ -290,7 +297,8 @@ constexpr int kRotChWide = AA_ROT_CH_WIDE;
 constexpr int kRotChMid = AA_ROT_CH_MID;
 
 template <int KMAX, int WAVES, bool PRO>
-__global__ __launch_bounds__(64 * WAVES) void k_rotate_gram(RotArgs a, Small sm, Pend p, int commit) {
+__global__ __launch_bounds__(64 * WAVES) void k_rotate_gram(RotArgs a, Small sm, PendArg<PRO> p,
+                                                              int commit) {
   if (ended<PRO>(sm, p)) return;
   commit_r(sm, a.k, commit);
   // staging rows, then the per-wave pair sums: gram_lds_doubles(gram_cols(a), WAVES)
@@ -339,7 +347,7 @@ __host__ __device__ constexpr int gram_split_lds_doubles(int na) {
 }
 
 template <int, bool PRO>
-__global__ __launch_bounds__(kWG) void k_rotate_gram_split_t(RotArgs a, Small sm, Pend p,
+__global__ __launch_bounds__(kWG) void k_rotate_gram_split_t(RotArgs a, Small sm, PendArg<PRO> p,
                                                              int commit) {
   if (ended<PRO>(sm, p)) return;
   commit_r(sm, a.k, commit);
@@ -361,7 +369,7 @@ __global__ __launch_bounds__(kWG) void k_rotate_gram_split_t(RotArgs a, Small sm
 constexpr int kGramSmall = 8;
 
 template <int NAMAX, bool PRO>
-__global__ __launch_bounds__(kWG) void k_rotate_gram_small(RotArgs a, Small sm, Pend p,
+__global__ __launch_bounds__(kWG) void k_rotate_gram_small(RotArgs a, Small sm, PendArg<PRO> p,
                                                            int commit) {
   if (ended<PRO>(sm, p)) return;
   commit_r(sm, a.k, commit);
@@ -403,7 +411,7 @@ __global__ __launch_bounds__(kWG) void k_history(HistArgs a, Small sm, int given
 }
 
 template <bool PRO>
-__global__ __launch_bounds__(kWG) void k_xupdate(XupdArgs a, Small sm, Pend p) {
+__global__ __launch_bounds__(kWG) void k_xupdate(XupdArgs a, Small sm, PendArg<PRO> p) {
   if (ended<PRO>(sm, p)) {
     // the iteration has ended: x_next = x, except in the step that broke down
     // (breakdown latched, not yet recorded as the end), which returns G(x_i)
