@@ -125,13 +125,22 @@ __global__ __launch_bounds__(kFinWG) void k_finalize(Small sm, Tail t, int nred,
 
 // Completes a pending reduction inside its consumer: every workgroup sums the
 // partials (four values a wave at a time) and runs the tail, the first one as
-// its writer.  Returns true when the iteration has ended.  At n = 32768 a
-// finalize launch is 3 us on the GPU and as much on the host; this is 1 to 1.5 us
-// of each workgroup's time, while the partials are few.
+// its writer.  Returns true when the iteration has ended: before this launch, or
+// by the tail.  At n = 32768 a finalize launch is 3 us on the GPU and as much on
+// the host; this is 1 to 1.5 us of each workgroup's time, while the partials are
+// few.
+//
+// The tails of TAIL_RES and TAIL_NORM write the words that say so (stop state,
+// status) while other workgroups of the launch start, so one thread reads them
+// for its whole workgroup: waves reading for themselves could part, some gone
+// and the others with sums that nobody formed.  (Sums of an iteration that ended
+// before are formed from what the partials hold, and dropped.)
 __device__ inline bool complete(const Small& sm, const Pend& p) {
   __shared__ double red[kPendRed];
+  __shared__ int gone;
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, nw = blockDim.x >> 6;
-  if (p.t.op == TAIL_GRAM) {
+  if (p.t.op == TAIL_GRAM) {  // no workgroup of this launch writes either word
+    if (aa_stopped(sm)) return true;
     // T is read by the next kernel only: each workgroup sums its share of the
     // pairs
     for (int c = blockIdx.x * nw + w; c < p.nred; c += gridDim.x * nw) {
@@ -143,6 +152,7 @@ __device__ inline bool complete(const Small& sm, const Pend& p) {
     }
     return false;
   }
+  const int done = threadIdx.x == 0 && sm.stop ? sm.stop->done | *sm.status : 0;
   for (int c0 = 4 * w; c0 < p.nred; c0 += 4 * nw) {
     double s[4] = {0.0, 0.0, 0.0, 0.0};
     for (int g = lane; g < p.G; g += 4 * 64) {  // sixteen loads in flight
@@ -161,7 +171,9 @@ __device__ inline bool complete(const Small& sm, const Pend& p) {
     const double r = multi_reduce<4>(s);
     if (lane < 4 && c0 + lane < p.nred) red[c0 + lane] = r;
   }
+  if (threadIdx.x == 0) gone = done;
   __syncthreads();
+  if (gone) return true;
   run_tail(sm, p.t, red, blockIdx.x == 0);
   if (p.t.op == TAIL_RES) return sm.stop && stop_hit(sm, p.t, red[0]);
   __syncthreads();
@@ -179,9 +191,8 @@ using PendArg = std::conditional_t<PRO, Pend, NoPend>;
 
 template <bool PRO>
 __device__ __forceinline__ bool ended(const Small& sm, const PendArg<PRO>& p) {
-  if (aa_stopped(sm)) return true;
   if constexpr (PRO) return complete(sm, p);
-  return false;
+  else return aa_stopped(sm);
 }
 
 template <bool PRO>
