@@ -142,12 +142,17 @@ struct Parts {
 
 // The stopping test before iteration k (every workgroup decides alike; the
 // first records it, and at k = 0 keeps r.r of the right-hand side).  Returns
-// true when the solve has ended.
+// true when the solve has ended.  The first workgroup may record the end while
+// others start, so one thread reads it for its whole workgroup: waves reading
+// for themselves could part, some gone and the others with a sum that lacks
+// theirs.
 template <int NT>
 __device__ __forceinline__ bool pcg_check(const Pcg& a, int k) {
+  __shared__ int ended;
   const Parts<NT> parts(a.p_rr, a.np_fine);
-  if (a.ist[I_DONE]) return true;
-  const double rr = parts.template sum<0>();
+  if (threadIdx.x == 0) ended = a.ist[I_DONE];
+  const double rr = parts.template sum<0>();  // (its barrier also orders `ended`)
+  if (ended) return true;
   const double rr0 = k == 0 ? rr : a.sc[S_RR0];
   if (k == 0 && blockIdx.x == 0 && threadIdx.x == 0) a.sc[S_RR0] = rr;
   bool stop;
