@@ -416,8 +416,14 @@ aa_status aa_batch_split_count(const aa_batch *b, int *count);
  * looked up first in, and afterwards appended to, a text file of lines
  * "<gcn arch> <workload signature> <grid> <order> <pairs> <ms per
  * iteration>"; the signature hashes the format, the variant, the flags and
- * every instance's (n, m, dim).  A cache hit applies the stored schedule and
- * runs nothing.  best may be NULL.  Waits for the stream. */
+ * every instance's (n, m, dim) and part in the trials.  A cache hit applies the
+ * stored schedule and runs nothing.  The schedule is the persistent kernel's:
+ * the trials of a learned batch, whose entry points use no other, run every
+ * instance there, those of a plain batch leave the instances with many
+ * workgroups to their passes (see aa_batch_set_split).  Where that leaves it no
+ * instance, the schedule stays as set: best holds it with trials = 1 and the
+ * time of one run, and the cache is not written.  best may be NULL.  Waits for
+ * the stream. */
 aa_status aa_batch_autotune(aa_batch *b, int iters, const char *cache_path,
                             aa_batch_schedule *best);
 

@@ -123,7 +123,8 @@ void drop_graph(aa_batch* b) {
   b->exec_iters = 0;
 }
 
-hipError_t enqueue_mode(aa_batch* b, int mode, float dscale) {
+// all: the wide instances too (plain mode leaves them out otherwise).
+hipError_t enqueue_mode(aa_batch* b, int mode, float dscale, bool all = false) {
   BatchArgs a{};
   a.inst = b->d_inst;
   a.state = b->d_state;
@@ -136,7 +137,7 @@ hipError_t enqueue_mode(aa_batch* b, int mode, float dscale) {
   a.max_iter = b->max_iter;
   a.ov_iter = -1;
   a.mode = mode;
-  a.skip = mode == BM_PLAIN && b->nwide > 0 ? b->d_skip : nullptr;
+  a.skip = mode == BM_PLAIN && b->nwide > 0 && !all ? b->d_skip : nullptr;
   a.feat = b->d_feat;
   a.out = b->d_out;
   a.dout = b->d_dout;
@@ -346,13 +347,14 @@ aa_status update_split(aa_batch* b) {
   return changed ? plan_wide(b) : AA_OK;
 }
 
-hipError_t enqueue(aa_batch* b, int iters) {
+// all: every instance in the persistent kernel.
+hipError_t enqueue(aa_batch* b, int iters, bool all = false) {
   for (int i = 0; i < iters; ++i) {
-    if (b->nwide < b->count) {
-      const hipError_t e = enqueue_mode(b, BM_PLAIN, 0.f);
+    if (all || b->nwide < b->count) {
+      const hipError_t e = enqueue_mode(b, BM_PLAIN, 0.f, all);
       if (e != hipSuccess) return e;
     }
-    if (b->nwide > 0) {
+    if (!all && b->nwide > 0) {
       const hipError_t e = enqueue_wide(b);
       if (e != hipSuccess) return e;
     }
@@ -528,12 +530,19 @@ aa_status aa_batch_autotune(aa_batch* b, int iters, const char* cache_path,
   // the split policy's instances go back first: the schedule is chosen for
   // the batch as it starts
   if (merge_split(b) != AA_OK) return AA_EHIP;
+  // The schedule is the persistent kernel's.  A learned batch's entry points run
+  // every instance there, a plain run those that are not wide; so do the trials.
+  const bool all = b->learned;
   int dev = 0;
   hipDeviceProp_t prop;
   if (hipGetDevice(&dev) != hipSuccess || hipGetDeviceProperties(&prop, dev) != hipSuccess)
     return AA_EHIP;
   const int cus = prop.multiProcessorCount > 0 ? prop.multiProcessorCount : 256;
-  // FNV-1a over the workload: variant, flags, every instance's (n, m, dim)
+  // FNV-1a over the workload: variant, flags, every instance's (n, m, dim) and
+  // whether the trials leave it out
+  std::vector<char> out(b->count, 0);
+  if (!all)
+    for (int j : b->cost_wide) out[j] = 1;
   uint64_t sig = 1469598103934665603ull;
   auto mix = [&](uint64_t v) {
     for (int i = 0; i < 8; ++i) {
@@ -541,13 +550,14 @@ aa_status aa_batch_autotune(aa_batch* b, int iters, const char* cache_path,
       sig *= 1099511628211ull;
     }
   };
-  mix(2u);  // cache format: grid, order, row pairs
+  mix(3u);  // cache format: grid, order, row pairs; instances left out
   mix((uint64_t)b->variant);
   mix((uint64_t)b->flags);
   for (int j = 0; j < b->count; ++j) {
     mix((uint64_t)b->n[j]);
     mix((uint64_t)b->m[j]);
     mix((uint64_t)b->dim[j]);
+    mix((uint64_t)out[j]);
   }
   char sigs[32];
   snprintf(sigs, sizeof sigs, "%016llx", (unsigned long long)sig);
@@ -584,6 +594,22 @@ aa_status aa_batch_autotune(aa_batch* b, int iters, const char* cache_path,
   }
   aa_status st = AA_OK;
   aa_batch_schedule win{0, 0, 1e300, 0, 4};
+  auto trial = [&](float& ms) {
+    return hipEventRecord(e0, b->stream) == hipSuccess && enqueue(b, iters, all) == hipSuccess &&
+           hipEventRecord(e1, b->stream) == hipSuccess && hipEventSynchronize(e1) == hipSuccess &&
+           hipEventElapsedTime(&ms, e0, e1) == hipSuccess;
+  };
+  if (!all && b->nwide == b->count) {
+    // no instance in the persistent kernel: nothing to choose.  The schedule
+    // stays, timed once, and is no entry of the cache.
+    float ms = 0.f;
+    const bool ok = trial(ms);
+    (void)hipEventDestroy(e0);
+    (void)hipEventDestroy(e1);
+    if (!ok) return AA_EHIP;
+    if (best) *best = aa_batch_schedule{b->grid, b->order_mode, ms / iters, 1, b->pairs};
+    return AA_OK;
+  }
   // tiles (row pairs per lane: 4 or 2) x persistent workgroups per compute
   // unit x instance order
   for (int pr = 4; pr >= 2 && st == AA_OK; pr -= 2) {
@@ -595,9 +621,7 @@ aa_status aa_batch_autotune(aa_batch* b, int iters, const char* cache_path,
         st = aa_batch_set_schedule(b, g, o, 0);
         if (st != AA_OK) break;
         float ms = 0.f;
-        if (hipEventRecord(e0, b->stream) != hipSuccess || enqueue(b, iters) != hipSuccess ||
-            hipEventRecord(e1, b->stream) != hipSuccess || hipEventSynchronize(e1) != hipSuccess ||
-            hipEventElapsedTime(&ms, e0, e1) != hipSuccess) {
+        if (!trial(ms)) {
           st = AA_EHIP;
           break;
         }
