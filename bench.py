@@ -379,9 +379,9 @@ def batched_run(probs, ms, variant, tol, cap, chunk, stream, net=None, steady=20
 
 def batched_tail(variant, takes=(8, 32, 128), fuse=0, steady=20):
     """The tail of a batch: only the `take` largest instances of the batched
-    table still active.  Steady time per iteration with the split policy off
-    (the cost model alone decides which instances leave the persistent kernel)
-    and with it on (every instance on many workgroups)."""
+    table still active.  Steady time per iteration with every instance in the
+    persistent kernel (one workgroup each) and with the split policy on (every
+    instance on many workgroups)."""
     import torch
     import aa_workloads as W
     from paper_2110_09667_amd import aa

@@ -398,8 +398,11 @@ aa_status aa_batch_set_tiles(aa_batch *b, int pairs);
  * split instance ends it in the iteration that detects it with x_{i+1} =
  * G(x_i), as aa_step does.  The policy is evaluated when aa_batch_run starts (a
  * wait for the stream); the learned entry points and the autotuner return
- * every instance the policy took first.  min_n = 0 disables the split (and
- * returns split instances).  Default: min_n = 65536, active_max = 0. */
+ * every instance the policy took first.  min_n = 0 disables both, the cost
+ * model and the split: every instance goes back to one workgroup, which sums
+ * it by itself whatever the rest of the batch is (a later min_n > 0 brings the
+ * cost model's choice back; a change between the two waits for the stream).
+ * Default: min_n = 65536, active_max = 0. */
 aa_status aa_batch_set_split(aa_batch *b, int64_t min_n, int active_max);
 
 /* Instances currently on the split path (as of the last aa_batch_run). */

@@ -533,8 +533,9 @@ class AABatch:
 
     def set_split(self, min_n: int = 65536, active_max: int = 0):
         """Move active instances with n >= min_n onto the grid-wide passes
-        once at most active_max are active (0: one per compute unit; min_n
-        = 0 never)."""
+        once at most active_max are active (0: a quarter of the compute
+        units).  min_n = 0: every instance stays with one workgroup, those
+        of the cost model too."""
         _check(lib().aa_batch_set_split(self.b, min_n, active_max), "aa_batch_set_split")
 
     def split_count(self) -> int:

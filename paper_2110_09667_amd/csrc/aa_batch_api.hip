@@ -48,7 +48,7 @@ struct aa_batch {
   // instances with many workgroups each (aa_batch_wide.hip): those the cost
   // model takes out of the persistent kernel for good, and those the split
   // policy adds once few are active
-  int64_t split_min_n = 65536;  // 0: never
+  int64_t split_min_n = 65536;  // 0: never, nor the cost model's
   int split_active_max = 0;     // split when at most this many are active (0: CUs / 4)
   std::vector<int> cost_wide, split;
   std::vector<BInst> hinst;      // host copies of the descriptors
@@ -221,6 +221,12 @@ void choose_wide(aa_batch* b) {
   b->cost_wide.assign(ord.begin(), ord.begin() + take);
 }
 
+// The cost model's choice, none while aa_batch_set_split has switched off.
+const std::vector<int>& cost_set(const aa_batch* b) {
+  static const std::vector<int> none;
+  return b->split_min_n > 0 ? b->cost_wide : none;
+}
+
 // Chunks of every wide instance (largest first), their partials, the tables.
 // Chunks are as long as leaves about 4096 of them, at most 16 tiles, longer
 // where the tables or the partials would not hold them; instances that even
@@ -228,7 +234,7 @@ void choose_wide(aa_batch* b) {
 aa_status plan_wide(aa_batch* b) {
   drop_graph(b);
   std::vector<int> set = b->split;
-  for (int j : b->cost_wide)
+  for (int j : cost_set(b))
     if (std::find(b->split.begin(), b->split.end(), j) == b->split.end()) set.push_back(j);
   std::stable_sort(set.begin(), set.end(),
                    [&](int x, int y) { return iter_bytes(b, x) > iter_bytes(b, y); });
@@ -505,10 +511,12 @@ aa_status aa_batch_set_schedule(aa_batch* b, int grid, int order, int use_graph)
 
 aa_status aa_batch_set_split(aa_batch* b, int64_t min_n, int active_max) {
   if (!b || min_n < 0 || active_max < 0) return AA_EINVAL;
+  const bool was_on = b->split_min_n > 0, on = min_n > 0;
   b->split_min_n = min_n;
   b->split_active_max = active_max;
-  if (min_n == 0 && merge_split(b) != AA_OK) return AA_EHIP;
-  return AA_OK;
+  if (on == was_on) return AA_OK;
+  if (!on) b->split.clear();
+  return plan_wide(b);
 }
 
 aa_status aa_batch_split_count(const aa_batch* b, int* count) {
@@ -542,7 +550,7 @@ aa_status aa_batch_autotune(aa_batch* b, int iters, const char* cache_path,
   // whether the trials leave it out
   std::vector<char> out(b->count, 0);
   if (!all)
-    for (int j : b->cost_wide) out[j] = 1;
+    for (int j : cost_set(b)) out[j] = 1;
   uint64_t sig = 1469598103934665603ull;
   auto mix = [&](uint64_t v) {
     for (int i = 0; i < 8; ++i) {
