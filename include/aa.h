@@ -561,6 +561,8 @@ aa_status aa_em_apply(const aa_em_mixture *h_mix, const double *d_x, int64_t nsa
 typedef struct aa_pde2d aa_pde2d;
 enum { AA_PDE_HEAT_NL1 = 1, AA_PDE_HEAT_NL2 = 2, AA_PDE_BRATU = 3 };
 aa_status aa_pde2d_workspace_size(int64_t N, int max_iter, size_t *bytes);
+/* Waits for `stream` (unless it is being captured): what later calls read of
+ * the workspace is in place, whatever stream they use. */
 aa_status aa_pde2d_init(aa_pde2d **ctx, int64_t N, int problem, double lambda, double tol,
                         int max_iter, void *d_workspace, size_t bytes, void *stream);
 /* d_out = G(d_u); d_b: the heat problems' source f at the grid points (N^2

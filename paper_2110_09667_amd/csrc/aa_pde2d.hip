@@ -1302,7 +1302,14 @@ aa_status aa_pde2d_init(aa_pde2d** ctx, int64_t N, int problem, double lambda, d
     hipLaunchKernelGGL(k_matrix, dim3(n * n), dim3(kCoarseWG), 0, c->st,
                        coarse_args(c, c->first_mat, c->nlev, 0), c->mat);
   }
-  if (hipGetLastError() != hipSuccess) {
+  // every later call reads the matrix, on whatever stream the caller sets then:
+  // wait for it here (a stream being captured runs nothing yet)
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  hipError_t e = hipGetLastError();
+  if (e == hipSuccess && c->st) e = hipStreamIsCapturing(c->st, &cap);
+  if (e == hipSuccess && c->first_mat < c->nlev && cap == hipStreamCaptureStatusNone)
+    e = hipStreamSynchronize(c->st);
+  if (e != hipSuccess) {
     free(c);
     return AA_EHIP;
   }
