@@ -156,6 +156,9 @@ __device__ __forceinline__ double multi_reduce(double (&v)[N]) {
 #endif
 
 typedef double f64x2 __attribute__((ext_vector_type(2)));
+// the same at the alignment of a double (a caller's vector may start anywhere):
+// still one 16-byte access
+typedef double f64x2_any __attribute__((ext_vector_type(2), aligned(8)));
 
 // One streamed 16-byte pair.
 __device__ __forceinline__ f64x2 ld2v(const double2* p) {

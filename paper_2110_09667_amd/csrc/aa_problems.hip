@@ -203,7 +203,7 @@ __global__ __launch_bounds__(kEmWG) void k_em_broadcast(const double* __restrict
   const double a = ph == 0 ? g0 : ph == 1 ? g1 : g2, b = ph == 0 ? g1 : ph == 1 ? g2 : g0;
   const int64_t npair = n / 2, stride = (int64_t)gridDim.x * kEmWG;
   for (int64_t r = first; r < npair; r += stride)
-    *reinterpret_cast<f64x2*>(out + 2 * r) = f64x2{a, b};
+    *reinterpret_cast<f64x2_any*>(out + 2 * r) = f64x2_any{a, b};
   if ((n & 1) && first == 0) out[n - 1] = g2;  // n is a multiple of three
 }
 
