@@ -280,9 +280,12 @@ typedef enum {
  * enqueues is bracketed by hipEvents on the context's stream, with one more
  * event between a streaming pass and its finalize kernel, so the pass and the
  * finalize are timed apart (events are created on the first enable; no device
- * memory is allocated).  Event records order the stream more strictly than
- * plain launches, so profiled steps run slightly slower than unprofiled
- * ones.  Disabling or aa_profile_reset discards what was recorded. */
+ * memory is allocated).  Meanwhile aa_step runs every kind as a launch of its
+ * own, where it otherwise computes the rotations beside the history pass and,
+ * for short vectors, finalizes reductions and scales in the passes that follow;
+ * event records also order the stream more strictly than plain launches: so
+ * profiled steps are slower than unprofiled ones.  Disabling or
+ * aa_profile_reset discards what was recorded. */
 aa_status aa_profile_enable(aa_ctx *ctx, int enable);
 
 /* Totals for one kernel kind since the last reset: elapsed milliseconds

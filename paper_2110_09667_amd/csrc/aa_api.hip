@@ -409,7 +409,8 @@ aa_status qr_add_impl(aa_ctx* c, const double* v, const double* f = nullptr,
 // pairs per 4 rows instead of 10).  The standalone QRDelete refreshes all of T.
 //
 // pend (inside a step): the history pass has computed the rotations (R after
-// them in Rg; not with the T transform) and its reduction may be pending.
+// them in Rg; not with the T transform, nor while profiling) and its reduction
+// may be pending.
 aa_status qr_delete_impl(aa_ctx* c, bool refresh_next, Pend* pend = nullptr) {
   const int k = c->k;
   if (k <= 0) return AA_ESTATE;
@@ -421,7 +422,7 @@ aa_status qr_delete_impl(aa_ctx* c, bool refresh_next, Pend* pend = nullptr) {
   // kernel (no reduction); otherwise the rotation pass refreshes it.
   const bool transform = c->variant == AA_ICWY && (c->flags & AA_ICWY_T_TRANSFORM);
   hipError_t e = hipSuccess;
-  const bool commit = pend && !transform;
+  const bool commit = pend && !transform && !c->prof_on;
   if (!commit) {
     e = launch_pending(c->sm, pend, c->stream);  // the stopping test, before R changes
     if (e == hipSuccess)
@@ -490,6 +491,11 @@ aa_status fused_delete_add(aa_ctx* c, const double* v, const double* f, bool* rh
   const int k = c->k, kk = k - 1;
   const int naug = f ? 2 : 1;
   const hipStream_t st = c->stream;
+  hipError_t e = hipSuccess;
+  if (c->prof_on) {  // (the history pass has not computed the rotations)
+    e = timed(c, AA_K_GIVENS, 0, [&] { return launch_givens(c->sm, k, st); });
+    if (e != hipSuccess) return AA_EHIP;
+  }
   RotArgs r{c->Q, c->ldq, c->n, k, c->sm.givens, 1, v, f, naug};
   const int na = kk + naug;
   const int64_t pairs = (int64_t)na * (na - 1) / 2;
@@ -499,8 +505,8 @@ aa_status fused_delete_add(aa_ctx* c, const double* v, const double* f, bool* rh
   tg.inner = tg.op;
   tg.op = TAIL_GRAM_ADD;
   tg.gram_t = c->variant == AA_ICWY ? 1 : 0;
-  const hipError_t e = timed(c, AA_K_ROTATE, 2 * k - 1 + naug, [&] {
-    return launch_rotate(r, c->sm, tg, grid_rows(c, gmax), st, pend, true);
+  e = timed(c, AA_K_ROTATE, 2 * k - 1 + naug, [&] {
+    return launch_rotate(r, c->sm, tg, grid_rows(c, gmax), st, pend, !c->prof_on);
   });
   if (e != hipSuccess) return AA_EHIP;
   c->syncs_del += 1;
@@ -788,9 +794,10 @@ static aa_status step_enqueue(aa_ctx* c, const double* x, const double* g,
   tr.stop_mode = c->stop_mode;
   tr.stop_tol = c->stop_tol;
   tr.m_i = c->m_i;
-  // Reductions wait for the pass that uses them (not while profiling, which
-  // times passes and finalizes apart); an extra workgroup of the history pass
-  // computes QRDelete's rotations; the division by R_kk joins the next pass.
+  // Reductions wait for the pass that uses them; an extra workgroup of the
+  // history pass computes QRDelete's rotations; the division by R_kk joins the
+  // next pass.  While profiling, which times every kind apart, each is a launch
+  // of its own.
   Pend wait{};
   Pend* pend = &wait;
   struct Slots {  // without slots every reduction is finalized at once
@@ -806,7 +813,7 @@ static aa_status step_enqueue(aa_ctx* c, const double* x, const double* g,
   const bool transform = c->variant == AA_ICWY && (c->flags & AA_ICWY_T_TRANSFORM);
   const bool fuse_del = i > m && fuse_delete_ok(c->variant) && (c->flags & AA_FUSE_DELETE) &&
                         c->k >= 2 && c->k - 1 + ((c->flags & AA_FUSE_RHS) ? 2 : 1) <= 64;
-  const int givens_k = fuse_del || (del && !transform) ? c->k : 0;
+  const int givens_k = !c->prof_on && (fuse_del || (del && !transform)) ? c->k : 0;
   if (timed(c, AA_K_HISTORY, 8, [&] {
         return launch_history(h, c->sm, tr, G, st, pend, givens_k);
       }) != hipSuccess)
