@@ -372,7 +372,7 @@ __global__ __launch_bounds__(kWG) void k_scale(WideArgs a) {
 // iteration with x_{i+1} = G(x_i); any other goes on and is ended by the next
 // iteration's test.
 __device__ __forceinline__ bool broken_now(const WideArgs& a, const BInst& I, int j) {
-  return a.split[j] == 2 && *I.sm.status != AA_OK;
+  return a.split[j] == kWideSplit && *I.sm.status != AA_OK;
 }
 
 __global__ __launch_bounds__(kWG) void k_xupdate(WideArgs a) {

@@ -49,8 +49,6 @@ __device__ __forceinline__ double sum_partials(const double* __restrict__ p, int
   return wave_sum(s);
 }
 
-// Fixed-order sum of the G partials of each of the nred values (one wave per
-// value, two values per wave in flight), then the dense tail.
 // Sums of the G partials of each value, one wave per value in the same fixed
 // order as k_finalize's (bitwise the same sums), stored after the partials
 // at partials[nred * G + c].  For the wide ICWY Gram (over a thousand values
@@ -65,7 +63,9 @@ __global__ __launch_bounds__(kWG) void k_sum_partials(Small sm, int nred, int G)
   if (lane == 0) sm.partials[(size_t)nred * G + c] = s;
 }
 
-// pre: the sums were formed by k_sum_partials.
+// Fixed-order sum of the G partials of each of the nred values (one wave per
+// value, two values per wave in flight), then the dense tail.  pre: the sums
+// were formed by k_sum_partials.
 __global__ __launch_bounds__(kFinWG) void k_finalize(Small sm, Tail t, int nred, int G, int pre) {
   __shared__ double red[kMaxRedAll];
   if (sm.stop) {

@@ -29,7 +29,6 @@ __device__ __forceinline__ uint16_t f2bf(float x) {
   u += 0x7fffu + ((u >> 16) & 1u);
   return (uint16_t)(u >> 16);
 }
-__device__ __forceinline__ float bf2f(uint16_t b) { return __uint_as_float((uint32_t)b << 16); }
 
 // Operand and result layout of v_mfma_f32_16x16x32_bf16: lane l supplies
 // A[l % 16][8 (l / 16) + e] and B[8 (l / 16) + e][l % 16], e < 8, and
