@@ -760,11 +760,12 @@ struct StepScope {
 
 // Longest vectors whose small reductions wait for their consumer and whose
 // column w is divided by R_kk in the pass that reads it next.  There an
-// iteration is a chain of launches: us an iteration without and with, 32^3 m =
-// 10 61.3 / 54.9, 64^3 m = 3 (MGS) 64.2 / 53.2, 700^2 m = 10 111 / 100.  Beyond,
-// hundreds of partials a value cost every workgroup what the finalize launch
-// did (1000^2 137 / 137, 1.5 M rows 1112 -> 1212 us a solve), and the division
-// costs a read stream more than a pass of its own (256^3: 39.6 -> 40.2 ms).
+// iteration is a chain of launches: us an iteration (map included) without and
+// with both, 32^3 m = 10 60 to 69 / 53, 64^3 m = 3 (MGS) 63 to 68 / 52, 700^2 m =
+// 10 113 / 101, 1000^2 m = 8 135 / 135.  Beyond, hundreds of partials a value
+// cost every workgroup as much as the finalize launch, and the division costs
+// a read stream more than a pass of its own: both together, 1.5 M rows 1112 ->
+// 1212 us a solve, 256^3 39.6 -> 40.2 ms (each alone: not measured).
 constexpr int64_t kWaitMaxN = 1 << 19;
 
 // One iteration of Alg. 1 enqueued kernel by kernel (host sequencing).

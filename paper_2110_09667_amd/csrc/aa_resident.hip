@@ -461,7 +461,11 @@ hipError_t launch_shape(const StepArgs& a, int variant, hipStream_t st) {
 }  // namespace res
 
 // Shapes: at most 40 doubles of Q per lane, which with the iteration's other
-// vectors fills the 256 registers of a lane of eight resident waves.
+// vectors fills the 256 registers of a lane of eight resident waves.  (DCGS-2
+// keeps one more vector, the column it reorthogonalizes: its widest instance, 8
+// rows a lane and 5 columns, spills 104 registers and takes 29 us where the
+// other variants take 20 to 21 in the same trace; the step with its vectors in
+// memory took 46.  No other instance spills vector registers.)
 bool resident_fits(int64_t n, int m) {
   return (n <= 1024 && m <= 20) || (n <= 2048 && m <= 10) || (n <= 4096 && m <= 5);
 }
