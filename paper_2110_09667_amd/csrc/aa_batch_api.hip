@@ -232,6 +232,8 @@ const std::vector<int>& cost_set(const aa_batch* b) {
 // where the tables or the partials would not hold them; instances that even
 // one chunk each does not fit stay in the persistent kernel.
 aa_status plan_wide(aa_batch* b) {
+  // a replay enqueued before may still run: it ends before its graph goes
+  if (b->exec && hipStreamSynchronize(b->stream) != hipSuccess) return AA_EHIP;
   drop_graph(b);
   std::vector<int> set = b->split;
   for (int j : cost_set(b))

@@ -54,3 +54,29 @@ def test_off_is_one_workgroup_an_instance(variant):
     lrn.read()
     for j in range(len(probs)):
         assert np.array_equal(lrn.x[j].cpu().numpy(), off[j]), j
+
+
+def test_switched_while_a_replay_is_enqueued():
+    """Runs replayed as graphs and not waited for, the switch thrown between them:
+    each change of the wide set lets the replay end first, and the iterates are
+    those of waited-for runs bit for bit."""
+    import torch
+    device()
+    from paper_2110_09667_amd import aa
+    probs = problems((180, 31, 77, 150))
+    got = []
+    for wait in (True, False):
+        stream = torch.cuda.Stream()
+        with torch.cuda.stream(stream):
+            b = aa.AABatch(probs, [M] * len(probs), "icwy", tol=0.0, max_iter=10 ** 9,
+                           stream=stream)
+            for min_n in (65536, 0, 65536, 1, 0):
+                b.set_split(min_n, 64)
+                b.run(6)
+                if wait:
+                    stream.synchronize()
+            st, _ = b.read()
+        assert all(s.iter == 30 and s.status == 0 for s in st)
+        got.append([x.cpu().numpy() for x in b.x])
+    for x, y in zip(*got):
+        assert np.isfinite(x).all() and np.array_equal(x, y)
